@@ -111,6 +111,37 @@ lshmoe_status static_scratch(void** out) {
   return LSHMOE_OK;
 }
 
+// first_bin, spins: see GroupPlan; spins = 0 keeps the plan's values.
+lshmoe_status compress(const void* tokens, const int32_t* expert, const uint64_t* bucket, int64_t T, int32_t d,
+                       int32_t k, int32_t E, int32_t L, int32_t r, lshmoe_dtype dtype, void* centroids,
+                       int32_t* seg_offsets, int32_t* seg_expert, int32_t* expert_offsets, int32_t* perm,
+                       int32_t* seg_of, int32_t* num_segments, void* workspace, size_t workspace_bytes,
+                       void* stream, uint32_t first_bin, uint32_t spins) {
+  if (!tokens || !expert || !bucket || !centroids || !seg_offsets || !seg_expert || !expert_offsets || !perm ||
+      !seg_of || !num_segments)
+    return fail(LSHMOE_ERR_NULL, "an input or output pointer is NULL");
+  lshmoe::GroupPlan plan;
+  if (lshmoe_status st = check_compress_shape(T, d, k, E, L, r, (int)dtype, &plan)) return st;
+  if (!workspace) return fail(LSHMOE_ERR_WORKSPACE, "workspace is NULL (%zu bytes needed)", plan.total_bytes);
+  if (((uintptr_t)workspace & 255u) != 0) return fail(LSHMOE_ERR_WORKSPACE, "workspace is not 256-byte aligned");
+  if (workspace_bytes < plan.total_bytes)
+    return fail(LSHMOE_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, plan.total_bytes);
+  if (spins != 0) {
+    plan.first_bin = first_bin;
+    plan.spins = spins;
+  }
+  hipStream_t s = (hipStream_t)stream;
+  hipError_t e = lshmoe::launch_group(plan, expert, bucket, k, E, seg_offsets, seg_expert, expert_offsets, perm, seg_of,
+                                      num_segments, (char*)workspace, s);
+  if (e != hipSuccess) return hip_fail("group launch", e);
+  e = lshmoe::launch_centroid(tokens, perm, seg_offsets, seg_of, num_segments, centroids,
+                              (float*)((char*)workspace + plan.off_partial),
+                              (uint32_t*)((char*)workspace + plan.off_counters), plan.N, k, d, dtype == LSHMOE_BF16,
+                              /*mean=*/true, s);
+  if (e != hipSuccess) return hip_fail("centroid launch", e);
+  return ok();
+}
+
 }  // namespace
 
 extern "C" {
@@ -192,25 +223,22 @@ lshmoe_status lshmoe_compress(const void* tokens, const int32_t* expert, const u
                               int32_t* seg_offsets, int32_t* seg_expert, int32_t* expert_offsets, int32_t* perm,
                               int32_t* seg_of, int32_t* num_segments, void* workspace, size_t workspace_bytes,
                               void* stream) {
-  if (!tokens || !expert || !bucket || !centroids || !seg_offsets || !seg_expert || !expert_offsets || !perm ||
-      !seg_of || !num_segments)
-    return fail(LSHMOE_ERR_NULL, "an input or output pointer is NULL");
-  lshmoe::GroupPlan plan;
-  if (lshmoe_status st = check_compress_shape(T, d, k, E, L, r, (int)dtype, &plan)) return st;
-  if (!workspace) return fail(LSHMOE_ERR_WORKSPACE, "workspace is NULL (%zu bytes needed)", plan.total_bytes);
-  if (((uintptr_t)workspace & 255u) != 0) return fail(LSHMOE_ERR_WORKSPACE, "workspace is not 256-byte aligned");
-  if (workspace_bytes < plan.total_bytes)
-    return fail(LSHMOE_ERR_WORKSPACE, "workspace has %zu bytes, %zu needed", workspace_bytes, plan.total_bytes);
-  hipStream_t s = (hipStream_t)stream;
-  hipError_t e = lshmoe::launch_group(plan, expert, bucket, k, E, seg_offsets, seg_expert, expert_offsets, perm, seg_of,
-                                      num_segments, (char*)workspace, s);
-  if (e != hipSuccess) return hip_fail("group launch", e);
-  e = lshmoe::launch_centroid(tokens, perm, seg_offsets, seg_of, num_segments, centroids,
-                              (float*)((char*)workspace + plan.off_partial),
-                              (uint32_t*)((char*)workspace + plan.off_counters), plan.N, k, d, dtype == LSHMOE_BF16,
-                              /*mean=*/true, s);
-  if (e != hipSuccess) return hip_fail("centroid launch", e);
-  return ok();
+  return compress(tokens, expert, bucket, T, d, k, E, L, r, dtype, centroids, seg_offsets, seg_expert, expert_offsets, perm,
+                  seg_of, num_segments, workspace, workspace_bytes, stream, 0, 0);
+}
+
+// Not part of the ABI (no header declares it): lshmoe_compress with the workgroups of the bins below first_bin leaving
+// at once and the others looking `spins` times at an open bin before they try to take it over, so that a test can
+// have bins taken over.
+lshmoe_status lshmoe_test_compress_takeover(const void* tokens, const int32_t* expert, const uint64_t* bucket, int64_t T,
+                                            int32_t d, int32_t k, int32_t E, int32_t L, int32_t r, lshmoe_dtype dtype,
+                                            void* centroids, int32_t* seg_offsets, int32_t* seg_expert,
+                                            int32_t* expert_offsets, int32_t* perm, int32_t* seg_of, int32_t* num_segments,
+                                            void* workspace, size_t workspace_bytes, void* stream, uint32_t first_bin,
+                                            uint32_t spins) {
+  if (first_bin > 255 || spins == 0) return fail(LSHMOE_ERR_SHAPE, "first_bin is below 256 and spins positive");
+  return compress(tokens, expert, bucket, T, d, k, E, L, r, dtype, centroids, seg_offsets, seg_expert, expert_offsets, perm,
+                  seg_of, num_segments, workspace, workspace_bytes, stream, first_bin, spins);
 }
 
 lshmoe_status lshmoe_compress_static(const void* tokens, const int32_t* expert, const uint64_t* bucket, int64_t T,

@@ -24,29 +24,28 @@ hipError_t launch_hash_sphere(const void* tokens, const void* pivots, const floa
                               bool bf16, uint64_t* bucket, hipStream_t stream);
 
 // ---- step 2: group ------------------------------------------------------
-constexpr int kSortTile = 2048;            // assignments per sort tile
+constexpr int kSortTile = 2048;            // largest sort tile (assignments)
 constexpr int kSegTile = 1024;             // sorted positions per cluster-numbering tile
 constexpr int kMaxDigitBits = 9;           // radix digit width limit
 constexpr int kGroupBins = 1 << kMaxDigitBits;
-constexpr int kFusedMaxTiles = 256;        // up to this many sort tiles: no scan launch
+constexpr int kMaxTiles = 256;             // up to this many sort tiles: two launches
 constexpr int kSelfPrefixMaxTiles = 4096;  // up to this many numbering tiles: no scan launch
 constexpr int kSmallMaxN = 4096;           // up to this many assignments: one workgroup, one launch
 
 struct GroupPlan {
   int64_t N;
   int ebits, bbits;      // key = expert << bbits | bucket
-  int passes;            // radix passes over ebits + bbits key bits
+  bool one_bin;          // one workgroup, one launch
+  bool bins;             // tiles sorted by the top key bits, then one workgroup per bin
+  int top_shift;         // key bits below the bin (all of them without bins)
+  int passes;            // radix passes over those bits
   int shift[8], width[8];  // digit of pass p is (key >> shift[p]) & ((1 << width[p]) - 1)
-  bool fused;            // scatter blocks derive their offsets themselves (small inputs)
-  bool msd;              // one global pass on the top digit, then every bin sorted by one workgroup
-  int top_shift, top_width;        // msd: the global pass's digit
-  int low_passes;                  // msd: radix passes over the remaining bits
-  int low_shift[8], low_width[8];
-  int tile;              // assignments per sort tile (kSortTile, or less on small inputs)
-  uint32_t sort_blocks;  // sort tiles
+  int tile;              // assignments per sort tile
+  uint32_t tiles;        // sort tiles
+  uint32_t first_bin, spins;   // bins: see BinArgs (a test forces the takeover of bins with them)
   uint32_t seg_blocks;   // tiles of kSegTile sorted positions
   // byte offsets into the workspace
-  size_t off_key[2], off_idx[2], off_table, off_blocksum, off_binstart, off_chunktbl, off_chunkheads;
+  size_t off_key[3], off_idx[2], off_table, off_blocksum;
   size_t off_partial, off_counters;  // window sums and window counters of the centroid step
   size_t total_bytes;
 };

@@ -1,0 +1,93 @@
+"""Grouping by bins (one workgroup per bin of the top key bits): sizes at the edges of its tiles, of its LDS sort and of
+the route itself, and the takeover of bins whose own workgroups do not run.  Integer outputs, compared exactly."""
+import ctypes
+
+import numpy as np
+import pytest
+import torch
+
+import paper_2411_08446_amd as lsh
+import paper_2411_08446_amd.binding as binding
+from workloads import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def H():
+    import gpu_harness
+    gpu_harness.lsh.load_library()
+    return gpu_harness
+
+
+# the key is 2 expert bits and L * 5 bucket bits; bin: its top 8 bits
+@pytest.mark.parametrize("in_bin", [1, 63, 64, 65, 1023, 1025, 4095, 4096, 4097, 8191, 12289])
+@pytest.mark.parametrize("L,distinct", [(3, 5), (3, 4000), (6, 40), (6, 100000)])   # one radix pass; sub-bins or several passes
+def test_bin_sizes(H, in_bin, L, distinct):
+    # one bin of in_bin keys among 5000 others: around a wave, a round of the workgroup and the LDS sort's limit,
+    # with few different keys (crowded sub-bins), and with nearly all different
+    d, dtype, E, r = 8, "bf16", 4, 16
+    rng = np.random.default_rng(in_bin * 10 + L + distinct)
+    low = 5 * L - 6
+    N = in_bin + 5000
+    ids = rng.integers(0, 1 << (5 * L), N, dtype=np.uint64)
+    expert = rng.integers(0, E, N)
+    where = rng.permutation(N)[:in_bin]
+    expert[where] = 2
+    ids[where] = (np.uint64(37) << np.uint64(low)) | (rng.integers(0, distinct, in_bin, dtype=np.uint64) % np.uint64(1 << low))
+    tokens = synth.f32_to_storage(rng.standard_normal((N, d)).astype(np.float32), dtype)
+    rot = np.zeros((L, r, d), tokens.dtype)
+    print("case bin of", in_bin, "L", L, "distinct", distinct, flush=True)
+    H.run_and_check(tokens, rot, expert.astype(np.int32).reshape(N, 1), E, dtype, lambda c: c, bucket_override=ids, skip_hash=True)
+
+
+@pytest.mark.parametrize("N", [4096, 65535, 65536, 65537, 131073, 262144, 262145, 524287])
+def test_tile_sizes(H, N):
+    # the tile of the first launch doubles at 65536, 131072 and 262144 assignments; 4096 is one bin
+    d, dtype, E, L, r = 8, "bf16", 300, 3, 8                        # 9 expert bits: a bin holds several experts
+    rng = np.random.default_rng(N)
+    pool = rng.integers(0, 16 ** 3, max(1, N // 3), dtype=np.uint64)
+    tokens = synth.f32_to_storage(rng.standard_normal((N, d)).astype(np.float32), dtype)
+    rot = np.zeros((L, r, d), tokens.dtype)
+    expert = np.minimum(rng.integers(0, E, (N, 1)), rng.integers(0, E, (N, 1))).astype(np.int32)
+    print("case tiles N", N, flush=True)
+    H.run_and_check(tokens, rot, expert, E, dtype, lambda c: c, bucket_override=pool[rng.integers(0, pool.size, N)], skip_hash=True)
+
+
+@pytest.mark.parametrize("first_bin", [1, 37, 255])
+@pytest.mark.parametrize("skew", [False, True])                     # True: one bin of 6000 keys, sorted in global memory
+def test_bins_whose_workgroups_do_not_run_are_taken_over(first_bin, skew):
+    # The workgroups of the bins below first_bin leave at once; the others find those bins open, claim them one by one
+    # and do them before their own.  Every output equals that of the ordinary call.
+    lib = lsh.load_library()
+    E, L, r, d, N = 4, 4, 16, 8, 20000
+    rng = np.random.default_rng(first_bin)
+    expert = rng.integers(0, E, (N, 1)).astype(np.int32)
+    ids = rng.integers(0, 3000, N).astype(np.int64) * 333
+    if skew:
+        expert[:6000], ids[:6000] = 0, rng.integers(0, 1000, 6000)
+    x = torch.from_numpy(rng.standard_normal((N, d)).astype(np.float32)).cuda()
+    et, bt = torch.from_numpy(expert).cuda(), torch.from_numpy(ids).cuda()
+    outs = []
+    for take_over in (False, True):
+        o = lsh.CompressOutputs.allocate(N, d, 1, E, L, r, torch.float32)
+        for t in (o.centroids, o.seg_offsets, o.seg_expert, o.expert_offsets, o.perm, o.seg_of, o.num_segments):
+            t.fill_(-7)
+        o.workspace.fill_(0xA5)
+        print("case takeover first_bin", first_bin, "skew", skew, take_over, flush=True)
+        if take_over:
+            ws, ws_bytes = binding._aligned_ws(o.workspace)
+            p = lambda t: ctypes.c_void_p(t.data_ptr())
+            status = lib.lshmoe_test_compress_takeover(
+                p(x), p(et), p(bt), ctypes.c_int64(N), d, 1, E, L, r, lsh.LSHMOE_F32, p(o.centroids), p(o.seg_offsets),
+                p(o.seg_expert), p(o.expert_offsets), p(o.perm), p(o.seg_of), p(o.num_segments), ctypes.c_void_p(ws),
+                ctypes.c_size_t(ws_bytes), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream),
+                ctypes.c_uint32(first_bin), ctypes.c_uint32(2))
+            assert status == lsh.LSHMOE_OK
+        else:
+            lsh.lshmoe_compress(x, et, bt, E, L, r, o)
+        torch.cuda.synchronize()
+        outs.append(o)
+    a, b = outs
+    for name in ("num_segments", "seg_offsets", "seg_expert", "expert_offsets", "perm", "seg_of", "centroids"):
+        assert torch.equal(getattr(a, name), getattr(b, name)), name
