@@ -330,6 +330,18 @@ def test_hash_rows_with_a_tail(H, dtype, T, L, r):
     _hash_case(H, dtype, T, L, r, d=264 if dtype == "bf16" else 132)
 
 
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,L,r,pieces", [
+    (257, 1, 16, 8), (300, 2, 16, 1), (8192, 3, 24, 9), (8193, 3, 24, 15), (8192, 4, 64, 24), (8193, 10, 16, 16),
+    (777, 2, 64, 72), (8000, 4, 3, 23), (16384, 10, 16, 24), (16385, 10, 16, 17), (16384, 8, 32, 8), (16385, 4, 64, 31),
+    (65535, 9, 16, 8), (65536, 9, 16, 9), (9001, 31, 2, 10), (8193, 3, 20, 40), (24576, 3, 20, 12), (33000, 4, 30, 8)])
+def test_hash_edges_of_the_shapes(H, dtype, T, L, r, pieces):
+    # both sides of the token counts at which another shape takes over, for rows of a few 16-byte pieces up to nine
+    # chunks of eight (tails of one to seven among them): rows that fit the rings as a whole and rows that do not, hashes
+    # of half a tile, a tile and two tiles, over one wave and over several
+    _hash_case(H, dtype, T, L, r, d=pieces * (8 if dtype == "bf16" else 4))
+
+
 def _hash_case(H, dtype, T, L, r, d=None):
     # Large inputs with rows of whole 128-byte chunks take the kernels that stage both operands through LDS:
     # 193..256 rows of R per pass and T >= 65536 the one that splits the rows of R between two waves and joins the
