@@ -48,16 +48,16 @@ __global__ __launch_bounds__(256) void grad_tokens_kernel(
 #pragma unroll
         for (int i = 0; i < E; ++i) acc[i] += h[i];
       } else if (no_res) {
-        const float fn = (float)n;
+        const float fn = (float)n, inv = 1.0f / fn;
 #pragma unroll
-        for (int i = 0; i < E; ++i) acc[i] += h[i] / fn;
+        for (int i = 0; i < E; ++i) acc[i] += div_count(h[i], fn, inv);
       } else {
         float g[E], gs[E];
-        Piece<DT>::widen(load16(grad_out + (size_t)a * row_bytes + c * 16), g);
+        Piece<DT>::widen(load16_stream(grad_out + (size_t)a * row_bytes + c * 16), g);
         Piece<DT>::widen(load16(grad_expert_out + (size_t)s * row_bytes + c * 16), gs);
-        const float fn = (float)n;
+        const float fn = (float)n, inv = 1.0f / fn;
 #pragma unroll
-        for (int i = 0; i < E; ++i) acc[i] += g[i] + (h[i] - gs[i]) / fn;
+        for (int i = 0; i < E; ++i) acc[i] += g[i] + div_count(h[i] - gs[i], fn, inv);
       }
     }
     store16_stream(grad_tokens + (size_t)t * row_bytes + c * 16, Piece<DT>::narrow(acc));
@@ -114,6 +114,8 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(
   const bool live = t < T;                                  // lanes of a dead group still take part in the butterfly
   const size_t row_bytes = (size_t)cpr * 16;
   const bool no_res = (flags & 1u) != 0;
+  // a token's own rows are read once (unless its experts are several batches): they leave the caches to the cluster rows
+  auto load_row = [&](const char* p) { return k <= (uint32_t)kBatch ? load16_stream(p) : load16(p); };
   for (uint32_t j0 = 0; j0 < k; j0 += kBatch) {
     int32_t s[kBatch];
     float w[kBatch], dot[kBatch];
@@ -132,8 +134,8 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(
     const bool any_full = full[0] || full[1] || full[2] || full[3];
     for (uint32_t c = lane % LPR; c < cpr && live; c += LPR) {
       float g[E], xv[E];
-      Piece<DT>::widen(load16(grad_out + (size_t)t * row_bytes + c * 16), g);
-      if (any_full) Piece<DT>::widen(load16(tokens + (size_t)t * row_bytes + c * 16), xv);
+      Piece<DT>::widen(load_row(grad_out + (size_t)t * row_bytes + c * 16), g);
+      if (any_full) Piece<DT>::widen(load_row(tokens + (size_t)t * row_bytes + c * 16), xv);
 #pragma unroll
       for (int q = 0; q < kBatch; ++q) {
         if (!on[q]) continue;

@@ -12,14 +12,22 @@ constexpr int kWave = 64;
 struct F32 {};   // IEEE binary32 storage
 struct BF16 {};  // bfloat16 storage (upper half of binary32)
 
-__device__ __forceinline__ float bf16_bits_to_f32(uint32_t h) { return __uint_as_float(h << 16); }
+// Two binary32 -> two bfloat16, round to nearest even; NaN stays NaN.  One instruction (v_cvt_pk_bf16_f32): rounding with
+// integer operations took six per element, in kernels that move rows a third of their vector work.
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ uint32_t f32_to_bf16_pair(float lo, float hi) {
+  const f32x2 v = {lo, hi};
+  return __builtin_bit_cast(uint32_t, __builtin_convertvector(v, bf16x2));
+}
 
-// binary32 -> bfloat16, round to nearest even on the 16 discarded bits.
-__device__ __forceinline__ uint32_t f32_to_bf16_bits(float f) {
-  uint32_t u = __float_as_uint(f);
-  if ((u & 0x7fffffffu) > 0x7f800000u) return 0x7fc0u;  // NaN stays NaN
-  u += 0x7fffu + ((u >> 16) & 1u);
-  return u >> 16;
+// a / n for a member count n with y = 1 / n (both computed once per row): one Newton step on a * y, correctly rounded by
+// Markstein's theorem (y is the correctly rounded reciprocal) wherever nothing underflows, in four operations; the general
+// division takes eleven.  r is zero where a * y is exact and NaN where it is infinite: the product stands then.
+__device__ __forceinline__ float div_count(float a, float n, float y) {
+  const float q = a * y;
+  const float r = fmaf(-q, n, a);
+  return fabsf(r) > 0.0f ? fmaf(r, y, q) : q;
 }
 
 // One wave per row (or cluster) can mean more than 2^32 threads, which a one-dimensional launch cannot express
@@ -43,6 +51,12 @@ __device__ __forceinline__ void store16(char* p, uint4 v) { *reinterpret_cast<ui
 __device__ __forceinline__ void store16_stream(char* p, uint4 v) {
   const u32x4 w = {v.x, v.y, v.z, v.w};
   __builtin_nontemporal_store(w, reinterpret_cast<u32x4*>(p));
+}
+
+// Streaming load: rows that are read once should not push out rows that others will read again.
+__device__ __forceinline__ uint4 load16_stream(const char* p) {
+  const u32x4 w = __builtin_nontemporal_load(reinterpret_cast<const u32x4*>(p));
+  return make_uint4(w.x, w.y, w.z, w.w);
 }
 
 template <typename DT> struct Piece;   // arithmetic on one 16-byte piece
@@ -70,7 +84,7 @@ template <> struct Piece<BF16> {
   static __device__ __forceinline__ uint4 narrow(const float (&v)[8]) {
     uint32_t w[4];
 #pragma unroll
-    for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16_bits(v[2 * i]) | (f32_to_bf16_bits(v[2 * i + 1]) << 16);
+    for (int i = 0; i < 4; ++i) w[i] = f32_to_bf16_pair(v[2 * i], v[2 * i + 1]);
     return make_uint4(w[0], w[1], w[2], w[3]);
   }
 };
