@@ -29,20 +29,20 @@ template <int LPR> __device__ __forceinline__ int32_t uniform(int32_t v) {
 }
 
 // Compensated sum of the token rows at sorted positions [a, b), wave-wide: lanes stride over the 16-byte pieces
-// of the row, eight rows in flight (a walk by one wave is bound by memory latency).  emit(c, acc) receives the
+// c_lo .. c_hi - 1 of the row, eight rows in flight (a walk by one wave is bound by memory latency).  emit(c, acc) receives the
 // sums of piece c.  Kept small in registers on purpose: the kernel's occupancy is set by its largest path.
 template <typename DT, typename Emit>
 __device__ __forceinline__ void row_sum_kahan(const char* __restrict__ tokens, const int32_t* __restrict__ perm,
-                                              int32_t a, int32_t b, uint32_t k, uint32_t cpr, size_t row_bytes,
-                                              Emit emit) {
+                                              int32_t a, int32_t b, uint32_t k, uint32_t c_lo, uint32_t c_hi,
+                                              size_t row_bytes, Emit emit) {
   constexpr int E = Piece<DT>::kElems;
   constexpr int kRows = 8;
   const uint32_t lane = threadIdx.x & 63;
   // every lane of the wave walks every pass, also lanes past the end of the row (they hold member ids, see
   // below, and only skip the row loads): the loop bounds are wave-uniform
-  for (uint32_t c0 = 0; c0 < cpr; c0 += 64) {
+  for (uint32_t c0 = c_lo; c0 < c_hi; c0 += 64) {
     const uint32_t c = c0 + lane;
-    const bool on = c < cpr;
+    const bool on = c < c_hi;
     float acc[E], comp[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = comp[i] = 0.0f;
@@ -87,7 +87,7 @@ __device__ __forceinline__ void window_sum(const char* __restrict__ tokens, cons
                                            int32_t a, int32_t b, uint32_t k, uint32_t cpr, size_t row_bytes,
                                            float* __restrict__ out_row) {
   constexpr int E = Piece<DT>::kElems;
-  row_sum_kahan<DT>(tokens, perm, a, b, k, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
+  row_sum_kahan<DT>(tokens, perm, a, b, k, 0, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
 #pragma unroll
     for (int i = 0; i < E; i += 4)
       *(float4*)(out_row + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
@@ -120,7 +120,7 @@ __device__ __forceinline__ void long_cluster_window(
   if (old != m1 - m0) return;
   __threadfence();  // last window of the cluster: every other partial row is complete and visible
   const uint32_t nwin = m1 - m0 + 1;
-  const float fn = (float)(hi - lo);
+  const float fn = (float)(hi - lo), inv = 1.0f / fn;
   char* dst = centroids + (size_t)s * row_bytes;
   constexpr int kRows = 4;
   for (uint32_t c = lane; c < cpr; c += 64) {
@@ -154,52 +154,64 @@ __device__ __forceinline__ void long_cluster_window(
     }
     if (mean) {
 #pragma unroll
-      for (int i = 0; i < E; ++i) acc[i] /= fn;
+      for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
     }
     store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
   }
 }
 
 
-// The same with the four waves of a workgroup on one block of kWgWindow positions (needs the LDS of the shared
-// sums): every wave sums its quarter of the block's part of the cluster into LDS, wave 0 adds the four in wave
-// order, writes ONE partial row and bumps the counter - a quarter of the device-scope fences.  The workgroup that
-// brings the counter to the cluster's block count adds the partial rows in position order, again a quarter per
-// wave joined through LDS in wave order, so the result does not depend on which workgroup came last.
+// The same with workgroups (needs the LDS of the shared sums).  The sorted positions are cut into aligned blocks of W and
+// two workgroups take a block, each one half of the columns: every wave sums its quarter of the block's part of the
+// cluster into LDS, wave 0 adds the four in wave order, writes half a partial row and bumps the counter - a quarter of
+// the device-scope fences.  The workgroup that brings the counter to twice the cluster's block count adds the partial
+// rows in position order, again a quarter per wave joined through LDS in wave order, so the result does not depend on
+// which workgroup came last.
 // Called by all four waves of the workgroup with the same arguments (barriers inside).
-constexpr uint32_t kWgWindow = 2 * kCentroidWindow;   // measured: 128 and 512 positions per block are both slower
-static_assert(kWgWindow <= (uint32_t)kWindowMin, "a block meets at most two clusters that are cut into blocks");
+//
+// W: a wave is bound by memory latency, about 1.8 us per round of eight rows and 64 pieces, and the partial rows are read
+// in rounds of four by the last workgroup alone.  Blocks of 128 positions halve the first part for clusters of up to
+// kSmallWindowMax members; beyond that the second part would outweigh it and blocks are of 256 (with one huge cluster
+// 128 and 512 were both slower).  One cluster of 4362 rows of
+// 1536 bytes among 12022 others: the whole kernel 39.3 -> 25.1 us (with blocks of 256 by one workgroup each before).
+// A cluster's blocks of either size use slots of their own: block m of 256 positions holds the slots of block 2m of 128,
+// and at most one cluster beyond kWindowMin covers a block's first position and one starts inside it.
+constexpr int kSmallWindowMax = 8192;
+constexpr uint32_t kSmallWindow = kCentroidWindow, kLargeWindow = 2 * kCentroidWindow;
+static_assert(kLargeWindow <= (uint32_t)kWindowMin, "a block meets at most two clusters that are cut into blocks");
 
 template <typename DT>
 __device__ __forceinline__ void long_cluster_wg_window(
     const char* __restrict__ tokens, const int32_t* __restrict__ perm, const int32_t* __restrict__ seg_offsets,
     char* __restrict__ centroids, float* partial, uint32_t* counters, float* coop_sum, int32_t s, uint32_t block_p0,
-    int32_t a, int32_t b, uint32_t slot, uint32_t k, uint32_t cpr, uint32_t d, uint32_t mean) {
+    uint32_t W, int32_t a, int32_t b, uint32_t slot, uint32_t half, uint32_t k, uint32_t cpr, uint32_t d, uint32_t mean) {
   constexpr int E = Piece<DT>::kElems;
   const size_t row_bytes = (size_t)cpr * 16;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t w4 = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   uint32_t* last_flag = reinterpret_cast<uint32_t*>(coop_sum + (size_t)4 * d);   // one word behind the four rows
-  const int32_t qa = max(a, (int32_t)(block_p0 + w4 * (kWgWindow / 4)));
-  const int32_t qb = min(b, (int32_t)(block_p0 + (w4 + 1) * (kWgWindow / 4)));
+  const uint32_t c_lo = half == 0 ? 0 : (cpr + 1) / 2, c_hi = half == 0 ? (cpr + 1) / 2 : cpr;
+  const int32_t qa = max(a, (int32_t)(block_p0 + w4 * (W / 4)));
+  const int32_t qb = min(b, (int32_t)(block_p0 + (w4 + 1) * (W / 4)));
   float* mine = coop_sum + (size_t)w4 * d;
   if (qa < qb) {
-    row_sum_kahan<DT>(tokens, perm, qa, qb, k, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
+    row_sum_kahan<DT>(tokens, perm, qa, qb, k, c_lo, c_hi, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
 #pragma unroll
       for (int i = 0; i < E; i += 4)
         *(float4*)(mine + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
     });
   } else {
-    for (uint32_t i = lane; i < d; i += 64) mine[i] = 0.0f;
+    for (uint32_t i = c_lo * E + lane; i < c_hi * E; i += 64) mine[i] = 0.0f;
   }
   const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[s]);
   const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[s + 1]);
-  const uint32_t m0 = (uint32_t)lo / kWgWindow, m1 = (uint32_t)(hi - 1) / kWgWindow;
-  const uint32_t first_slot = 2 * m0 + ((uint32_t)lo % kWgWindow != 0 ? 1u : 0u);
+  const uint32_t m0 = (uint32_t)lo / W, m1 = (uint32_t)(hi - 1) / W;
+  const uint32_t step = 2 * (W / (uint32_t)kCentroidWindow);   // slots per block
+  const uint32_t first_slot = step * m0 + ((uint32_t)lo % W != 0 ? 1u : 0u);
   __syncthreads();
   if (w4 == 0) {
     float* out_row = partial + (size_t)slot * d;
-    for (uint32_t i = lane * 4; i < d; i += 256) {   // d is a multiple of 4
+    for (uint32_t i = c_lo * E + lane * 4; i < c_hi * E; i += 256) {   // E is a multiple of 4
       float4 v = *(const float4*)(coop_sum + i);
 #pragma unroll
       for (int w = 1; w < 4; ++w) {
@@ -209,11 +221,11 @@ __device__ __forceinline__ void long_cluster_wg_window(
       *(float4*)(out_row + i) = v;
     }
     __threadfence();  // the partial row is visible device-wide before the counter moves
-    if (lane == 0) *last_flag = atomicAdd(&counters[first_slot], 1u) == m1 - m0 ? 1u : 0u;
+    if (lane == 0) *last_flag = atomicAdd(&counters[first_slot], 1u) == 2 * (m1 - m0) + 1 ? 1u : 0u;
   }
   __syncthreads();    // the flag is set; the four LDS rows are free again
   if (*last_flag == 0u) return;   // the same for all four waves
-  __threadfence();    // last block of the cluster: every other partial row is complete and visible
+  __threadfence();    // last half block of the cluster: every other partial row is complete and visible
   const uint32_t nwin = m1 - m0 + 1;
   const uint32_t per = (nwin + 3) / 4;
   const uint32_t j0 = min(w4 * per, nwin), j1 = min(j0 + per, nwin);
@@ -227,7 +239,7 @@ __device__ __forceinline__ void long_cluster_wg_window(
 #pragma unroll
       for (int u = 0; u < kRows; ++u) {
         const uint32_t jj = min(j + u, j1 - 1);
-        const float* src = partial + (size_t)(jj == 0 ? first_slot : 2 * (m0 + jj)) * d + (size_t)c * E;
+        const float* src = partial + (size_t)(jj == 0 ? first_slot : step * (m0 + jj)) * d + (size_t)c * E;
 #pragma unroll
         for (int i = 0; i < E; i += 4) {
           const float4 v = *(const float4*)(src + i);
@@ -252,7 +264,7 @@ __device__ __forceinline__ void long_cluster_wg_window(
       *(float4*)(mine + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
   }
   __syncthreads();
-  const float fn = (float)(hi - lo);
+  const float fn = (float)(hi - lo), inv = 1.0f / fn;
   char* dst = centroids + (size_t)s * row_bytes;
   for (uint32_t c = threadIdx.x; c < cpr; c += 256) {
     float acc[E];
@@ -261,7 +273,7 @@ __device__ __forceinline__ void long_cluster_wg_window(
       acc[i] = coop_sum[(size_t)c * E + i];
 #pragma unroll
       for (int w = 1; w < 4; ++w) acc[i] += coop_sum[((size_t)w * cpr + c) * E + i];
-      if (mean) acc[i] /= fn;
+      if (mean) acc[i] = div_count(acc[i], fn, inv);
     }
     store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
   }
@@ -314,7 +326,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
       const int32_t a = min(lo + (int32_t)w4 * quarter, hi), b = min(a + quarter, hi);
       float* mine = coop_sum + (size_t)w4 * cpr * E;
       if (a < b) {
-        row_sum_kahan<DT>(tokens, perm, a, b, k, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
+        row_sum_kahan<DT>(tokens, perm, a, b, k, 0, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
 #pragma unroll
           for (int i = 0; i < E; i += 4)
             *(float4*)(mine + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
@@ -324,7 +336,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
       }
       __syncthreads();
       char* dst = centroids + (size_t)sj * row_bytes;
-      const float fn = (float)n;
+      const float fn = (float)n, inv = 1.0f / fn;
       for (uint32_t c = threadIdx.x; c < cpr; c += 256) {
         float acc[E];
 #pragma unroll
@@ -332,7 +344,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
           acc[i] = coop_sum[(size_t)c * E + i];
 #pragma unroll
           for (int w = 1; w < 4; ++w) acc[i] += coop_sum[((size_t)w * cpr + c) * E + i];
-          if (mean) acc[i] /= fn;
+          if (mean) acc[i] = div_count(acc[i], fn, inv);
         }
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       }
@@ -347,11 +359,11 @@ __global__ __launch_bounds__(256) void centroid_kernel(
     } else if (LPR == 64 && n > kPlainSumMax && n <= kWindowMin) {
       // a whole wave on a cluster of more than 16 members: compensated sum, eight rows in flight
       char* dst = centroids + (size_t)s * row_bytes;
-      const float fn = (float)n;
-      row_sum_kahan<DT>(tokens, perm, lo, hi, k, cpr, row_bytes, [&](uint32_t c, float (&acc)[E]) {
+      const float fn = (float)n, inv = 1.0f / fn;
+      row_sum_kahan<DT>(tokens, perm, lo, hi, k, 0, cpr, row_bytes, [&](uint32_t c, float (&acc)[E]) {
         if (mean) {
 #pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] /= fn;
+          for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
         }
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       });
@@ -412,35 +424,43 @@ __global__ __launch_bounds__(256) void centroid_kernel(
           }
         }
         if (mean) {
-          const float fn = (float)n;
+          const float fn = (float)n, inv = 1.0f / fn;
 #pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] /= fn;
+          for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
         }
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       }
     }
   }
   if (shares) {
-    // window duty with the workgroup's LDS rows: workgroup m looks after block m of 4 * kCentroidWindow positions
+    // window duty with the workgroup's LDS rows: workgroups 2m and 2m + 1 look after block m of kSmallWindow positions
+    // and, with m even, the block of kLargeWindow positions that starts there
     // (every wave of the workgroup gets here: nothing above returns for a single wave)
-    if ((uint64_t)block * kWgWindow >= N) return;
-    const uint32_t p0 = block * kWgWindow, p1 = min(p0 + kWgWindow, N);
+    const uint32_t m = block >> 1, half = block & 1;
+    if ((uint64_t)m * kSmallWindow >= N) return;
+    const uint32_t p0 = m * kSmallWindow;
+    const bool wide = (m & 1) == 0;
+    const int32_t pos[3] = {(int32_t)p0, (int32_t)(min(p0 + kSmallWindow, N) - 1),
+                            (int32_t)(min(p0 + (wide ? kLargeWindow : kSmallWindow), N) - 1)};
+    int32_t at[3];                           // clusters of the block's first position and of the two blocks' last ones
+#pragma unroll
+    for (int j = 0; j < 3; ++j) at[j] = perm[pos[j]];
+#pragma unroll
+    for (int j = 0; j < 3; ++j) at[j] = __builtin_amdgcn_readfirstlane(seg_of[at[j]]);
     const uint32_t d = cpr * E;
-    const int32_t sf = __builtin_amdgcn_readfirstlane(seg_of[perm[p0]]);
-    const int32_t sl = __builtin_amdgcn_readfirstlane(seg_of[perm[p1 - 1]]);
-    {
-      const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[sf]);
-      const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[sf + 1]);
-      if (hi - lo > kWindowMin)
-        long_cluster_wg_window<DT>(tokens, perm, seg_offsets, centroids, partial, counters, coop_sum, sf, p0, (int32_t)p0,
-                                   min(hi, (int32_t)p1), 2 * block, k, cpr, d, mean);
-    }
-    if (sl != sf) {
-      const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[sl]);
-      const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[sl + 1]);
-      if (hi - lo > kWindowMin)
-        long_cluster_wg_window<DT>(tokens, perm, seg_offsets, centroids, partial, counters, coop_sum, sl, p0, lo,
-                                   (int32_t)p1, 2 * block + 1, k, cpr, d, mean);
+    auto duty = [&](int32_t sc, uint32_t W, uint32_t slot) {
+      const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[sc]);
+      const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[sc + 1]);
+      if (hi - lo <= kWindowMin || (hi - lo <= kSmallWindowMax) != (W == kSmallWindow)) return;
+      long_cluster_wg_window<DT>(tokens, perm, seg_offsets, centroids, partial, counters, coop_sum, sc, p0, W,
+                                 max(lo, (int32_t)p0), min(hi, (int32_t)min(p0 + W, N)), slot, half, k, cpr, d, mean);
+    };
+    // both block sizes meet the cluster of the first position; it is of one size class
+    duty(at[0], kSmallWindow, 2 * m);
+    if (at[1] != at[0]) duty(at[1], kSmallWindow, 2 * m + 1);
+    if (wide) {
+      duty(at[0], kLargeWindow, 2 * m);
+      if (at[2] != at[0]) duty(at[2], kLargeWindow, 2 * m + 1);
     }
     return;
   }

@@ -235,6 +235,23 @@ def test_long_clusters_are_summed_in_windows(H, dtype, d, k):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("sizes,d", [
+    ((1025, 8193, 127, 1024, 8192, 5), 136),       # both block sizes, off the grid of either
+    ((128, 1025, 1151, 8192, 8200, 1030, 9000), 768),   # neighbours of both classes that meet in one block
+    ((8193,), 1000), ((1025,), 264), ((256, 1280, 9984, 1), 520)])   # ends on the grid; alone
+def test_long_clusters_of_both_block_sizes(H, dtype, sizes, d):
+    # clusters beyond 1024 members are summed in blocks of 128 positions, beyond 8192 in blocks of 256, two workgroups
+    # to a block with one half of the columns each: rows of an odd number of 16-byte pieces and of two passes per half
+    T, E = sum(sizes), 2
+    tokens, rot, _ = _rand_inputs(24, T, d, 1, E, 2, 16, dtype)
+    ids = np.empty(T, np.uint64)
+    ids[np.random.default_rng(25).permutation(T)] = np.repeat(np.arange(len(sizes)), sizes).astype(np.uint64)
+    run = H.run_and_check(tokens, rot, np.zeros((T, 1), np.int32), E, dtype, _scale_fn, bucket_override=ids)
+    assert np.diff(run.out.seg_offsets[:run.S + 1].cpu().numpy()).tolist() == list(sizes)
+    H.check_backward(run, T, d, 1, dtype, seed=26)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_one_huge_cluster_many_windows(H, dtype):
     # 20000 identical tokens on the multi-launch grouping route: 157 window sums are combined by the last wave
     T, d, E = 20000, 64, 2
