@@ -19,7 +19,12 @@ template <int LPR> __device__ __forceinline__ int32_t uniform(int32_t v) {
   return LPR == 64 ? __builtin_amdgcn_readfirstlane(v) : v;
 }
 
-template <typename DT, int LPR>
+// STREAM: a token's own rows, which are read once, go past the caches and leave them to the cluster rows.  Worth it where
+// the rows are more than the 8 x 4 MB of L2 (65536 x 1024 bf16, clusters of one or two: the combine's backward 130.9 ->
+// 122.3 us); rows that the step before may have left there are better read through them (669 x 644 f32: 5.4 against 6.1 us).
+inline bool streams_rows(int64_t T, uint32_t cpr) { return (uint64_t)T * cpr * 16 >= 32ull << 20; }
+
+template <typename DT, int LPR, bool STREAM>
 __global__ __launch_bounds__(256) void grad_tokens_kernel(
     const char* __restrict__ grad_out, const char* __restrict__ grad_centroids,
     const char* __restrict__ grad_expert_out, const int32_t* __restrict__ seg_of,
@@ -53,7 +58,7 @@ __global__ __launch_bounds__(256) void grad_tokens_kernel(
         for (int i = 0; i < E; ++i) acc[i] += div_count(h[i], fn, inv);
       } else {
         float g[E], gs[E];
-        Piece<DT>::widen(load16_stream(grad_out + (size_t)a * row_bytes + c * 16), g);
+        Piece<DT>::widen((STREAM ? load16_stream : load16)(grad_out + (size_t)a * row_bytes + c * 16), g);
         Piece<DT>::widen(load16(grad_expert_out + (size_t)s * row_bytes + c * 16), gs);
         const float fn = (float)n, inv = 1.0f / fn;
 #pragma unroll
@@ -71,7 +76,8 @@ void launch_lpr(const void* grad_out, const void* grad_centroids, const void* gr
   constexpr int G = 64 / LPR;
   const uint64_t waves = ((uint64_t)T + G - 1) / G;
   const uint32_t blocks = (uint32_t)((waves + 3) / 4);
-  hipLaunchKernelGGL((grad_tokens_kernel<DT, LPR>), grid_of_blocks(blocks), dim3(256), 0, stream, (const char*)grad_out,
+  auto kern = streams_rows(T, cpr) ? grad_tokens_kernel<DT, LPR, true> : grad_tokens_kernel<DT, LPR, false>;
+  hipLaunchKernelGGL(kern, grid_of_blocks(blocks), dim3(256), 0, stream, (const char*)grad_out,
                      (const char*)grad_centroids, (const char*)grad_expert_out, seg_of, seg_offsets,
                      (char*)grad_tokens, (uint32_t)T, (uint32_t)k, cpr, flags);
 }
@@ -99,7 +105,7 @@ void launch_typed(const void* grad_out, const void* grad_centroids, const void* 
 // group are added in a butterfly: the result does not depend on the launch.
 constexpr int kBatch = 4;
 
-template <typename DT, int LPR>
+template <typename DT, int LPR, bool STREAM>
 __global__ __launch_bounds__(256) void combine_backward_kernel(
     const char* __restrict__ tokens, const char* __restrict__ centroids, const char* __restrict__ expert_out,
     const int32_t* __restrict__ seg_of, const int32_t* __restrict__ seg_offsets, const float* __restrict__ gate_weight,
@@ -115,7 +121,7 @@ __global__ __launch_bounds__(256) void combine_backward_kernel(
   const size_t row_bytes = (size_t)cpr * 16;
   const bool no_res = (flags & 1u) != 0;
   // a token's own rows are read once (unless its experts are several batches): they leave the caches to the cluster rows
-  auto load_row = [&](const char* p) { return k <= (uint32_t)kBatch ? load16_stream(p) : load16(p); };
+  auto load_row = [&](const char* p) { return STREAM && k <= (uint32_t)kBatch ? load16_stream(p) : load16(p); };
   for (uint32_t j0 = 0; j0 < k; j0 += kBatch) {
     int32_t s[kBatch];
     float w[kBatch], dot[kBatch];
@@ -173,7 +179,8 @@ void launch_combine_backward_lpr(const void* tokens, const void* centroids, cons
   constexpr int G = 64 / LPR;
   const uint64_t waves = ((uint64_t)T + G - 1) / G;
   const uint32_t blocks = (uint32_t)((waves + 3) / 4);
-  hipLaunchKernelGGL((combine_backward_kernel<DT, LPR>), grid_of_blocks(blocks), dim3(256), 0, stream,
+  auto kern = streams_rows(T, cpr) ? combine_backward_kernel<DT, LPR, true> : combine_backward_kernel<DT, LPR, false>;
+  hipLaunchKernelGGL(kern, grid_of_blocks(blocks), dim3(256), 0, stream,
                      (const char*)tokens, (const char*)centroids, (const char*)expert_out, seg_of, seg_offsets, gate_weight,
                      (const char*)grad_out, grad_w, (char*)grad_rows, (uint32_t)T, (uint32_t)k, cpr, flags);
 }

@@ -20,7 +20,11 @@ namespace {
 
 constexpr int kPlainSumMax = 16;  // members summed without compensation
 constexpr int kCoopMin = 32;      // clusters with more members (up to kWindowMin) are shared by the workgroup's waves
-constexpr int kWindowMin = 1024;  // clusters with more members are cut into windows of kCentroidWindow positions
+// Clusters with more members are cut into windows of positions.  The fewest that the windows' slots allow (see
+// long_cluster_wg_window): one workgroup walks 1024 rows of 1536 bytes in 32 rounds per wave and pass, six workgroups and
+// more the same cluster in four.  Measured against 1024, kernels whose
+// largest clusters have hundreds of members: 67.6 -> 24.5 us, 44.2 -> 13.8 us, 57.8 -> 28.8 us.
+constexpr int kWindowMin = 256;
 static_assert(kWindowMin >= kCentroidWindow, "a window meets at most two windowed clusters only if they are longer than it");
 constexpr size_t kCoopMaxLds = 32 * 1024;  // more LDS per workgroup would cut the occupancy of the common path
 
@@ -172,10 +176,11 @@ __device__ __forceinline__ void long_cluster_window(
 // W: a wave is bound by memory latency, about 1.8 us per round of eight rows and 64 pieces, and the partial rows are read
 // in rounds of four by the last workgroup alone.  Blocks of 128 positions halve the first part for clusters of up to
 // kSmallWindowMax members; beyond that the second part would outweigh it and blocks are of 256 (with one huge cluster
-// 128 and 512 were both slower).  One cluster of 4362 rows of
-// 1536 bytes among 12022 others: the whole kernel 39.3 -> 25.1 us (with blocks of 256 by one workgroup each before).
+// 128 and 512 were both slower).  One cluster of 4362 rows of 1536 bytes among 12022 others: the whole kernel
+// 39.3 -> 25.1 us (with blocks of 256 by one workgroup each before).
 // A cluster's blocks of either size use slots of their own: block m of 256 positions holds the slots of block 2m of 128,
-// and at most one cluster beyond kWindowMin covers a block's first position and one starts inside it.
+// and at most one cluster beyond kWindowMin covers a block's first position and one starts inside it - of both sizes
+// together, since no two clusters of 256 members and more start within 256 positions.
 constexpr int kSmallWindowMax = 8192;
 constexpr uint32_t kSmallWindow = kCentroidWindow, kLargeWindow = 2 * kCentroidWindow;
 static_assert(kLargeWindow <= (uint32_t)kWindowMin, "a block meets at most two clusters that are cut into blocks");

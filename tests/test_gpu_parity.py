@@ -236,11 +236,11 @@ def test_long_clusters_are_summed_in_windows(H, dtype, d, k):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("sizes,d", [
-    ((1025, 8193, 127, 1024, 8192, 5), 136),       # both block sizes, off the grid of either
-    ((128, 1025, 1151, 8192, 8200, 1030, 9000), 768),   # neighbours of both classes that meet in one block
-    ((8193,), 1000), ((1025,), 264), ((256, 1280, 9984, 1), 520)])   # ends on the grid; alone
+    ((257, 8193, 127, 256, 8192, 5), 136),         # both block sizes, off the grid of either
+    ((10, 257, 8200, 257, 299, 8192, 8200, 258, 9000), 768),   # neighbours of both classes that meet in one block
+    ((8193,), 1000), ((257,), 264), ((256, 1280, 9984, 1), 520)])   # ends on the grid; alone
 def test_long_clusters_of_both_block_sizes(H, dtype, sizes, d):
-    # clusters beyond 1024 members are summed in blocks of 128 positions, beyond 8192 in blocks of 256, two workgroups
+    # clusters beyond 256 members are summed in blocks of 128 positions, beyond 8192 in blocks of 256, two workgroups
     # to a block with one half of the columns each: rows of an odd number of 16-byte pieces and of two passes per half
     T, E = sum(sizes), 2
     tokens, rot, _ = _rand_inputs(24, T, d, 1, E, 2, 16, dtype)
