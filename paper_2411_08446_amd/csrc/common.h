@@ -30,9 +30,10 @@ __device__ __forceinline__ float div_count(float a, float n, float y) {
   return fabsf(r) > 0.0f ? fmaf(r, y, q) : q;
 }
 
-// One wave per row (or cluster) can mean more than 2^32 threads, which a one-dimensional launch cannot express
-// (a dispatch counts work-items per dimension in 32 bits): grids of 256-thread workgroups beyond 2^22 workgroups
-// are folded into two dimensions.  Surplus workgroups of the last row leave through the kernels' bounds checks.
+// One wave per row (or cluster), or several waves to a few tokens, can mean more than 2^32 threads, which a
+// one-dimensional launch cannot express (a dispatch counts work-items per dimension in 32 bits): grids beyond 2^22
+// workgroups (of at most 512 threads) are folded into two dimensions.  Surplus workgroups of the last row leave through
+// the kernels' bounds checks.
 inline dim3 grid_of_blocks(uint64_t blocks) {
   constexpr uint64_t kMaxX = 1ull << 22;
   if (blocks <= kMaxX) return dim3((uint32_t)(blocks == 0 ? 1 : blocks));

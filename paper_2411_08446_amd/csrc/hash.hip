@@ -335,7 +335,9 @@ __global__ __launch_bounds__(GROUPS * HALVES * 64, 1) void hash_stream_kernel(
   const uint32_t row_bytes = (uint32_t)row_pieces * 16u;
   const int nchunks = KTAIL ? (row_pieces + kPieces - 1) / kPieces : row_pieces / kPieces;
   const int last_pieces = KTAIL ? row_pieces - (nchunks - 1) * kPieces : kPieces;   // pieces of the last chunk, 1..8
-  const uint32_t tok_blk = blockIdx.x * (uint32_t)S::kTokens;
+  const uint64_t first_tok = linear_block() * S::kTokens;
+  if (first_tok >= T) return;                // surplus workgroups of a folded grid, before any barrier
+  const uint32_t tok_blk = (uint32_t)first_tok;
   const char* x_blk = tokens + (size_t)tok_blk * row_bytes;
 
   // a wave's load instruction covers 8 rows x 8 pieces (lane l at slot base + l); the swizzle is applied by
@@ -679,7 +681,8 @@ hipError_t launch_stream(const char* x, const char* R, uint64_t* bucket, int64_t
     if (e != hipSuccess) return e;
     raised.store(true, std::memory_order_release);
   }
-  const dim3 grid((uint32_t)((T + S::kTokens - 1) / S::kTokens)), block(S::kWaves * 64);
+  // folded: the shapes of 32 or 64 tokens per workgroup have four or eight work-items per token
+  const dim3 grid = grid_of_blocks(((uint64_t)T + S::kTokens - 1) / S::kTokens), block(S::kWaves * 64);
   hipLaunchKernelGGL(kern, grid, block, S::kLdsBytes, stream, x, R, bucket, (uint32_t)T, row_pieces, L, r, hpg, gate_w, E,
                      logits);
   return hipGetLastError();

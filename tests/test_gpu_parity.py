@@ -797,3 +797,26 @@ def test_maximum_size_indexing(H):
     y_ref = oracle.restore_ref(H.to_storage(xt[at // k], dtype), H.to_storage(out.centroids[s_a], dtype),
                                H.to_storage(ect[s_a], dtype), np.arange(len(asamp), dtype=np.int32), 1, dtype)
     H.assert_rows_close(H.to_storage(y1f[at], dtype), y_ref, dtype, "restore sample")
+
+
+def test_hash_grid_beyond_one_dimension(H):
+    # single precision, 96 rows of R: 32 tokens per workgroup of 256 threads, so from 2^29 tokens on the launch has more
+    # than 2^32 work-items.  Every id is written (no sentinel is left) and samples agree with the oracle.
+    T, d, L, r = (1 << 29) + 45, 4, 3, 32
+    print("case hash of", T, "tokens", flush=True)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(78)
+    xt = torch.empty((T, d), device="cuda")
+    step = 1 << 26
+    for lo in range(0, T, step):
+        xt[lo:lo + step].normal_(generator=g)
+    rot = np.random.default_rng(6).standard_normal((L, r, d)).astype(np.float32)
+    bt = torch.full((T,), -1, dtype=torch.int64, device="cuda")
+    H.lsh.lshmoe_hash(xt, H.to_device(rot, "f32"), bt)
+    torch.cuda.synchronize()
+    for lo in range(0, T, step):
+        assert int(bt[lo:lo + step].min()) >= 0, "ids left unwritten from token %d on" % lo
+    rng = np.random.default_rng(10)
+    samp = np.unique(np.concatenate([rng.integers(0, T, 4000), [0, T - 1, (1 << 29) - 1, 1 << 29, (1 << 29) + 31, (1 << 29) + 32]]))
+    st = torch.from_numpy(samp).cuda()
+    H.check_hash(bt[st].cpu().numpy().view(np.uint64), H.to_storage(xt[st], "f32"), rot, "f32")
