@@ -330,7 +330,7 @@ __global__ __launch_bounds__(kSegThreads) void seg_write_kernel(
 constexpr int kBinBits = 8;
 constexpr int kBins = 1 << kBinBits;
 static_assert(kBins == kSortThreads, "one bin per thread of tile_bin_kernel");
-constexpr uint32_t kClaimStride = 32;        // claims of different bins sit in different 128-byte lines
+constexpr uint32_t kClaimStride = 8;         // four claims to a 128-byte line: exchanges on one word or line queue up
 constexpr uint32_t kSyncWords = kBins * (1 + kClaimStride);   // published head counts of the bins, then their claims
 
 template <int TILE>
@@ -451,7 +451,7 @@ struct BinLds {
 static_assert(sizeof(BinLds) <= 140 * 1024, "LDS of a compute unit, less the rest of the kernel");
 
 struct BinArgs {
-  KeySource src;              // DIRECT
+  KeySource src;              // DIRECT, and the keys of a bin of more than kBinCap keys
   const uint32_t* table;      // [tiles][kBins]: start of the bin inside the tile | keys << 16
   const uint64_t* tile_key;   // the tiles, each sorted by bin
   const int32_t* tile_idx;
@@ -461,8 +461,7 @@ struct BinArgs {
   int passes;                 // radix passes over the key bits below the bin
   int shift[8], width[8];
   int sub_shift;              // sub-bin of a key is (key >> sub_shift) & (kSubBins - 1)
-  uint64_t* big_key[2];       // radix buffers of a bin of more than kBinCap keys; its ids go between big_idx and perm
-  int32_t* big_idx;
+  int32_t* big_idx;           // the ids of a bin of more than kBinCap keys go between here and perm
   int32_t *seg_offsets, *seg_expert, *expert_offsets, *perm, *seg_of, *num_segments;
   uint32_t* sync;             // kSyncWords, zero on entry (not used with DIRECT)
   uint32_t* window_counters;  // cleared here for the centroid step
@@ -553,10 +552,10 @@ struct BinShared {
 struct BinState {                    // a sorted bin
   uint32_t n, start, heads;          // keys, first position, clusters
   uint32_t x_lo, x_hi;               // experts whose first possible key lies in this bin: their offsets are written with it
-  const uint64_t* sorted;            // null: in LDS; else the keys in global memory, their ids being in perm
+  bool big;                          // the sorted ids are in perm; else keys and ids are in LDS
   uint32_t less, equal;              // in LDS: the first `less` keys come before `equal` ones that are `common`
   uint64_t common;
-  uint32_t heads_before;             // keys in global memory: clusters before the wave's slice
+  uint32_t heads_before;             // big: clusters before the wave's slice
 };
 
 // Collects and sorts a bin and counts its clusters.  taken: not 0 in thread 0 when the bin belongs to another
@@ -626,8 +625,8 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
   // has in common (padding).  If one key makes up most of the bin, its assignments go straight to their place in perm
   // (two walks over the bin, no sort) and the rest, if it is small enough, is sorted in LDS.  (26000 equal keys among
   // 131072, compress call at d = 8: 132 us, 361 with the passes below.)  Else the same radix passes as in LDS run
-  // through global memory, by the one workgroup, about 2 ns per key and pass: an input whose keys all share a few
-  // bins is better off with more workgroups per bin, but no other one pays for it.
+  // through global memory, by the one workgroup.  Only ids are moved: the keys are made from the inputs again in every
+  // walk, so that the workspace holds no further key buffers.
   uint32_t less = n, equal = 0;                     // rest[0, less) comes before the common key, `equal` keys are it
   uint64_t common = 0;
   if (!DIRECT && n > (uint32_t)kBinCap) {
@@ -687,7 +686,13 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
   }
   const uint32_t rest = n - equal;                  // keys to sort
   const bool big = !DIRECT && rest > (uint32_t)kBinCap;
-  st.sorted = nullptr;
+  st.big = big;
+  auto key_of = [&](int32_t id) {
+    uint64_t key;
+    int32_t unused;
+    load_item<true>(a.src, (uint32_t)id, key, unused);
+    return key;
+  };
   const uint32_t slice = ((rest + kBinWaves - 1) / kBinWaves + 63u) & ~63u;   // keys per wave, whole rounds
   const uint32_t wlo = min((uint32_t)wave * slice, rest), whi = min(wlo + slice, rest);
   uint32_t heads = 0;
@@ -826,11 +831,10 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
     if (wave == 0) sh.head_cnt[lane] = inc - mine;   // read after the barriers of the wait for the bins before
     if (DIRECT) __syncthreads();
   } else {
-    // collected into one piece of global memory, then radix passes there; every wave walks its slice 64 keys at a
-    // time, twice per pass
+    // the ids are collected into one piece of global memory, then radix passes there; every wave walks its slice 64
+    // keys at a time, twice per pass
     {
       int32_t* ids = ((a.passes & 1) ? a.big_idx : a.perm) + start;   // the last pass leaves the ids in perm
-      uint64_t* keys = a.big_key[1] + start;
       for (uint32_t b = tid; b < n; b += kBigRounds * kBinThreads) {
         uint64_t key[kBigRounds];
         int32_t idx[kBigRounds];
@@ -838,10 +842,7 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
         for (int q = 0; q < kBigRounds; ++q) fetch(min(b + q * kBinThreads, n - 1), key[q], idx[q]);
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q) {
-          if (b + q * kBinThreads < n) {
-            keys[b + q * kBinThreads] = key[q];
-            ids[b + q * kBinThreads] = idx[q];
-          }
+          if (b + q * kBinThreads < n) ids[b + q * kBinThreads] = idx[q];
         }
       }
       __syncthreads();
@@ -849,8 +850,6 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
     for (int p = 0; p < a.passes; ++p) {
       const int shift = a.shift[p], width = a.width[p];
       const uint32_t mask = (1u << width) - 1u;
-      const uint64_t* skey = a.big_key[(p + 1) & 1] + start;
-      uint64_t* dkey = a.big_key[p & 1] + start;
       const bool to_perm = ((a.passes - 1 - p) & 1) == 0;
       const int32_t* sidx = (to_perm ? a.big_idx : a.perm) + start;
       int32_t* didx = (to_perm ? a.perm : a.big_idx) + start;
@@ -860,7 +859,7 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
       for (uint32_t b = wlo; b < whi; b += kBigRounds * 64) {   // several rounds of loads in flight
         uint64_t key[kBigRounds];
 #pragma unroll
-        for (int q = 0; q < kBigRounds; ++q) key[q] = skey[min(b + q * 64 + lane, n - 1)];
+        for (int q = 0; q < kBigRounds; ++q) key[q] = key_of(sidx[min(b + q * 64 + lane, n - 1)]);
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q)
           if (b + q * 64 + lane < whi) atomicAdd(&m.cnt[wave][(uint32_t)(key[q] >> shift) & mask], 1u);
@@ -873,9 +872,8 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
         int32_t idx[kBigRounds];
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q) {
-          const uint32_t i = min(b + q * 64 + lane, n - 1);
-          key[q] = skey[i];
-          idx[q] = sidx[i];
+          idx[q] = sidx[min(b + q * 64 + lane, n - 1)];
+          key[q] = key_of(idx[q]);
         }
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q) {
@@ -886,7 +884,6 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
             const uint32_t rank = (uint32_t)__popcll(same & lt_mask);
             const uint32_t run = m.cnt[wave][digit];
             if (valid) {
-              dkey[run + rank] = key[q];
               didx[run + rank] = idx[q];
               if (rank == 0) m.cnt[wave][digit] = run + (uint32_t)__popcll(same);   // after every lane of the round has read
             }
@@ -895,16 +892,15 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
       }
       __syncthreads();   // the pass's global writes are visible to the whole workgroup (one compute unit, one L1)
     }
-    const uint64_t* big_sorted = a.big_key[(a.passes + 1) & 1] + start;
-    st.sorted = big_sorted;
+    const int32_t* ids = a.perm + start;
     uint32_t mine = 0;
     for (uint32_t b = wlo; b < whi; b += kBigRounds * 64) {
       uint64_t key[kBigRounds], prev[kBigRounds];
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
         const uint32_t i = min(b + q * 64 + lane, n - 1);
-        key[q] = big_sorted[i];
-        prev[q] = big_sorted[i == 0 ? 0 : i - 1];
+        key[q] = key_of(ids[i]);
+        prev[q] = key_of(ids[i == 0 ? 0 : i - 1]);
       }
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
@@ -945,7 +941,7 @@ __device__ __forceinline__ void write_bin(const BinArgs& a, uint32_t bin, uint32
     a.seg_of[assignment] = (int32_t)seg;
   };
   uint32_t x_tail = st.x_lo;                        // experts of this bin behind its last key
-  if (st.sorted == nullptr) {
+  if (!st.big) {
     const uint32_t rest = n - st.equal;
     if (st.equal != 0) {                            // the cluster of the common key
       if (tid == 0) sh.head_cnt[64] = st.heads - 1u;
@@ -986,6 +982,12 @@ __device__ __forceinline__ void write_bin(const BinArgs& a, uint32_t bin, uint32
     }
     if (rest > 0) x_tail = max(x_tail, (uint32_t)(m.key[rest - 1] >> a.bbits) + 1u);
   } else {
+    auto key_of = [&](int32_t id) {
+      uint64_t key;
+      int32_t unused;
+      load_item<true>(a.src, (uint32_t)id, key, unused);
+      return key;
+    };
     const uint32_t slice = ((n + kBinWaves - 1) / kBinWaves + 63u) & ~63u;
     const uint32_t wlo = min((uint32_t)wave * slice, n), whi = min(wlo + slice, n);
     uint32_t seg = base + st.heads_before;
@@ -995,9 +997,9 @@ __device__ __forceinline__ void write_bin(const BinArgs& a, uint32_t bin, uint32
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
         const uint32_t i = min(b + q * 64 + lane, n - 1);
-        key[q] = st.sorted[i];
-        prev[q] = st.sorted[i == 0 ? 0 : i - 1];
         idx[q] = a.perm[st.start + i];
+        key[q] = key_of(idx[q]);
+        prev[q] = key_of(a.perm[st.start + (i == 0 ? 0 : i - 1)]);
       }
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
@@ -1008,7 +1010,7 @@ __device__ __forceinline__ void write_bin(const BinArgs& a, uint32_t bin, uint32
         seg += (uint32_t)__popcll(hmask);
       }
     }
-    x_tail = max(x_tail, (uint32_t)(st.sorted[n - 1] >> a.bbits) + 1u);
+    x_tail = max(x_tail, (uint32_t)(key_of(a.perm[st.start + n - 1]) >> a.bbits) + 1u);
   }
   for (uint32_t x = x_tail + tid; x < st.x_hi; x += kBinThreads) a.expert_offsets[x] = (int32_t)(base + st.heads);
   if (tid == 0 && (DIRECT || bin == kBins - 1)) {
@@ -1158,18 +1160,28 @@ bool plan_group(int64_t T, int d, int k, int E, int L, int r, GroupPlan* plan) {
   p.spins = 1u << 10;
   p.seg_blocks = (uint32_t)((p.N + kSegTile - 1) / kSegTile);
   size_t off = 0;
-  for (int i = 0; i < 3; ++i) {
-    p.off_key[i] = off;
-    if (i < 2 || p.bins) off = align256(off + (size_t)p.N * 8);
+  if (!p.one_bin) {   // one workgroup keeps everything in LDS
+    for (int i = 0; i < 2; ++i) {
+      p.off_key[i] = off;
+      off = align256(off + (size_t)p.N * 8);
+    }
+    for (int i = 0; i < 2; ++i) {
+      p.off_idx[i] = off;
+      off = align256(off + (size_t)p.N * 4);
+    }
   }
-  for (int i = 0; i < 2; ++i) {
-    p.off_idx[i] = off;
-    off = align256(off + (size_t)p.N * 4);
+  if (p.bins) {
+    // The second key buffer is free.  The table (at most 4 N bytes + 1 KB) and behind it the bins' published counts and
+    // claims lie there: the sizes that the built-in scratch holds do not shrink for the sake of this route.
+    p.off_table = p.off_key[1];
+    p.off_blocksum = align256(p.off_table + (size_t)kBins * p.tiles * 4);
+    static_assert(4 * (size_t)kSmallMaxN >= 1024 + kSyncWords * 4, "room behind the table at every size of this route");
+  } else if (!p.one_bin) {
+    p.off_table = off;
+    off = align256(off + (size_t)kGroupBins * p.tiles * 4);
+    p.off_blocksum = off;   // head counts per numbering tile (+ 1)
+    off = align256(off + ((size_t)p.seg_blocks + 1) * 4);
   }
-  p.off_table = off;
-  off = align256(off + (p.bins ? (size_t)kBins * p.tiles * 4 : (size_t)kGroupBins * p.tiles * 4));
-  p.off_blocksum = off;   // head counts per numbering tile (+ 1), or the bins' published counts and claims
-  off = align256(off + (p.bins ? (size_t)kSyncWords : (size_t)p.seg_blocks + 1) * 4);
   const size_t windows = 2 * (size_t)((p.N + kCentroidWindow - 1) / kCentroidWindow);
   p.off_partial = off;
   off = align256(off + windows * (size_t)d * 4);
@@ -1185,7 +1197,7 @@ hipError_t launch_group(const GroupPlan& plan, const int32_t* expert, const uint
                         int32_t* seg_offsets, int32_t* seg_expert, int32_t* expert_offsets, int32_t* perm,
                         int32_t* seg_of, int32_t* num_segments, char* ws, hipStream_t stream) {
   const uint32_t N = (uint32_t)plan.N;
-  uint64_t* keybuf[3] = {(uint64_t*)(ws + plan.off_key[0]), (uint64_t*)(ws + plan.off_key[1]), (uint64_t*)(ws + plan.off_key[2])};
+  uint64_t* keybuf[2] = {(uint64_t*)(ws + plan.off_key[0]), (uint64_t*)(ws + plan.off_key[1])};
   int32_t* idxbuf[2] = {(int32_t*)(ws + plan.off_idx[0]), (int32_t*)(ws + plan.off_idx[1])};
   uint32_t* table = (uint32_t*)(ws + plan.off_table);
   uint32_t* blocksum = (uint32_t*)(ws + plan.off_blocksum);
@@ -1209,7 +1221,6 @@ hipError_t launch_group(const GroupPlan& plan, const int32_t* expert, const uint
       a.width[p] = plan.width[p];
     }
     a.sub_shift = plan.top_shift > kSubBits ? plan.top_shift - kSubBits : 0;
-    a.big_key[0] = keybuf[1]; a.big_key[1] = keybuf[2];
     a.big_idx = idxbuf[1];
     a.seg_offsets = seg_offsets; a.seg_expert = seg_expert; a.expert_offsets = expert_offsets;
     a.perm = perm; a.seg_of = seg_of; a.num_segments = num_segments;

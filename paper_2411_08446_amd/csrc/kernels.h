@@ -45,7 +45,7 @@ struct GroupPlan {
   uint32_t first_bin, spins;   // bins: see BinArgs (a test forces the takeover of bins with them)
   uint32_t seg_blocks;   // tiles of kSegTile sorted positions
   // byte offsets into the workspace
-  size_t off_key[3], off_idx[2], off_table, off_blocksum;
+  size_t off_key[2], off_idx[2], off_table, off_blocksum;
   size_t off_partial, off_counters;  // window sums and window counters of the centroid step
   size_t total_bytes;
 };

@@ -133,3 +133,18 @@ def test_binding_refuses_host_tensors():
     x = torch.zeros(4, 8)
     with pytest.raises(ValueError):
         lsh.lshmoe_hash(x, torch.zeros(1, 2, 8), torch.zeros(4, dtype=torch.int64))
+
+
+# (d, k, E, L, r), tokens: sizes that lshmoe_compress_static held before grouping went by bins (the largest T per row)
+STATIC_SIZES = [((1024, 2, 64, 4, 64), 94080), ((768, 1, 16, 2, 32), 229376), ((512, 1, 64, 4, 64), 293632),
+                ((256, 1, 64, 4, 64), 407968), ((128, 2, 8, 3, 20), 253344), ((64, 1, 64, 4, 64), 576384),
+                ((16, 1, 4, 2, 16), 642752), ((8, 1, 64, 4, 64), 655328), ((8, 8, 64, 10, 16), 81916),
+                ((4096, 2, 300, 2, 16), 29696), ((60000, 1, 4, 2, 16), 4352)]
+
+
+@pytest.mark.parametrize("shape,T", STATIC_SIZES)
+@pytest.mark.parametrize("dtype", [0, 1])
+def test_built_in_scratch_holds_the_sizes_it_held(lib, shape, T, dtype):
+    limit = 16 << 20
+    for t in (T, T - 1, T - 64, T // 2, T // 3, T // 16):
+        assert lsh.lshmoe_workspace_bytes(t, *shape, dtype) <= limit, t
