@@ -12,6 +12,8 @@
 // the workgroup share the cluster through LDS, beyond that the cluster is cut
 // into blocks of positions that many workgroups (or waves) sum side by side;
 // the one that finishes last adds the block sums in position order.
+#include <type_traits>
+
 #include "kernels.h"
 
 namespace lshmoe {
@@ -32,9 +34,17 @@ template <int LPR> __device__ __forceinline__ int32_t uniform(int32_t v) {
   return LPR == 64 ? __builtin_amdgcn_readfirstlane(v) : v;  // a whole wave shares the value: keep it scalar
 }
 
+// a + b without loss: a becomes the rounded sum, its rounding error is added to err (Knuth's two-sum; Kahan's shorter step
+// needs the larger operand first, which holds for a long sum's next row but not where sums of the same size meet).
+__device__ __forceinline__ void two_sum(float& a, float b, float& err) {
+  const float t = a + b, bb = t - a;
+  err += (a - (t - bb)) + (b - bb);
+  a = t;
+}
+
 // Compensated sum of the token rows at sorted positions [a, b), wave-wide: lanes stride over the 16-byte pieces
-// c_lo .. c_hi - 1 of the row, eight rows in flight (a walk by one wave is bound by memory latency).  emit(c, acc) receives the
-// sums of piece c.  Kept small in registers on purpose: the kernel's occupancy is set by its largest path.
+// c_lo .. c_hi - 1 of the row, eight rows in flight (a walk by one wave is bound by memory latency).  emit(c, acc, comp)
+// receives the sums of piece c and their compensations (the sum is acc - comp).  Kept small in registers on purpose: the kernel's occupancy is set by its largest path.
 template <typename DT, typename Emit>
 __device__ __forceinline__ void row_sum_kahan(const char* __restrict__ tokens, const int32_t* __restrict__ perm,
                                               int32_t a, int32_t b, uint32_t k, uint32_t c_lo, uint32_t c_hi,
@@ -81,21 +91,8 @@ __device__ __forceinline__ void row_sum_kahan(const char* __restrict__ tokens, c
         }
       }
     }
-    if (on) emit(c, acc);
+    if (on) emit(c, acc, comp);
   }
-}
-
-// ... written as binary32 to out_row: the sum of one window of a long cluster.
-template <typename DT>
-__device__ __forceinline__ void window_sum(const char* __restrict__ tokens, const int32_t* __restrict__ perm,
-                                           int32_t a, int32_t b, uint32_t k, uint32_t cpr, size_t row_bytes,
-                                           float* __restrict__ out_row) {
-  constexpr int E = Piece<DT>::kElems;
-  row_sum_kahan<DT>(tokens, perm, a, b, k, 0, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
-#pragma unroll
-    for (int i = 0; i < E; i += 4)
-      *(float4*)(out_row + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
-  });
 }
 
 // A cluster with more than kWindowMin members is summed by many waves: the sorted positions are cut into
@@ -104,19 +101,45 @@ __device__ __forceinline__ void window_sum(const char* __restrict__ tokens, cons
 // starting inside the block (slot 2m + 1; there is at most one, since a long cluster is longer than a block).
 // Every window bumps its cluster's counter; the wave that brings it to the cluster's window count adds the
 // partial sums in position order, so the result does not depend on which wave came last.
+//
+// The compensation of a window's sum is kept beside it, or a cluster of 257 to 1024 members would lose up to 0.4 times
+// the error of one wave's sum over all its rows (rms against binary64, Gaussian rows, 1024 members: one wave 1.07e-9,
+// windows without 1.48e-9, with 1.06e-9).  A block that lies in the cluster as a whole has its other slot free for it.  The
+// two ends of the cluster put theirs into the cluster's own centroid row, which is written last: rounded to bfloat16 (eight
+// bits of a correction will do) those of both ends fit a binary32 row, each 16-byte piece's into the piece itself.  Rows of
+// bfloat16 are rounded far above that; there the ends are added to their sums.
 template <typename DT>
 __device__ __forceinline__ void long_cluster_window(
     const char* __restrict__ tokens, const int32_t* __restrict__ perm, const int32_t* __restrict__ seg_offsets,
     char* __restrict__ centroids, float* partial, uint32_t* counters, int32_t s, int32_t a, int32_t b, uint32_t slot,
     uint32_t k, uint32_t cpr, uint32_t d, uint32_t mean) {
   constexpr int E = Piece<DT>::kElems;
+  constexpr bool kEndRows = std::is_same<DT, F32>::value;
   const size_t row_bytes = (size_t)cpr * 16;
   const uint32_t lane = threadIdx.x & 63;
   const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[s]);
   const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[s + 1]);
-  window_sum<DT>(tokens, perm, a, b, k, cpr, row_bytes, partial + (size_t)slot * d);
   const uint32_t m0 = (uint32_t)lo / kCentroidWindow, m1 = (uint32_t)(hi - 1) / kCentroidWindow;
   const uint32_t first_slot = 2 * m0 + ((uint32_t)lo % kCentroidWindow != 0 ? 1u : 0u);
+  char* dst = centroids + (size_t)s * row_bytes;
+  const bool whole = b - a == kCentroidWindow;      // blocks are aligned: the cluster covers this one
+  float* out_row = partial + (size_t)slot * d;
+  char* end_half = dst + (a == lo ? 0 : 8);         // the first end's corrections are the first half of each piece
+  row_sum_kahan<DT>(tokens, perm, a, b, k, 0, cpr, row_bytes, [&](uint32_t c, float (&acc)[E], const float (&comp)[E]) {
+    if (!kEndRows && !whole) {
+#pragma unroll
+      for (int i = 0; i < E; ++i) acc[i] -= comp[i];
+    }
+#pragma unroll
+    for (int i = 0; i < E; i += 4) {
+      *(float4*)(out_row + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+      if (whole)
+        *(float4*)(out_row + d + (size_t)c * E + i) = make_float4(comp[i], comp[i + 1], comp[i + 2], comp[i + 3]);
+      else if (kEndRows)
+        *(uint2*)(end_half + c * 16) =
+            make_uint2(f32_to_bf16_pair(comp[i], comp[i + 1]), f32_to_bf16_pair(comp[i + 2], comp[i + 3]));
+    }
+  });
   __threadfence();  // the partial row is visible device-wide before the counter moves
   uint32_t old = 0;
   if (lane == 0) old = atomicAdd(&counters[first_slot], 1u);
@@ -124,23 +147,35 @@ __device__ __forceinline__ void long_cluster_window(
   if (old != m1 - m0) return;
   __threadfence();  // last window of the cluster: every other partial row is complete and visible
   const uint32_t nwin = m1 - m0 + 1;
+  const bool whole0 = (uint32_t)lo % kCentroidWindow == 0, whole1 = (uint32_t)hi % kCentroidWindow == 0;
   const float fn = (float)(hi - lo), inv = 1.0f / fn;
-  char* dst = centroids + (size_t)s * row_bytes;
-  constexpr int kRows = 4;
+  constexpr int kRows = 2;
   for (uint32_t c = lane; c < cpr; c += 64) {
-    float acc[E], comp[E];
+    float acc[E], err[E];
 #pragma unroll
-    for (int i = 0; i < E; ++i) acc[i] = comp[i] = 0.0f;
+    for (int i = 0; i < E; ++i) acc[i] = err[i] = 0.0f;
+    if (kEndRows) {
+#pragma unroll
+      for (int end = 0; end < 2; ++end) {
+        if (end == 0 ? whole0 : whole1) continue;
+        const uint2 w = *(const uint2*)(dst + c * 16 + end * 8);
+        err[0] -= __uint_as_float(w.x << 16); err[1] -= __uint_as_float(w.x & 0xffff0000u);
+        err[2] -= __uint_as_float(w.y << 16); err[3] -= __uint_as_float(w.y & 0xffff0000u);
+      }
+    }
     for (uint32_t j = 0; j < nwin; j += kRows) {
-      float x[kRows][E];
+      float x[kRows][E], comp[kRows][E];
 #pragma unroll
       for (int u = 0; u < kRows; ++u) {
         const uint32_t jj = min(j + u, nwin - 1);
         const float* src = partial + (size_t)(jj == 0 ? first_slot : 2 * (m0 + jj)) * d + (size_t)c * E;
+        const bool whole_j = (jj != 0 || whole0) && (jj != nwin - 1 || whole1);
 #pragma unroll
         for (int i = 0; i < E; i += 4) {
           const float4 v = *(const float4*)(src + i);
+          const float4 w = whole_j ? *(const float4*)(src + d + i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
           x[u][i] = v.x; x[u][i + 1] = v.y; x[u][i + 2] = v.z; x[u][i + 3] = v.w;
+          comp[u][i] = w.x; comp[u][i + 1] = w.y; comp[u][i + 2] = w.z; comp[u][i + 3] = w.w;
         }
       }
 #pragma unroll
@@ -148,14 +183,14 @@ __device__ __forceinline__ void long_cluster_window(
         if (j + u < nwin) {
 #pragma unroll
           for (int i = 0; i < E; ++i) {
-            const float y = x[u][i] - comp[i];
-            const float t = acc[i] + y;
-            comp[i] = (t - acc[i]) - y;
-            acc[i] = t;
+            two_sum(acc[i], x[u][i], err[i]);
+            err[i] -= comp[u][i];
           }
         }
       }
     }
+#pragma unroll
+    for (int i = 0; i < E; ++i) acc[i] += err[i];
     if (mean) {
 #pragma unroll
       for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
@@ -164,13 +199,15 @@ __device__ __forceinline__ void long_cluster_window(
   }
 }
 
-
 // The same with workgroups (needs the LDS of the shared sums).  The sorted positions are cut into aligned blocks of W and
 // two workgroups take a block, each one half of the columns: every wave sums its quarter of the block's part of the
-// cluster into LDS, wave 0 adds the four in wave order, writes half a partial row and bumps the counter - a quarter of
-// the device-scope fences.  The workgroup that brings the counter to twice the cluster's block count adds the partial
+// cluster into LDS, wave 0 adds the four in wave order, writes half a partial row, fences and bumps the counter (two
+// device-scope fences per block).  The workgroup that brings the counter to twice the cluster's block count adds the partial
 // rows in position order, again a quarter per wave joined through LDS in wave order, so the result does not depend on
-// which workgroup came last.
+// which workgroup came last.  Every join is by two-sums, and the first takes the waves' compensations with it (in LDS, in
+// the columns of the other half): with plain sums the error was a third larger than that of four waves that share the
+// whole cluster (rms against binary64, Gaussian rows, 600 / 1024 members: 2.41 / 1.66e-9 for four waves, 3.00 / 2.21e-9
+// with plain joins, 2.28 / 1.57e-9 so).
 // Called by all four waves of the workgroup with the same arguments (barriers inside).
 //
 // W: a wave is bound by memory latency, about 1.8 us per round of eight rows and 64 pieces, and the partial rows are read
@@ -194,19 +231,25 @@ __device__ __forceinline__ void long_cluster_wg_window(
   const size_t row_bytes = (size_t)cpr * 16;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t w4 = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  uint32_t* last_flag = reinterpret_cast<uint32_t*>(coop_sum + (size_t)4 * d);   // one word behind the four rows
-  const uint32_t c_lo = half == 0 ? 0 : (cpr + 1) / 2, c_hi = half == 0 ? (cpr + 1) / 2 : cpr;
+  const uint32_t stride = d + E;   // a row in LDS: one piece more, for the compensations of the longer half
+  uint32_t* last_flag = reinterpret_cast<uint32_t*>(coop_sum + (size_t)4 * stride);   // one word behind the four rows
+  const uint32_t middle = (cpr + 1) / 2;
+  const uint32_t c_lo = half == 0 ? 0 : middle, c_hi = half == 0 ? middle : cpr;
+  const uint32_t to_comp = (half == 0 ? middle : 0u - middle) * E;   // from a column's sum to its compensation
   const int32_t qa = max(a, (int32_t)(block_p0 + w4 * (W / 4)));
   const int32_t qb = min(b, (int32_t)(block_p0 + (w4 + 1) * (W / 4)));
-  float* mine = coop_sum + (size_t)w4 * d;
+  float* mine = coop_sum + (size_t)w4 * stride;
   if (qa < qb) {
-    row_sum_kahan<DT>(tokens, perm, qa, qb, k, c_lo, c_hi, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
+    row_sum_kahan<DT>(tokens, perm, qa, qb, k, c_lo, c_hi, row_bytes,
+                      [&](uint32_t c, const float (&acc)[E], const float (&comp)[E]) {
 #pragma unroll
-      for (int i = 0; i < E; i += 4)
-        *(float4*)(mine + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+      for (int i = 0; i < E; i += 4) {
+        *(float4*)(mine + c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+        *(float4*)(mine + (c * E + to_comp) + i) = make_float4(comp[i], comp[i + 1], comp[i + 2], comp[i + 3]);
+      }
     });
   } else {
-    for (uint32_t i = c_lo * E + lane; i < c_hi * E; i += 64) mine[i] = 0.0f;
+    for (uint32_t i = c_lo * E + lane; i < c_hi * E; i += 64) mine[i] = mine[i + to_comp] = 0.0f;
   }
   const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[s]);
   const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[s + 1]);
@@ -217,13 +260,17 @@ __device__ __forceinline__ void long_cluster_wg_window(
   if (w4 == 0) {
     float* out_row = partial + (size_t)slot * d;
     for (uint32_t i = c_lo * E + lane * 4; i < c_hi * E; i += 256) {   // E is a multiple of 4
-      float4 v = *(const float4*)(coop_sum + i);
+      float4 v = *(const float4*)(coop_sum + i), e = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
 #pragma unroll
-      for (int w = 1; w < 4; ++w) {
-        const float4 u = *(const float4*)(coop_sum + (size_t)w * d + i);
-        v.x += u.x; v.y += u.y; v.z += u.z; v.w += u.w;
+      for (int w = 0; w < 4; ++w) {
+        const float4 u = *(const float4*)(coop_sum + w * stride + i);
+        const float4 q = *(const float4*)(coop_sum + w * stride + (i + to_comp));
+        if (w > 0) {
+          two_sum(v.x, u.x, e.x); two_sum(v.y, u.y, e.y); two_sum(v.z, u.z, e.z); two_sum(v.w, u.w, e.w);
+        }
+        e.x -= q.x; e.y -= q.y; e.z -= q.z; e.w -= q.w;
       }
-      *(float4*)(out_row + i) = v;
+      *(float4*)(out_row + i) = make_float4(v.x + e.x, v.y + e.y, v.z + e.z, v.w + e.w);
     }
     __threadfence();  // the partial row is visible device-wide before the counter moves
     if (lane == 0) *last_flag = atomicAdd(&counters[first_slot], 1u) == 2 * (m1 - m0) + 1 ? 1u : 0u;
@@ -236,9 +283,9 @@ __device__ __forceinline__ void long_cluster_wg_window(
   const uint32_t j0 = min(w4 * per, nwin), j1 = min(j0 + per, nwin);
   constexpr int kRows = 4;
   for (uint32_t c = lane; c < cpr; c += 64) {
-    float acc[E], comp[E];
+    float acc[E], err[E];
 #pragma unroll
-    for (int i = 0; i < E; ++i) acc[i] = comp[i] = 0.0f;
+    for (int i = 0; i < E; ++i) acc[i] = err[i] = 0.0f;
     for (uint32_t j = j0; j < j1; j += kRows) {
       float x[kRows][E];
 #pragma unroll
@@ -255,18 +302,14 @@ __device__ __forceinline__ void long_cluster_wg_window(
       for (int u = 0; u < kRows; ++u) {
         if (j + u < j1) {
 #pragma unroll
-          for (int i = 0; i < E; ++i) {
-            const float y = x[u][i] - comp[i];
-            const float t = acc[i] + y;
-            comp[i] = (t - acc[i]) - y;
-            acc[i] = t;
-          }
+          for (int i = 0; i < E; ++i) two_sum(acc[i], x[u][i], err[i]);
         }
       }
     }
 #pragma unroll
     for (int i = 0; i < E; i += 4)
-      *(float4*)(mine + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+      *(float4*)(mine + c * E + i) =
+          make_float4(acc[i] + err[i], acc[i + 1] + err[i + 1], acc[i + 2] + err[i + 2], acc[i + 3] + err[i + 3]);
   }
   __syncthreads();
   const float fn = (float)(hi - lo), inv = 1.0f / fn;
@@ -275,9 +318,11 @@ __device__ __forceinline__ void long_cluster_wg_window(
     float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) {
-      acc[i] = coop_sum[(size_t)c * E + i];
+      float err = 0.0f;
+      acc[i] = coop_sum[c * E + i];
 #pragma unroll
-      for (int w = 1; w < 4; ++w) acc[i] += coop_sum[((size_t)w * cpr + c) * E + i];
+      for (int w = 1; w < 4; ++w) two_sum(acc[i], coop_sum[w * stride + c * E + i], err);
+      acc[i] += err;
       if (mean) acc[i] = div_count(acc[i], fn, inv);
     }
     store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
@@ -292,7 +337,8 @@ __global__ __launch_bounds__(256) void centroid_kernel(
     float* partial, uint32_t* counters, uint32_t N, uint32_t k, uint32_t cpr, uint32_t mean, uint32_t coop) {
   constexpr int G = 64 / LPR;  // clusters handled side by side by one wave
   constexpr int E = Piece<DT>::kElems;
-  extern __shared__ float coop_sum[];  // coop: [4 waves][cpr * E] partial sums of a cluster the workgroup shares
+  // coop: [4 waves][cpr * E] partial sums of a cluster the workgroup shares, or [4 waves][(cpr + 1) * E] and a flag
+  extern __shared__ float coop_sum[];
   const uint32_t S = (uint32_t)*num_segments;
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t block64 = linear_block();
@@ -331,7 +377,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
       const int32_t a = min(lo + (int32_t)w4 * quarter, hi), b = min(a + quarter, hi);
       float* mine = coop_sum + (size_t)w4 * cpr * E;
       if (a < b) {
-        row_sum_kahan<DT>(tokens, perm, a, b, k, 0, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E]) {
+        row_sum_kahan<DT>(tokens, perm, a, b, k, 0, cpr, row_bytes, [&](uint32_t c, const float (&acc)[E], const float (&)[E]) {
 #pragma unroll
           for (int i = 0; i < E; i += 4)
             *(float4*)(mine + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
@@ -360,12 +406,12 @@ __global__ __launch_bounds__(256) void centroid_kernel(
     const int32_t lo = uniform<LPR>(seg_offsets[s]), hi = uniform<LPR>(seg_offsets[s + 1]);
     const int32_t n = hi - lo;
     if (shared_size(n)) {
-      // left to the workgroup, below
+      // done by the workgroup, above
     } else if (LPR == 64 && n > kPlainSumMax && n <= kWindowMin) {
       // a whole wave on a cluster of more than 16 members: compensated sum, eight rows in flight
       char* dst = centroids + (size_t)s * row_bytes;
       const float fn = (float)n, inv = 1.0f / fn;
-      row_sum_kahan<DT>(tokens, perm, lo, hi, k, 0, cpr, row_bytes, [&](uint32_t c, float (&acc)[E]) {
+      row_sum_kahan<DT>(tokens, perm, lo, hi, k, 0, cpr, row_bytes, [&](uint32_t c, float (&acc)[E], const float (&)[E]) {
         if (mean) {
 #pragma unroll
           for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
@@ -501,7 +547,8 @@ void launch_lpr(const void* tokens, const int32_t* perm, const int32_t* seg_offs
   const uint32_t blocks = (uint32_t)((waves + 3) / 4);
   const size_t coop_bytes = (size_t)4 * cpr * Piece<DT>::kElems * sizeof(float);  // four partial rows in binary32
   const bool coop = LPR == 64 && coop_bytes <= kCoopMaxLds;
-  hipLaunchKernelGGL((centroid_kernel<DT, LPR>), grid_of_blocks(blocks), dim3(256), coop ? coop_bytes + 16 : 0, stream,
+  constexpr size_t kCoopMore = 4 * Piece<DT>::kElems * sizeof(float) + 16;   // a piece more per row, the flag
+  hipLaunchKernelGGL((centroid_kernel<DT, LPR>), grid_of_blocks(blocks), dim3(256), coop ? coop_bytes + kCoopMore : 0, stream,
                      (const char*)tokens, perm, seg_offsets, seg_of, num_segments, (char*)centroids, partial, counters,
                      (uint32_t)N, (uint32_t)k, cpr, mean ? 1u : 0u, coop ? 1u : 0u);
 }

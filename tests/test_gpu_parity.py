@@ -820,3 +820,50 @@ def test_hash_grid_beyond_one_dimension(H):
     samp = np.unique(np.concatenate([rng.integers(0, T, 4000), [0, T - 1, (1 << 29) - 1, 1 << 29, (1 << 29) + 31, (1 << 29) + 32]]))
     st = torch.from_numpy(samp).cuda()
     H.check_hash(bt[st].cpu().numpy().view(np.uint64), H.to_storage(xt[st], "f32"), rot, "f32")
+
+
+def _kahan_sums(rows):
+    # compensated sums over axis 1 of [C, n, d] in binary32
+    acc, comp = np.zeros_like(rows[:, 0]), np.zeros_like(rows[:, 0])
+    for j in range(rows.shape[1]):
+        y = rows[:, j] - comp
+        t = acc + y
+        comp = (t - acc) - y
+        acc = t
+    return acc
+
+
+@pytest.mark.parametrize("n", [257, 600, 1024])
+@pytest.mark.parametrize("d,C", [(768, 24), (32, 500), (16, 1000), (2056, 8)])   # blocks by workgroups; by waves (narrow, wide rows)
+def test_sums_of_long_clusters_are_as_good_as_one_walk(H, n, d, C):
+    # C clusters of n members in blocks of positions: the rms error against binary64 is held to that of the sum without
+    # blocks, replayed here: four compensated quarters added up where a workgroup shares a cluster, one compensated walk
+    # where a wave has it.  2 per cent are for the statistics of C * d >= 16000 rounding errors (a standard error of 0.6).
+    rng = np.random.default_rng(n + d)
+    lead = 37                                           # off the grid of the blocks
+    x = rng.standard_normal((lead + C * n, d)).astype(np.float32)
+    ids = np.zeros(lead + C * n, np.int64)
+    where = lead + rng.permutation(C * n)               # member j of cluster c, in the order of the tokens
+    cluster = np.empty(C * n, np.int64)
+    cluster[where - lead] = np.repeat(np.arange(C), n)
+    ids[lead:] = 1 + cluster
+    E, L, r = 1, 3, 16
+    xt = torch.from_numpy(x).cuda()
+    out = H.lsh.CompressOutputs.allocate(lead + C * n, d, 1, E, L, r, torch.float32)
+    print("case sums n", n, "d", d, flush=True)
+    H.lsh.lshmoe_compress(xt, torch.zeros((lead + C * n, 1), dtype=torch.int32, device="cuda"), torch.from_numpy(ids).cuda(),
+                          E, L, r, out)
+    torch.cuda.synchronize()
+    assert int(out.num_segments) == C + 1
+    got = out.centroids[1:C + 1].cpu().numpy().astype(np.float64)
+    rows = x[lead:][np.argsort(cluster, kind="stable")].reshape(C, n, d)
+    exact = rows.astype(np.float64).mean(axis=1)
+    if 256 < d * 4 <= 8192:
+        q = (n + 3) // 4
+        plain = sum((_kahan_sums(rows[:, w * q:(w + 1) * q]) for w in range(1, 4)), start=_kahan_sums(rows[:, :q]))
+    else:
+        plain = _kahan_sums(rows)
+    ref = float(np.sqrt((((plain / np.float32(n)).astype(np.float64) - exact) ** 2).mean()))
+    rms = float(np.sqrt(((got - exact) ** 2).mean()))
+    print("  rms error %.3e, without blocks %.3e" % (rms, ref), flush=True)
+    assert rms <= 1.02 * ref
