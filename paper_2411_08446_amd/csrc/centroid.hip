@@ -12,8 +12,6 @@
 // the workgroup share the cluster through LDS, beyond that the cluster is cut
 // into blocks of positions that many workgroups (or waves) sum side by side;
 // the one that finishes last adds the block sums in position order.
-#include <type_traits>
-
 #include "kernels.h"
 
 namespace lshmoe {
@@ -193,7 +191,7 @@ __device__ __forceinline__ void long_cluster_window(
     for (int i = 0; i < E; ++i) acc[i] += err[i];
     if (mean) {
 #pragma unroll
-      for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
+      for (int i = 0; i < E; ++i) acc[i] = div_count<DT>(acc[i], fn, inv);
     }
     store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
   }
@@ -323,7 +321,7 @@ __device__ __forceinline__ void long_cluster_wg_window(
 #pragma unroll
       for (int w = 1; w < 4; ++w) two_sum(acc[i], coop_sum[w * stride + c * E + i], err);
       acc[i] += err;
-      if (mean) acc[i] = div_count(acc[i], fn, inv);
+      if (mean) acc[i] = div_count<DT>(acc[i], fn, inv);
     }
     store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
   }
@@ -395,7 +393,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
           acc[i] = coop_sum[(size_t)c * E + i];
 #pragma unroll
           for (int w = 1; w < 4; ++w) acc[i] += coop_sum[((size_t)w * cpr + c) * E + i];
-          if (mean) acc[i] = div_count(acc[i], fn, inv);
+          if (mean) acc[i] = div_count<DT>(acc[i], fn, inv);
         }
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       }
@@ -414,7 +412,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
       row_sum_kahan<DT>(tokens, perm, lo, hi, k, 0, cpr, row_bytes, [&](uint32_t c, float (&acc)[E], const float (&)[E]) {
         if (mean) {
 #pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
+          for (int i = 0; i < E; ++i) acc[i] = div_count<DT>(acc[i], fn, inv);
         }
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       });
@@ -477,7 +475,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
         if (mean) {
           const float fn = (float)n, inv = 1.0f / fn;
 #pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] = div_count(acc[i], fn, inv);
+          for (int i = 0; i < E; ++i) acc[i] = div_count<DT>(acc[i], fn, inv);
         }
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       }

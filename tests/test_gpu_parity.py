@@ -867,3 +867,31 @@ def test_sums_of_long_clusters_are_as_good_as_one_walk(H, n, d, C):
     rms = float(np.sqrt(((got - exact) ** 2).mean()))
     print("  rms error %.3e, without blocks %.3e" % (rms, ref), flush=True)
     assert rms <= 1.02 * ref
+
+
+@pytest.mark.parametrize("d", [16, 128, 768])          # lane groups and whole waves per row
+def test_subnormal_rows_are_divided_exactly(H, d):
+    # Binary32 rows of whole multiples of 2^-149: their sums are exact here, so means and token gradients are one
+    # correctly rounded division by the member count.  Clusters of 2 to 40, 200 and 300 members.
+    rng = np.random.default_rng(d)
+    sizes = list(range(2, 41)) + [200, 300]
+    T, S, E, L, r = sum(sizes), len(sizes), 1, 3, 16
+    x = (rng.integers(-4000, 4000, (T, d)).astype(np.float64) * 2.0 ** -149).astype(np.float32)
+    ids = np.repeat(np.arange(S), sizes)
+    xt, bt = torch.from_numpy(x).cuda(), torch.from_numpy(ids).cuda()
+    out = H.lsh.CompressOutputs.allocate(T, d, 1, E, L, r, torch.float32)
+    print("case subnormal rows d", d, flush=True)
+    H.lsh.lshmoe_compress(xt, torch.zeros((T, 1), dtype=torch.int32, device="cuda"), bt, E, L, r, out)
+    h = torch.from_numpy((rng.integers(-4000, 4000, (S, d)).astype(np.float64) * 2.0 ** -149).astype(np.float32)).cuda()
+    grad = torch.empty((T, d), device="cuda")
+    H.lsh.lshmoe_compress_backward(None, h, None, out.seg_of, out.seg_offsets, 1, grad, flags=H.lsh.LSHMOE_FLAG_NO_RESIDUAL)
+    torch.cuda.synchronize()
+    assert int(out.num_segments) == S
+    offs = np.concatenate([[0], np.cumsum(sizes)])
+    sums = np.add.reduceat(x.astype(np.float64), offs[:-1], axis=0)       # exact
+    n = np.array(sizes, dtype=np.float64)[:, None]
+    step = 2.0 ** -149
+    ref = np.rint(sums / step / n)                                        # halves to even, as the format rounds
+    assert np.array_equal(out.centroids[:S].cpu().numpy().astype(np.float64) / step, ref)
+    ref = np.rint(h.cpu().numpy().astype(np.float64) / step / n)
+    assert np.array_equal(grad.cpu().numpy().astype(np.float64) / step, np.repeat(ref, sizes, axis=0))
