@@ -60,6 +60,13 @@ __device__ __forceinline__ void load_item(const KeySource& src, uint32_t i, uint
   }
 }
 
+__device__ __forceinline__ uint64_t key_of(const KeySource& src, int32_t id) {   // the key of an assignment
+  uint64_t key;
+  int32_t unused;
+  load_item<true>(src, (uint32_t)id, key, unused);
+  return key;
+}
+
 // Lanes of the wave whose `bits`-bit digit equals this lane's, among the lanes with `valid` (bits <= kMaxDigitBits,
 // wave-uniform).
 __device__ __forceinline__ uint64_t same_digit_lanes(uint32_t digit, int bits, bool valid) {
@@ -330,20 +337,43 @@ __global__ __launch_bounds__(kSegThreads) void seg_write_kernel(
 constexpr int kBinBits = 8;
 constexpr int kBins = 1 << kBinBits;
 static_assert(kBins == kSortThreads, "one bin per thread of tile_bin_kernel");
+// Words that the workgroups of bin_group_kernel exchange, zero on entry.  parts: the most parts that large bins are cut
+// into (max_parts).
 constexpr uint32_t kClaimStride = 8;         // four claims to a 128-byte line: exchanges on one word or line queue up
-constexpr uint32_t kSyncWords = kBins * (1 + kClaimStride);   // published head counts of the bins, then their claims
+constexpr uint32_t kCountAt = 0;             // published cluster counts: bins, then parts
+constexpr uint32_t kArriveAt = 2 * kBins;    // parts of a bin that have their count, and the sum of the counts
+constexpr uint32_t kTotalAt = 3 * kBins;     // keys of the bins (published when some bin may be large)
+constexpr uint32_t kClaimAt = 4 * kBins;     // claims: bins, then parts
+constexpr int kPeaks = kSortThreads / kWave;
+__host__ __device__ constexpr uint32_t sync_words(uint32_t parts) { return kClaimAt + (kBins + parts) * kClaimStride; }
+
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) {   // in the last lane: the largest of the lanes
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xf, 0xf, false));   // row_shr:1
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xf, 0xf, false));   // row_shr:2
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xf, 0xf, false));   // row_shr:4
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xf, 0xf, false));   // row_shr:8
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xa, 0xf, false));   // row_bcast:15 into rows 1 and 3
+  v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xc, 0xf, false));   // row_bcast:31 into rows 2 and 3
+  return v;
+}
 
 template <int TILE>
 __global__ __launch_bounds__(kSortThreads) void tile_bin_kernel(KeySource src, uint32_t N, int shift,
                                                                 uint32_t* __restrict__ table, uint64_t* __restrict__ dst_key,
-                                                                int32_t* __restrict__ dst_idx, uint32_t* __restrict__ sync) {
+                                                                int32_t* __restrict__ dst_idx, uint32_t* __restrict__ sync,
+                                                                uint32_t parts, uint32_t* __restrict__ peak) {
   constexpr int kItems = TILE / kSortThreads, kGroups = TILE / kWave;
   static_assert(TILE <= 0xffff, "start and count of a bin in a tile share a word");
   __shared__ uint32_t cnt[kGroups][kBins];   // keys of a bin in a group of 64; then the group's first position of it
   __shared__ uint32_t wave_sum[kSortThreads / kWave];
   if (blockIdx.x == 0) {                     // what bin_group_kernel expects to find cleared
-    sync[threadIdx.x] = 0;
-    sync[kBins + threadIdx.x * kClaimStride] = 0;
+    static_assert(kBins == kSortThreads, "a word of each kind per thread");
+    sync[kCountAt + threadIdx.x] = 0;
+    sync[kCountAt + kBins + threadIdx.x] = 0;
+    sync[kArriveAt + threadIdx.x] = 0;
+    sync[kTotalAt + threadIdx.x] = 0;
+    sync[kClaimAt + threadIdx.x * kClaimStride] = 0;
+    if (threadIdx.x < parts) sync[kClaimAt + (kBins + threadIdx.x) * kClaimStride] = 0;
   }
   const uint32_t base = blockIdx.x * TILE;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -376,6 +406,8 @@ __global__ __launch_bounds__(kSortThreads) void tile_bin_kernel(KeySource src, u
     uint32_t unused;
     uint32_t run = block_exclusive_scan(total, wave_sum, unused);
     table[blockIdx.x * kBins + threadIdx.x] = run | (total << 16);
+    const uint32_t most = wave_max(total);   // of this wave's quarter of the bins
+    if (lane == 63) peak[blockIdx.x * kPeaks + wave] = most;
 #pragma unroll
     for (int g = 0; g < kGroups; ++g) {
       cnt[g][threadIdx.x] = run;
@@ -406,11 +438,11 @@ __global__ __launch_bounds__(kSortThreads) void tile_bin_kernel(KeySource src, u
 //
 // The wait for the bins before.  A workgroup claims its bin with an exchange on the bin's claim word, publishes the
 // bin's count before it waits for anything, and waits only for counts.  When one does not come it tries to claim the
-// lowest bin that is still open: if that succeeds, the bin's own workgroup has not started (and will leave when it
-// does), and the waiting workgroup does the bin itself - nothing before it is open, so without a wait - and then
+// lowest bin that is still open: if that succeeds, the bin's own workgroup has not started (and will leave it alone when
+// it does), and the waiting workgroup does the bin itself - nothing before it is open, so without a wait - and then
 // returns to its own; if not, the bin's owner is running and will publish.  So every wait ends, whatever else runs on
 // the GPU and in whatever order workgroups are started.  (A ticket counter gives the same, but 256 workgroups adding
-// to one word took 3.4 us.)  The counts and claims are the only data exchanged inside the launch, as relaxed
+// to one word took 3.4 us.)  Counts, claims and sizes of bins are the only data exchanged inside the launch, as relaxed
 // device-scope accesses: no fence is needed.
 //
 // Sorting up to kBinCap keys, two ways:
@@ -421,9 +453,25 @@ __global__ __launch_bounds__(kSortThreads) void tile_bin_kernel(KeySource src, u
 //     from ballots.  Cost grows with the number of digits, whatever the data.
 // A pass costs about as much as comparing with kCrowdPerPass keys, so the sub-bins are taken when no sub-bin holds
 // more than that many keys per pass saved, and never for a single pass (25088 assignments of a Zipf gate: 14.2 us
-// with sub-bins, 10.5 without).
-// Larger bins: see sort_bin.  Everything must fit the 128 registers of a 1024-thread workgroup: a kernel that spills
+// with sub-bins, 10.5 without).  Everything must fit the 128 registers of a 1024-thread workgroup: a kernel that spills
 // a few of them to scratch memory starts 3 to 8 us later, which is why kBinCap is not 8192.
+//
+// Large bins, of more than kBinCap keys.  There is none when the largest counts that the tiles have of any bin add up to no
+// more than that; this costs a few words per tile and is so on balanced inputs.  Otherwise every workgroup publishes the
+// size of its bin, and all of them learn which bins are large.
+//   One key makes up most of the bin (padding; 1024 samples say so): its assignments go straight to their place in perm
+//     without a sort and the rest is sorted in LDS, by the bin's own workgroup.
+//   Else the bin is cut into parts of about 1024 keys (up to 2048 on the largest inputs: there are no more parts than
+//     workgroups) by key ranges, at equal steps of a sorted sample of its keys.  The bin's workgroup does the first part,
+//     workgroups of small bins the others, after they have published their own bin's count and before they write that bin,
+//     whose sorted ids are set aside in perm.  For a part the sample is sorted and the bin walked to pick out the part's
+//     keys; then the part is like a bin, with a count and a claim of its own; the last part of a bin to be counted
+//     publishes the bin's count.  A key that is frequent itself begins a part (the sample has it at a step) and takes the
+//     way of the padding there.
+// A part that is large all the same (the sample missed it) is radix sorted through global memory by its workgroup.
+// Measured, compress call at d = 8, against one workgroup per bin, whatever its size, and (in brackets) the four launches
+// before: 65536 and 131072 assignments of a Zipf gate over 64 experts, whose first holds a quarter, 54 -> 44 us (48) and
+// 64 -> 50 us (56); 131072 of one expert of 64 243 -> 60 us (174); half of 131072 with one expert of 256 488 -> 93 us (255).
 //
 // DIRECT: the whole input (up to kSmallMaxN assignments) is the one bin of a single workgroup.
 constexpr int kXcds = 8;
@@ -435,7 +483,11 @@ constexpr int kSubBits = 12;
 constexpr int kSubBins = 1 << kSubBits;
 static_assert(kBinThreads >= kBins && kSubBins % kBinThreads == 0, "counters per thread");
 constexpr uint32_t kCrowdPerPass = 32;
-constexpr int kBigRounds = 4;                       // rounds of 64 keys a wave has in flight in a larger bin
+constexpr int kBigRounds = 4;                       // rounds of 64 keys a wave has in flight on a walk
+constexpr uint32_t kSampleOnceMax = 1u << 16;       // keys of a bin up to which a sample of 1024 cuts it into parts; else 4096
+constexpr int kTotalLooks = 64;                     // looks at the sizes of the bins before they are added up from the table
+constexpr uint32_t kPartKeys = 1024;                // keys of a part, at least
+constexpr uint32_t kWaveSlot = kBinCap / kBinWaves; // LDS places of a wave on a walk
 static_assert(kSmallMaxN <= kBinCap, "a single workgroup sorts the smallest inputs in LDS");
 
 struct BinLds {
@@ -450,25 +502,45 @@ struct BinLds {
 };
 static_assert(sizeof(BinLds) <= 140 * 1024, "LDS of a compute unit, less the rest of the kernel");
 
-struct BinArgs {
-  KeySource src;              // DIRECT, and the keys of a bin of more than kBinCap keys
+struct BinArgs {               // what is needed first comes first: the fields arrive by cache lines
+  uint32_t* sync;             // sync_words(), zero on entry (not used with DIRECT)
   const uint32_t* table;      // [tiles][kBins]: start of the bin inside the tile | keys << 16
+  const uint4* peak;          // [tiles]: the largest count in each quarter of the bins
+  uint32_t tiles, tile_bits;
   const uint64_t* tile_key;   // the tiles, each sorted by bin
   const int32_t* tile_idx;
-  uint32_t tiles, tile_bits;
+  int passes;                 // radix passes over the key bits below the bin
+  int sub_shift;              // sub-bin of a key is (key >> sub_shift) & (kSubBins - 1)
+  uint32_t spins;             // looks at the open counts before a workgroup tries to take one of them over
   uint32_t N, E;
   int bbits, top_shift;       // bin of a key is key >> top_shift
-  int passes;                 // radix passes over the key bits below the bin
-  int shift[8], width[8];
-  int sub_shift;              // sub-bin of a key is (key >> sub_shift) & (kSubBins - 1)
-  int32_t* big_idx;           // the ids of a bin of more than kBinCap keys go between here and perm
   int32_t *seg_offsets, *seg_expert, *expert_offsets, *perm, *seg_of, *num_segments;
-  uint32_t* sync;             // kSyncWords, zero on entry (not used with DIRECT)
   uint32_t* window_counters;  // cleared here for the centroid step
   uint32_t n_counters;
   uint32_t first_bin;         // the workgroups of the bins before it leave at once (0; a test forces the takeover of bins with it)
-  uint32_t spins;             // looks at the open counts before a workgroup tries to take one of them over
+  int shift[8], width[8];
+  uint32_t part_keys;         // keys of a part, on average
+  int32_t* big_idx;           // the ids of a part that is sorted through global memory go between here and perm
+  KeySource src;              // DIRECT, and keys that are made again
 };
+
+// A value that all lanes have in common, kept in scalar registers: what comes out of LDS would sit in vector ones.
+__device__ __forceinline__ uint32_t scalar(uint32_t v) { return (uint32_t)__builtin_amdgcn_readfirstlane((int)v); }
+__device__ __forceinline__ uint64_t scalar(uint64_t v) {
+  return (uint64_t)scalar((uint32_t)(v >> 32)) << 32 | scalar((uint32_t)v);
+}
+
+// Code that balanced inputs do not need goes behind the rest: what they run is read into the instruction cache in one piece.
+__device__ __forceinline__ bool seldom(bool v) { return __builtin_expect(v, false); }
+
+// threadIdx.x, as a value that the compiler must take for a new one: what it computes from it would otherwise be moved out of
+// the loop over a workgroup's turns, and has to be spilled there.
+__device__ __forceinline__ uint32_t own_thread() {
+  uint32_t tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));
+  __builtin_assume(tid < (uint32_t)kBinThreads);
+  return tid;
+}
 
 // Inclusive sum over the lanes of the wave, in the vector unit's cross-lane paths (no LDS).
 __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
@@ -484,19 +556,35 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t v) {
 // Exclusive scan of one value per thread of the workgroup.  One barrier inside; the next one that the caller passes
 // frees wave_sum.
 __device__ __forceinline__ uint32_t bin_exclusive_scan(uint32_t v, uint32_t* wave_sum /*[kBinWaves]*/, uint32_t& total) {
-  const int wave = threadIdx.x >> 6;
+  const uint32_t tid = own_thread(), wave = tid >> 6;
   const uint32_t inc = wave_inclusive_sum(v);
-  if ((threadIdx.x & 63) == 63) wave_sum[wave] = inc;
+  if ((tid & 63) == 63) wave_sum[wave] = inc;
   __syncthreads();
   uint32_t before = 0;
   total = 0;
 #pragma unroll
-  for (int w = 0; w < kBinWaves; ++w) {
+  for (uint32_t w = 0; w < (uint32_t)kBinWaves; ++w) {
     const uint32_t t = wave_sum[w];
     if (w < wave) before += t;
     total += t;
   }
+  total = scalar(total);
   return before + inc - v;
+}
+
+// Whether any thread of the workgroup says so.  One barrier inside; said may be used again behind the next one.
+__device__ __forceinline__ bool workgroup_any(bool v, uint32_t* said /*[kBinWaves], 16-byte aligned*/) {
+  const uint32_t tid = own_thread();
+  const bool any = __any(v);
+  if ((tid & 63) == 0) said[tid >> 6] = any ? 1u : 0u;
+  __syncthreads();
+  uint32_t all = 0;
+#pragma unroll
+  for (int w = 0; w < kBinWaves; w += 4) {
+    const uint4 q = *reinterpret_cast<const uint4*>(said + w);
+    all |= q.x | q.y | q.z | q.w;
+  }
+  return scalar(all) != 0u;
 }
 
 // Digit counts per wave -> start offsets in (digit, wave) order.  Called by the whole workgroup between two barriers.
@@ -542,46 +630,127 @@ __device__ __forceinline__ void count_round_digits(uint32_t* cnt, const uint64_t
   }
 }
 
-struct BinShared {
-  uint32_t wave_sum[2][kBinWaves];
-  uint32_t tile_before[kMaxTiles], tile_from[kMaxTiles];   // keys of the bin in earlier tiles; where the tile's begin
-  uint32_t head_cnt[65];             // clusters in, then before, a round of one wave; [64]: ... before the common key
-  uint32_t claimed, open_bin;
-};
+// What a workgroup works on: a whole bin, item i for bin i, or a part, item kBins + i for part i of all.
+constexpr uint32_t kNoItem = ~0u;
 
-struct BinState {                    // a sorted bin
-  uint32_t n, start, heads;          // keys, first position, clusters
-  uint32_t x_lo, x_hi;               // experts whose first possible key lies in this bin: their offsets are written with it
-  bool big;                          // the sorted ids are in perm; else keys and ids are in LDS
+struct BinState {                    // a sorted bin or part; in LDS, so that it takes no registers while others are sorted
+  uint32_t n, start;                 // keys, first position
   uint32_t less, equal;              // in LDS: the first `less` keys come before `equal` ones that are `common`
   uint64_t common;
-  uint32_t heads_before;             // big: clusters before the wave's slice
 };
 
-// Collects and sorts a bin and counts its clusters.  taken: not 0 in thread 0 when the bin belongs to another
-// workgroup; the answer is false then.
-template <bool DIRECT>
-__device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_t taken, BinLds& m,
-                                         BinShared& sh, BinState& st) {
-  const uint32_t tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const uint64_t lt_mask = (1ull << lane) - 1ull;
+struct BinShared {
+  uint32_t wave_sum[3][kBinWaves];
+  __align__(16) uint32_t said[3][kBinWaves];
+  uint32_t tile_before[kMaxTiles], tile_from[kMaxTiles];   // keys of the bin in earlier tiles; where the tile's begin
+  uint4 wave_four[kBinWaves];
+  uint32_t head_cnt[65];             // clusters in, then before, a round of one wave (big: its slice); [64]: ... before the common key
+  uint32_t claimed, open, my_part, my_bin, interrupted, interrupted_bin;
+  uint32_t total[kBins], first_part[kBins];                // when some bin may be large: keys, number of the first part
+  BinState state[2];                 // of a bin, of a part
+  uint32_t column_n, column_start;   // of the own bin, when some bin may be large
+  uint64_t range_lo, range_hi;       // the part's keys: from range_lo on (but for the first part), below range_hi (but for the last)
+  uint64_t sub_base;                 // its sub-bins: (key - sub_base) >> sub_shift
+  int sub_shift;
+  uint32_t aside, aside_heads[kBinWaves];   // clusters of the own bin (top bit: in perm) and its head_cnt, set aside
+};
+
+__device__ __forceinline__ uint32_t parts_of(const BinArgs& a, uint32_t n) { return n > (uint32_t)kBinCap ? n / a.part_keys : 0u; }
+
+// Learns the sizes of all bins (from their workgroups; from the table if one does not come) and numbers the parts of the
+// large ones.  sh.my_part: the part that falls to this workgroup, or kNoItem, and its bin.
+__device__ __forceinline__ void number_parts(const BinArgs& a, uint32_t own, BinShared& sh) {
+  const uint32_t tid = own_thread();
+  uint32_t v = 0;
+  bool all = false;
+  for (int look = 0; look < kTotalLooks && !all; ++look) {
+    if (tid < kBins && v == 0) v = __hip_atomic_load(&a.sync[kTotalAt + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    all = !workgroup_any(tid < kBins && v == 0, sh.said[look & 1]);
+  }
+  if (tid < kBins) sh.total[tid] = all ? v - 1u : 0u;
+  if (tid == 0) sh.my_part = kNoItem;
+  __syncthreads();
+  if (!all) {
+    constexpr uint32_t kRows = kBinThreads / kBins, kBatch = 8;   // rows of the table side by side, loads in flight
+    const uint32_t bin = tid % kBins;
+    uint32_t sum = 0;
+    for (uint32_t t0 = tid / kBins; t0 < a.tiles; t0 += kRows * kBatch) {
+      uint32_t e[kBatch];
+#pragma unroll
+      for (uint32_t q = 0; q < kBatch; ++q) {
+        const uint32_t t = t0 + q * kRows;
+        e[q] = t < a.tiles ? a.table[t * kBins + bin] : 0u;
+      }
+#pragma unroll
+      for (uint32_t q = 0; q < kBatch; ++q) sum += e[q] >> 16;
+    }
+    atomicAdd(&sh.total[bin], sum);
+    __syncthreads();
+  }
+  // Numbers of the parts, and of the workgroups for them: part 0 of a bin is its own workgroup's, the others fall to those
+  // whose bins are not large (there are no more than 256 parts in all, so they are enough), of at most average size first.
+  const uint32_t n = tid < kBins ? sh.total[tid] : 0u, parts = parts_of(a, n);
+  const bool average = tid < kBins && parts == 0 && n <= min(a.N / kBins, (uint32_t)kBinThreads);
+  const bool more = tid < kBins && parts == 0 && !average;
+  uint32_t all_of;
+  const uint32_t at = bin_exclusive_scan(parts << 20 | (average ? 1u << 10 : 0u) | (more ? 1u : 0u), sh.wave_sum[0], all_of);
+  const uint32_t first = at >> 20, averages = (at >> 10) & 1023u, mores = at & 1023u;
+  if (tid < kBins) sh.first_part[tid] = first;
+  if (tid == own) sh.open = average ? averages : more ? ((all_of >> 10) & 1023u) + mores : kNoItem;   // which of them this is
+  __syncthreads();
+  const uint32_t me = sh.open, first_other = first - (tid - averages - mores);   // large bins before: one part each is not for others
+  if (tid < kBins && parts != 0) {
+    const uint32_t q = tid == own ? 0u : 1u + (me - first_other);
+    if (tid == own || (me != kNoItem && me >= first_other && q < parts)) {
+      sh.my_part = kBins + first + q;
+      sh.my_bin = tid;
+    }
+  }
+  __syncthreads();
+}
+
+// The code of a workgroup: the whole input; a bin, none being large; anything when some bin may be large.  The second is
+// what balanced inputs run: with the third's code in between it took 1 us more to arrive.
+enum { kDirect, kBalanced, kCrowded };
+
+// Collects and sorts a bin or part and counts its clusters.  taken: not 0 in thread 0 when it belongs to another
+// workgroup.  own: the item is the workgroup's own bin and this the first turn.
+// False: the item is another's, or the bin is done in parts, or the part's bin as a whole (LDS still holds what was sorted
+// before then), or some bin may be large, which kBalanced finds on the first turn (crowded).  True: heads are its clusters;
+// big: the sorted ids are in perm, else keys and ids are in LDS.  With kCrowded the workgroup's own bin, if it is large and
+// done in parts, becomes its first part.
+template <int MODE>
+__device__ __forceinline__ bool sort_item(const BinArgs& a, uint32_t& item, uint32_t bin, uint32_t taken, bool own,
+                                          bool& crowded, uint32_t& heads, bool& big, BinLds& m, BinShared& sh) {
+  constexpr bool DIRECT = MODE == kDirect, CROWDED = MODE == kCrowded;
+  uint32_t tid = own_thread();
+  int lane = tid & 63, wave = tid >> 6;
+  bool part = CROWDED && item >= kBins;
   uint32_t n = a.N, start = 0;
-  if (!DIRECT) {
+  if (CROWDED && own) {                             // kBalanced has been here
+    n = scalar(sh.column_n);
+    start = scalar(sh.column_start);
+  } else if (!DIRECT) {
     static_assert(kMaxTiles == kBins && kMaxTiles % 64 == 0, "one tile per thread of the first waves");
-    uint32_t keys = 0, first = 0;
+    uint32_t keys = 0, first = 0, most = 0;
     if (tid < a.tiles) {
       const uint32_t e = a.table[tid * kBins + bin];
+      if (own) {
+        const uint4 p = a.peak[tid];
+        most = max(max(p.x, p.y), max(p.z, p.w));
+      }
       first = e & 0xffffu;
       keys = e >> 16;
     }
+    const uint32_t inc_most = wave_inclusive_sum(most);
     const uint32_t inc = wave_inclusive_sum(keys), inc_first = wave_inclusive_sum(first);
     if (lane == 63) {
       sh.wave_sum[0][wave] = inc;
       sh.wave_sum[1][wave] = inc_first;
+      sh.wave_sum[2][wave] = inc_most;
     }
     __syncthreads();
-    uint32_t before = inc - keys;
+    uint32_t before = inc - keys, bound = 0;
     n = 0;
 #pragma unroll
     for (int w = 0; w < kMaxTiles / 64; ++w) {      // later waves hold no tile
@@ -589,50 +758,57 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
       if (w < wave) before += c;
       n += c;
       start += sh.wave_sum[1][w];
+      bound += sh.wave_sum[2][w];
     }
+    n = scalar(n);
+    start = scalar(start);
     if (tid < a.tiles) {
       sh.tile_before[tid] = before;
       sh.tile_from[tid] = (tid << a.tile_bits) + first - before;   // source of element i of the bin: tile_from + i
     }
     if (tid == 0) sh.claimed = taken == 0;
+    if (MODE == kBalanced && own) {
+      crowded = scalar(bound) > (uint32_t)kBinCap;
+      if (seldom(crowded) && tid == 0) {
+        sh.column_n = n;
+        sh.column_start = start;
+        __hip_atomic_store(&a.sync[kTotalAt + bin], n + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
     __syncthreads();
-    if (!sh.claimed) return false;                  // the bin is done by a workgroup that waited for it
   }
-  // experts whose first possible key lies in this bin: their offsets are written here
-  uint32_t x_lo = 0, x_hi = a.E;
-  if (!DIRECT) {
-    const int up = a.bbits - a.top_shift;
-    x_lo = up >= 0 ? (bin + (1u << up) - 1u) >> up : bin << -up;
-    x_hi = up >= 0 ? (bin + 1u + (1u << up) - 1u) >> up : (bin + 1u) << -up;
-    x_lo = min(x_lo, a.E);
-    x_hi = min(x_hi, a.E);
-  }
-  auto fetch = [&](uint32_t i, uint64_t& key, int32_t& idx) {   // element i < n of the bin, in assignment order
+  if (MODE == kBalanced && seldom(crowded)) return false;
+  if (!DIRECT && seldom(scalar(sh.claimed) == 0u)) return false;   // done by a workgroup that waited for it
+  auto tile_of = [&](uint32_t i, uint32_t lo, uint32_t hi) {    // last tile with tile_before <= i, of those from lo on before hi
+    while (hi - lo > 1) {
+      const uint32_t mid = (lo + hi) >> 1;
+      if (sh.tile_before[mid] <= i) lo = mid; else hi = mid;
+    }
+    return lo;
+  };
+  // element i < n of the bin, in assignment order
+  auto fetch = [&](uint32_t i, uint32_t tile_lo, uint32_t tile_hi, uint64_t& key, int32_t& idx) {
     if (DIRECT) {
       load_item<true>(a.src, i, key, idx);
     } else {
-      uint32_t lo = 0, hi = a.tiles;                // last tile with tile_before <= i
-      while (hi - lo > 1) {
-        const uint32_t mid = (lo + hi) >> 1;
-        if (sh.tile_before[mid] <= i) lo = mid; else hi = mid;
-      }
+      const uint32_t lo = tile_of(i, tile_lo, tile_hi);
       key = a.tile_key[sh.tile_from[lo] + i];
       idx = a.tile_idx[sh.tile_from[lo] + i];
     }
   };
 
-  // A bin of more than kBinCap keys is hardly ever made of many clusters: it is the one key that a share of the tokens
-  // has in common (padding).  If one key makes up most of the bin, its assignments go straight to their place in perm
-  // (two walks over the bin, no sort) and the rest, if it is small enough, is sorted in LDS.  (26000 equal keys among
-  // 131072, compress call at d = 8: 132 us, 361 with the passes below.)  Else the same radix passes as in LDS run
-  // through global memory, by the one workgroup.  Only ids are moved: the keys are made from the inputs again in every
-  // walk, so that the workspace holds no further key buffers.
-  uint32_t less = n, equal = 0;                     // rest[0, less) comes before the common key, `equal` keys are it
+  enum { kSample, kPick, kSort };
+  int step = kSort;
+  bool picked = false;                              // the keys to sort are in LDS
+  uint32_t common_heads = 0;
+  big = false;
   uint64_t common = 0;
-  if (!DIRECT && n > (uint32_t)kBinCap) {
-    uint64_t key;
+  if (CROWDED && n > (uint32_t)kBinCap) {
+    uint64_t key, own_key;
     int32_t idx;
-    fetch((uint32_t)(((uint64_t)n * (2u * lane + 1u)) >> 7), key, idx);   // 64 samples, the same in every wave
+    fetch((uint32_t)(((uint64_t)n * (2u * lane + 1u)) >> 7), 0, a.tiles, key, idx);         // 64 samples, the same in every wave
+    fetch((uint32_t)(((uint64_t)n * (2u * tid + 1u)) >> 11), 0, a.tiles, own_key, idx);     // 1024, one per thread
+    static_assert(kBinThreads == 1 << 10, "samples per workgroup");
     uint32_t best = 0;
     for (int l = 0; l < 64; l += 4) {               // sixteen candidates
       const uint64_t o = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(key >> 32), l) << 32) |
@@ -643,92 +819,217 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
         common = o;
       }
     }
-    // worth the walk when three quarters of the share that is needed shows up in the samples
-    if (best > 1 && (uint64_t)best * n * 4u >= (uint64_t)(n - kBinCap) * (64u * 3u)) {
+    uint32_t hits;
+    bin_exclusive_scan(own_key == common ? 1u : 0u, sh.wave_sum[0], hits);
+    __syncthreads();
+    // the other keys, by the sample, fill half of LDS at most: twice as many still fit
+    if ((uint64_t)(kBinThreads - hits) * n <= (uint64_t)kBinThreads * (kBinCap / 2)) {
+      if (part) return false;
+      step = kPick;
+    } else {
+      if (!part && !own) return false;
+      if (n <= kSampleOnceMax) {                    // the sample in hand will do: 16 keys and more per part
+        m.key[tid] = own_key;
+        m.idx[tid] = (int32_t)tid;
+        picked = true;
+      }
+      if (!part) {
+        number_parts(a, bin, sh);
+        item = scalar(sh.my_part);
+        part = true;
+        if (tid == 0) sh.claimed = atomicExch(&a.sync[kClaimAt + item * kClaimStride], 1u) == 0u;
+        __syncthreads();
+        if (!sh.claimed) return false;
+      }
+      step = kSample;
+    }
+  }
+
+  BinState& st = sh.state[part ? 1 : 0];
+  if (tid == 0) {
+    st.n = n;
+    st.start = start;
+    st.less = n;
+    st.equal = 0;
+    st.common = common;
+  }
+  uint32_t rest = n;                                // keys to sort
+  for (;;) {
+    const uint32_t tid = own_thread();
+    const int lane = tid & 63, wave = tid >> 6;
+    const uint64_t lt_mask = (1ull << lane) - 1ull;
+    if (CROWDED && step == kPick) {
+      // the keys of a part, or of a bin that is mostly one key
+      __syncthreads();
+      const uint32_t n = scalar(st.n), bin_start = scalar(st.start);
+      bool has_lo = false, has_hi = false;
+      uint64_t range_lo = 0, range_hi = 0;
+      if (part) {
+        const uint32_t q = item - kBins - scalar(sh.first_part[bin]);
+        has_lo = q > 0;
+        has_hi = q + 1 < parts_of(a, n);
+        range_lo = scalar(sh.range_lo);
+        range_hi = scalar(sh.range_hi);
+      }
+      const uint64_t common = part ? range_lo : scalar(st.common);
       const uint32_t hslice = ((n + kBinWaves - 1) / kBinWaves + 63u) & ~63u;
-      const uint32_t hlo = min((uint32_t)wave * hslice, n), hhi = min(hlo + hslice, n);
-      uint32_t eq = 0, lt = 0;
+      const uint32_t hlo = scalar(min((uint32_t)wave * hslice, n)), hhi = min(hlo + hslice, n);
+      uint32_t tile_lo = 0, tile_hi = a.tiles;      // tiles of the slice; finding them takes longer than a short walk gains
+      if (n > 4u * kBinCap) {
+        tile_lo = scalar(tile_of(min(hlo, n - 1), 0, a.tiles));
+        tile_hi = scalar(tile_of(max(hhi, 1u) - 1, 0, a.tiles)) + 1;
+      }
       auto walk = [&](auto&& f) {                   // f(valid, key, idx) for every round of the wave's slice
         for (uint32_t b = hlo; b < hhi; b += kBigRounds * 64) {
           uint64_t k[kBigRounds];
           int32_t id[kBigRounds];
 #pragma unroll
-          for (int q = 0; q < kBigRounds; ++q) fetch(min(b + q * 64 + lane, n - 1), k[q], id[q]);
+          for (int q = 0; q < kBigRounds; ++q) fetch(min(b + q * 64 + lane, hhi - 1), tile_lo, tile_hi, k[q], id[q]);
 #pragma unroll
           for (int q = 0; q < kBigRounds; ++q) f(b + q * 64 + lane < hhi, k[q], id[q]);
         }
       };
-      walk([&](bool valid, uint64_t k, int32_t) {
-        eq += (uint32_t)__popcll(__ballot(valid && k == common));
-        lt += (uint32_t)__popcll(__ballot(valid && k < common));
+      // keys before the part, of it, of the common key, of the part before that; the part's go to the wave's places in LDS
+      // as long as there are any left
+      uint32_t below = 0, in = 0, eq = 0, lt = 0;
+      walk([&](bool valid, uint64_t k, int32_t id) {
+        const bool low = has_lo && k < range_lo, inside = valid && !low && !(has_hi && k >= range_hi);
+        const uint64_t r = __ballot(inside);
+        if (part) {
+          const uint32_t at = in + (uint32_t)__popcll(r & lt_mask);
+          if (inside && at < kWaveSlot) {
+            m.key[wave * kWaveSlot + at] = k;
+            m.idx[wave * kWaveSlot + at] = id;
+          }
+        }
+        below += (uint32_t)__popcll(__ballot(valid && low));
+        in += (uint32_t)__popcll(r);
+        eq += (uint32_t)__popcll(__ballot(inside && k == common));
+        lt += (uint32_t)__popcll(__ballot(inside && k < common));
       });
-      uint32_t eq_all, lt_all;
-      uint32_t eq_at = bin_exclusive_scan(lane == 0 ? eq : 0u, sh.wave_sum[0], eq_all);
-      bin_exclusive_scan(lane == 0 ? lt : 0u, sh.wave_sum[1], lt_all);
-      if (n - eq_all <= (uint32_t)kBinCap) {
-        less = lt_all;
-        equal = eq_all;
-        eq_at = (uint32_t)__builtin_amdgcn_readfirstlane((int)eq_at);
-        uint32_t rest_at = hlo - eq_at;             // keys of the rest before this wave's slice
+      if (lane == 0) sh.wave_four[wave] = make_uint4(in, eq, lt, below);
+      __syncthreads();
+      uint32_t rest_at = 0, eq_at = 0, in_all = 0, eq_all = 0, lt_all = 0, below_all = 0, in_most = 0;
+#pragma unroll
+      for (int w = 0; w < kBinWaves; ++w) {
+        const uint4 c = sh.wave_four[w];
+        if (w < wave) {
+          rest_at += c.x;
+          eq_at += c.y;
+        }
+        in_all += c.x;
+        eq_all += c.y;
+        lt_all += c.z;
+        below_all += c.w;
+        in_most = max(in_most, c.x);
+      }
+      in_all = scalar(in_all);
+      eq_all = scalar(eq_all);
+      rest_at = scalar(rest_at);
+      eq_at = scalar(eq_at);
+      const uint32_t start = bin_start + scalar(below_all);
+      uint32_t less = in_all, equal = 0;            // rest[0, less) comes before the common key, `equal` keys are it
+      if (in_all > (uint32_t)kBinCap) {
+        if (in_all - eq_all <= (uint32_t)kBinCap) {
+          less = scalar(lt_all);
+          equal = eq_all;
+          rest_at -= eq_at;
+        } else {
+          big = true;
+        }
+      }
+      if (part && scalar(in_most) <= kWaveSlot) {   // all of them are there: closed up
+        static_assert(kWaveSlot == kBinItems * 64, "a wave's places in its registers");
+        uint64_t k[kBinItems];
+        int32_t id[kBinItems];
+#pragma unroll
+        for (int q = 0; q < kBinItems; ++q) {
+          k[q] = m.key[wave * kWaveSlot + q * 64 + lane];
+          id[q] = m.idx[wave * kWaveSlot + q * 64 + lane];
+        }
+        __syncthreads();
+#pragma unroll
+        for (int q = 0; q < kBinItems; ++q) {
+          if (q * 64 + (uint32_t)lane < in) {
+            m.key[rest_at + q * 64 + lane] = k[q];
+            m.idx[rest_at + q * 64 + lane] = id[q];
+          }
+        }
+      } else {                                      // another walk, that knows the places
+        int32_t* ids = ((a.passes & 1) ? a.big_idx : a.perm) + start;   // big: the last pass leaves the ids in perm
         walk([&](bool valid, uint64_t k, int32_t id) {
-          const uint64_t e = __ballot(valid && k == common), r = __ballot(valid && k != common);
-          if (valid && k == common) a.perm[start + less + eq_at + (uint32_t)__popcll(e & lt_mask)] = id;
-          if (valid && k != common) {
-            m.key[rest_at + (uint32_t)__popcll(r & lt_mask)] = k;
-            m.idx[rest_at + (uint32_t)__popcll(r & lt_mask)] = id;
+          const bool inside = valid && !(has_lo && k < range_lo) && !(has_hi && k >= range_hi);
+          const bool same = equal != 0 && k == common;
+          const uint64_t e = __ballot(inside && same), r = __ballot(inside && !same);
+          if (inside && same) a.perm[start + less + eq_at + (uint32_t)__popcll(e & lt_mask)] = id;
+          if (inside && !same) {
+            const uint32_t at = rest_at + (uint32_t)__popcll(r & lt_mask);
+            if (big) {
+              ids[at] = id;
+            } else {
+              m.key[at] = k;
+              m.idx[at] = id;
+            }
           }
           eq_at += (uint32_t)__popcll(e);
           rest_at += (uint32_t)__popcll(r);
         });
       }
+      rest = in_all - equal;
+      common_heads = equal != 0 ? 1u : 0u;
+      picked = true;
+      step = kSort;
+      if (tid == 0) {                               // every thread has read the bin's
+        st.n = in_all;
+        st.start = start;
+        st.less = less;
+        st.equal = equal;
+        st.common = common;
+      }
       __syncthreads();
+      if (big) break;
     }
-  }
-  const uint32_t rest = n - equal;                  // keys to sort
-  const bool big = !DIRECT && rest > (uint32_t)kBinCap;
-  st.big = big;
-  auto key_of = [&](int32_t id) {
-    uint64_t key;
-    int32_t unused;
-    load_item<true>(a.src, (uint32_t)id, key, unused);
-    return key;
-  };
-  const uint32_t slice = ((rest + kBinWaves - 1) / kBinWaves + 63u) & ~63u;   // keys per wave, whole rounds
-  const uint32_t wlo = min((uint32_t)wave * slice, rest), whi = min(wlo + slice, rest);
-  uint32_t heads = 0;
-
-  if (!big) {
     uint64_t key[kBinItems];
     int32_t idx[kBinItems];
+    uint32_t zero = 0;                              // not a constant that sits in registers through the turns
+    asm volatile("" : "+v"(zero));
+    if (CROWDED && step == kSample) rest = picked ? (uint32_t)kBinThreads : (uint32_t)kBinCap;
 #pragma unroll
     for (int q = 0; q < kBinItems; ++q) {
       const uint32_t i = tid + q * kBinThreads;
       if (i < rest) {
-        if (equal == 0) {
-          fetch(i, key[q], idx[q]);
-        } else {
+        if (CROWDED && picked) {
           key[q] = m.key[i];
           idx[q] = m.idx[i];
+        } else {
+          fetch(CROWDED && step == kSample ? (uint32_t)(((uint64_t)i * st.n) / kBinCap) : i, 0, a.tiles, key[q], idx[q]);
         }
       }
     }
-    if (equal != 0) __syncthreads();
+    if (CROWDED && picked) __syncthreads();
+    const uint32_t slice = ((rest + kBinWaves - 1) / kBinWaves + 63u) & ~63u;   // keys per wave, whole rounds
+    const uint32_t wlo = min((uint32_t)wave * slice, rest), whi = min(wlo + slice, rest);
     bool sorted = false;
     if (a.passes > 1) {
       constexpr int kPer = kSubBins / kBinThreads;    // neighbouring sub-bins of a thread
       static_assert(kPer == 4, "moved 16 bytes at a time");
-      const int sub_shift = a.sub_shift;
-      auto sub_of = [&](uint64_t k) { return (uint32_t)(k >> sub_shift) & (kSubBins - 1); };
-      reinterpret_cast<uint4*>(m.sub.cnt)[tid] = make_uint4(0, 0, 0, 0);
+      const bool ranged = CROWDED && part && step == kSort;    // of a part's range
+      const uint64_t sub_base = ranged ? scalar(sh.sub_base) : 0;
+      const int sub_shift = ranged ? (int)scalar((uint32_t)sh.sub_shift) : a.sub_shift;
+      auto sub_of = [&](uint64_t k) { return (uint32_t)((k - sub_base) >> sub_shift) & (kSubBins - 1); };
+      reinterpret_cast<uint4*>(m.sub.cnt)[tid] = make_uint4(zero, zero, zero, zero);
       __syncthreads();
-      uint32_t slot[kBinItems];
+      uint32_t slot[kBinItems];                       // sub-bin << 16 | arrival
 #pragma unroll
       for (int q = 0; q < kBinItems; ++q)
-        if (tid + q * kBinThreads < rest) slot[q] = atomicAdd(&m.sub.cnt[sub_of(key[q])], 1u);
+        if (tid + q * kBinThreads < rest) {
+          const uint32_t sub = sub_of(key[q]);
+          slot[q] = atomicAdd(&m.sub.cnt[sub], 1u) | sub << 16;
+        }
       __syncthreads();
       const uint4 c = reinterpret_cast<const uint4*>(m.sub.cnt)[tid];
       const uint32_t most = max(max(c.x, c.y), max(c.z, c.w));
-      if (!__syncthreads_or(most > kCrowdPerPass * (uint32_t)a.passes)) {
+      if (!workgroup_any(most > kCrowdPerPass * (uint32_t)a.passes, sh.said[2])) {
         uint32_t unused;
         const uint32_t run = bin_exclusive_scan(c.x + c.y + c.z + c.w, sh.wave_sum[0], unused);
         reinterpret_cast<uint4*>(m.sub.base)[tid] = make_uint4(run, run + c.x, run + c.x + c.y, run + c.x + c.y + c.z);
@@ -736,7 +1037,7 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
 #pragma unroll
         for (int q = 0; q < kBinItems; ++q) {
           if (tid + q * kBinThreads < rest) {
-            const uint32_t at = m.sub.base[sub_of(key[q])] + slot[q];
+            const uint32_t at = m.sub.base[slot[q] >> 16] + (slot[q] & 0xffffu);
             m.key[at] = key[q];
             m.idx[at] = idx[q];
           }
@@ -746,7 +1047,7 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
 #pragma unroll
         for (int q = 0; q < kBinItems; ++q) {
           if (tid + q * kBinThreads < rest) {
-            const uint32_t sub = sub_of(key[q]);
+            const uint32_t sub = slot[q] >> 16;
             uint32_t t = m.sub.base[sub];
             const uint32_t end = t + m.sub.cnt[sub];
             rank[q] = t;
@@ -790,7 +1091,7 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
         const uint32_t mask = (1u << width) - 1u;
         __syncthreads();                            // the counters are no longer read
         for (int i = tid; i < kBinWaves * kGroupBins / 4; i += kBinThreads)
-          reinterpret_cast<uint4*>(&m.cnt[0][0])[i] = make_uint4(0, 0, 0, 0);
+          reinterpret_cast<uint4*>(&m.cnt[0][0])[i] = make_uint4(zero, zero, zero, zero);
         __syncthreads();                            // also: the keys are in LDS
         uint32_t place[kBinItems];
 #pragma unroll
@@ -815,6 +1116,23 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
       }
     }
     __syncthreads();
+    if (!CROWDED || step == kSort) break;
+    // the range of the part: steps of the sorted sample
+    if (tid == 0) {
+      const uint32_t parts = parts_of(a, st.n), q = item - kBins - sh.first_part[bin];
+      uint64_t lo = (uint64_t)bin << a.top_shift, hi = lo + (1ull << a.top_shift);   // hi: 0 at the end of 64 bits
+      if (q > 0) sh.range_lo = lo = m.key[q * rest / parts];
+      if (q + 1 < parts) sh.range_hi = hi = m.key[(q + 1) * rest / parts];
+      sh.sub_base = lo;
+      const uint64_t span = hi - lo - 1;            // an empty part has no use for it
+      sh.sub_shift = max(64 - kSubBits - (int)__clzll((long long)span), 0);
+    }
+    step = kPick;
+  }
+  tid = own_thread();
+  lane = tid & 63;
+  wave = tid >> 6;
+  if (!CROWDED || !big) {
     // heads: a key that differs from the one before it (the first key of a bin always starts a cluster)
 #pragma unroll
     for (int q = 0; q < kBinItems; ++q) {
@@ -826,27 +1144,16 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
     __syncthreads();
     static_assert(kBinItems * kBinWaves == 64, "one round of one wave per lane");
     const uint32_t mine = sh.head_cnt[lane], inc = wave_inclusive_sum(mine);
-    heads = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63) + (equal != 0 ? 1u : 0u);
+    heads = (uint32_t)__builtin_amdgcn_readlane((int)inc, 63) + common_heads;
     __syncthreads();
     if (wave == 0) sh.head_cnt[lane] = inc - mine;   // read after the barriers of the wait for the bins before
-    if (DIRECT) __syncthreads();
   } else {
-    // the ids are collected into one piece of global memory, then radix passes there; every wave walks its slice 64
-    // keys at a time, twice per pass
-    {
-      int32_t* ids = ((a.passes & 1) ? a.big_idx : a.perm) + start;   // the last pass leaves the ids in perm
-      for (uint32_t b = tid; b < n; b += kBigRounds * kBinThreads) {
-        uint64_t key[kBigRounds];
-        int32_t idx[kBigRounds];
-#pragma unroll
-        for (int q = 0; q < kBigRounds; ++q) fetch(min(b + q * kBinThreads, n - 1), key[q], idx[q]);
-#pragma unroll
-        for (int q = 0; q < kBigRounds; ++q) {
-          if (b + q * kBinThreads < n) ids[b + q * kBinThreads] = idx[q];
-        }
-      }
-      __syncthreads();
-    }
+    // radix passes through global memory, of ids alone: the keys are made from the inputs again on every walk, so that
+    // the workspace holds no further key buffers.  Every wave walks its slice 64 keys at a time, twice per pass.
+    const uint32_t n = scalar(st.n), start = scalar(st.start), zero = 0;
+    const uint64_t lt_mask = (1ull << lane) - 1ull;
+    const uint32_t slice = ((n + kBinWaves - 1) / kBinWaves + 63u) & ~63u;
+    const uint32_t wlo = min((uint32_t)wave * slice, n), whi = min(wlo + slice, n);
     for (int p = 0; p < a.passes; ++p) {
       const int shift = a.shift[p], width = a.width[p];
       const uint32_t mask = (1u << width) - 1u;
@@ -854,12 +1161,12 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
       const int32_t* sidx = (to_perm ? a.big_idx : a.perm) + start;
       int32_t* didx = (to_perm ? a.perm : a.big_idx) + start;
       for (int i = tid; i < kBinWaves * kGroupBins / 4; i += kBinThreads)
-        reinterpret_cast<uint4*>(&m.cnt[0][0])[i] = make_uint4(0, 0, 0, 0);
+        reinterpret_cast<uint4*>(&m.cnt[0][0])[i] = make_uint4(zero, zero, zero, zero);
       __syncthreads();
       for (uint32_t b = wlo; b < whi; b += kBigRounds * 64) {   // several rounds of loads in flight
         uint64_t key[kBigRounds];
 #pragma unroll
-        for (int q = 0; q < kBigRounds; ++q) key[q] = key_of(sidx[min(b + q * 64 + lane, n - 1)]);
+        for (int q = 0; q < kBigRounds; ++q) key[q] = key_of(a.src, sidx[min(b + q * 64 + lane, n - 1)]);
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q)
           if (b + q * 64 + lane < whi) atomicAdd(&m.cnt[wave][(uint32_t)(key[q] >> shift) & mask], 1u);
@@ -873,7 +1180,7 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q) {
           idx[q] = sidx[min(b + q * 64 + lane, n - 1)];
-          key[q] = key_of(idx[q]);
+          key[q] = key_of(a.src, idx[q]);
         }
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q) {
@@ -899,8 +1206,8 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
         const uint32_t i = min(b + q * 64 + lane, n - 1);
-        key[q] = key_of(ids[i]);
-        prev[q] = key_of(ids[i == 0 ? 0 : i - 1]);
+        key[q] = key_of(a.src, ids[i]);
+        prev[q] = key_of(a.src, ids[i == 0 ? 0 : i - 1]);
       }
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
@@ -908,43 +1215,60 @@ __device__ __forceinline__ bool sort_bin(const BinArgs& a, uint32_t bin, uint32_
         mine += (uint32_t)__popcll(__ballot(i < whi && (i == 0 || key[q] != prev[q])));
       }
     }
-    st.heads_before = bin_exclusive_scan(lane == 0 ? mine : 0u, sh.wave_sum[0], heads);
-    st.heads_before = (uint32_t)__shfl((int)st.heads_before, 0, 64);   // heads before this wave's slice
+    const uint32_t heads_before = bin_exclusive_scan(lane == 0 ? mine : 0u, sh.wave_sum[0], heads);
+    if (lane == 0) sh.head_cnt[wave] = heads_before;   // before this wave's slice
   }
-  st.n = n;
-  st.start = start;
-  st.less = less;
-  st.equal = equal;
-  st.common = common;
-  st.heads = heads;
-  st.x_lo = x_lo;
-  st.x_hi = x_hi;
+  if (DIRECT) __syncthreads();
   return true;
 }
 
-// Writes the outputs of a sorted bin; `base` clusters come before it.
-template <bool DIRECT>
-__device__ __forceinline__ void write_bin(const BinArgs& a, uint32_t bin, uint32_t base, const BinLds& m, BinShared& sh,
-                                          const BinState& st) {
-  const uint32_t tid = threadIdx.x;
+// Writes the outputs of a sorted bin or part; `base` clusters come before it.
+template <int MODE>
+__device__ __forceinline__ void write_item(const BinArgs& a, uint32_t item, uint32_t bin, uint32_t n, uint32_t start,
+                                           uint32_t heads, uint32_t equal, bool big, uint32_t base, const BinLds& m,
+                                           BinShared& sh, const BinState& st) {
+  const uint32_t tid = own_thread();
   const int lane = tid & 63, wave = tid >> 6;
   const uint64_t le_mask = ((1ull << lane) - 1ull) | (1ull << lane);
-  const uint32_t n = st.n;
+  constexpr bool DIRECT = MODE == kDirect, CROWDED = MODE == kCrowded;
+  const uint32_t less = CROWDED && equal != 0 ? scalar(st.less) : n;
+  // experts whose first possible key lies in the range: their offsets are written here
+  uint32_t x_lo = 0, x_hi = a.E;
+  bool last = true;
+  if (!DIRECT) {
+    const int up = a.bbits - a.top_shift;
+    x_lo = up >= 0 ? (bin + (1u << up) - 1u) >> up : bin << -up;
+    x_hi = up >= 0 ? (bin + 1u + (1u << up) - 1u) >> up : (bin + 1u) << -up;
+    last = bin == kBins - 1;
+    if (CROWDED && item >= kBins) {
+      auto first_expert = [&](uint64_t k) {         // the first expert whose possible keys begin at k or later
+        return (uint32_t)(k >> a.bbits) + ((k & ((1ull << a.bbits) - 1ull)) != 0 ? 1u : 0u);
+      };
+      const uint32_t q = item - kBins - scalar(sh.first_part[bin]);
+      if (q > 0) x_lo = first_expert(scalar(sh.range_lo));
+      if (q + 1 < parts_of(a, scalar(sh.total[bin]))) {
+        x_hi = first_expert(scalar(sh.range_hi));
+        last = false;
+      }
+    }
+    x_lo = min(x_lo, a.E);
+    x_hi = min(x_hi, a.E);
+  }
   auto emit = [&](uint32_t i, uint64_t key, uint64_t prev, bool head, uint32_t seg, int32_t assignment) {
     if (head) {
       const uint32_t e = (uint32_t)(key >> a.bbits);
-      a.seg_offsets[seg] = (int32_t)(st.start + i);
+      a.seg_offsets[seg] = (int32_t)(start + i);
       a.seg_expert[seg] = (int32_t)e;
       // experts that start (or are empty) between the key before and this one
-      for (uint32_t x = i == 0 ? st.x_lo : (uint32_t)(prev >> a.bbits) + 1u; x <= e; ++x) a.expert_offsets[x] = (int32_t)seg;
+      for (uint32_t x = i == 0 ? x_lo : (uint32_t)(prev >> a.bbits) + 1u; x <= e; ++x) a.expert_offsets[x] = (int32_t)seg;
     }
     a.seg_of[assignment] = (int32_t)seg;
   };
-  uint32_t x_tail = st.x_lo;                        // experts of this bin behind its last key
-  if (!st.big) {
-    const uint32_t rest = n - st.equal;
-    if (st.equal != 0) {                            // the cluster of the common key
-      if (tid == 0) sh.head_cnt[64] = st.heads - 1u;
+  uint32_t x_tail = x_lo;                        // experts of this bin behind its last key
+  if (!CROWDED || !big) {
+    const uint32_t rest = n - equal;
+    if (CROWDED && equal != 0) {                            // the cluster of the common key
+      if (tid == 0) sh.head_cnt[64] = heads - 1u;
       __syncthreads();
     }
 #pragma unroll
@@ -956,50 +1280,44 @@ __device__ __forceinline__ void write_bin(const BinArgs& a, uint32_t bin, uint32
         const bool head = i == 0 || key != prev;
         const uint64_t hmask = __ballot(head);
         uint32_t seg = base + sh.head_cnt[q * kBinWaves + wave] + (uint32_t)__popcll(hmask & le_mask) - 1u;
-        if (i < st.less) {
-          a.perm[st.start + i] = idx;
+        if (!CROWDED || i < less) {
+          a.perm[start + i] = idx;
           emit(i, key, prev, head, seg, idx);
         } else {                                    // behind the common key
-          if (i == st.less) sh.head_cnt[64] = seg - base;
-          a.perm[st.start + st.equal + i] = idx;
-          emit(st.equal + i, key, i == st.less ? st.common : prev, head, seg + 1u, idx);
+          if (i == less) sh.head_cnt[64] = seg - base;
+          a.perm[start + equal + i] = idx;
+          emit(equal + i, key, i == less ? st.common : prev, head, seg + 1u, idx);
         }
       }
     }
-    if (st.equal != 0) {
+    if (CROWDED && equal != 0) {
       __syncthreads();
       const uint32_t seg = base + sh.head_cnt[64];
-      if (tid == 0) emit(st.less, st.common, st.less == 0 ? st.common : m.key[st.less - 1], true, seg, a.perm[st.start + st.less]);
-      for (uint32_t b = tid; b < st.equal; b += kBigRounds * kBinThreads) {
+      if (tid == 0) emit(less, st.common, less == 0 ? st.common : m.key[less - 1], true, seg, a.perm[start + less]);
+      for (uint32_t b = tid; b < equal; b += kBigRounds * kBinThreads) {
         int32_t idx[kBigRounds];
 #pragma unroll
-        for (int q = 0; q < kBigRounds; ++q) idx[q] = a.perm[st.start + st.less + min(b + q * kBinThreads, st.equal - 1)];
+        for (int q = 0; q < kBigRounds; ++q) idx[q] = a.perm[start + less + min(b + q * kBinThreads, equal - 1)];
 #pragma unroll
         for (int q = 0; q < kBigRounds; ++q)
-          if (b + q * kBinThreads < st.equal) a.seg_of[idx[q]] = (int32_t)seg;
+          if (b + q * kBinThreads < equal) a.seg_of[idx[q]] = (int32_t)seg;
       }
       x_tail = max(x_tail, (uint32_t)(st.common >> a.bbits) + 1u);
     }
     if (rest > 0) x_tail = max(x_tail, (uint32_t)(m.key[rest - 1] >> a.bbits) + 1u);
   } else {
-    auto key_of = [&](int32_t id) {
-      uint64_t key;
-      int32_t unused;
-      load_item<true>(a.src, (uint32_t)id, key, unused);
-      return key;
-    };
     const uint32_t slice = ((n + kBinWaves - 1) / kBinWaves + 63u) & ~63u;
     const uint32_t wlo = min((uint32_t)wave * slice, n), whi = min(wlo + slice, n);
-    uint32_t seg = base + st.heads_before;
+    uint32_t seg = base + sh.head_cnt[wave];
     for (uint32_t b = wlo; b < whi; b += kBigRounds * 64) {
       uint64_t key[kBigRounds], prev[kBigRounds];
       int32_t idx[kBigRounds];
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
         const uint32_t i = min(b + q * 64 + lane, n - 1);
-        idx[q] = a.perm[st.start + i];
-        key[q] = key_of(idx[q]);
-        prev[q] = key_of(a.perm[st.start + (i == 0 ? 0 : i - 1)]);
+        idx[q] = a.perm[start + i];
+        key[q] = key_of(a.src, idx[q]);
+        prev[q] = key_of(a.src, a.perm[start + (i == 0 ? 0 : i - 1)]);
       }
 #pragma unroll
       for (int q = 0; q < kBigRounds; ++q) {
@@ -1010,13 +1328,167 @@ __device__ __forceinline__ void write_bin(const BinArgs& a, uint32_t bin, uint32
         seg += (uint32_t)__popcll(hmask);
       }
     }
-    x_tail = max(x_tail, (uint32_t)(key_of(a.perm[st.start + n - 1]) >> a.bbits) + 1u);
+    x_tail = max(x_tail, (uint32_t)(key_of(a.src, a.perm[start + n - 1]) >> a.bbits) + 1u);
   }
-  for (uint32_t x = x_tail + tid; x < st.x_hi; x += kBinThreads) a.expert_offsets[x] = (int32_t)(base + st.heads);
-  if (tid == 0 && (DIRECT || bin == kBins - 1)) {
-    a.expert_offsets[a.E] = (int32_t)(base + st.heads);
-    a.seg_offsets[base + st.heads] = (int32_t)a.N;
-    *a.num_segments = (int32_t)(base + st.heads);
+  for (uint32_t x = x_tail + tid; x < x_hi; x += kBinThreads) a.expert_offsets[x] = (int32_t)(base + heads);
+  if (tid == 0 && last) {
+    a.expert_offsets[a.E] = (int32_t)(base + heads);
+    a.seg_offsets[base + heads] = (int32_t)a.N;
+    *a.num_segments = (int32_t)(base + heads);
+  }
+}
+
+// Called by one thread: claims what keeps count number `open` from being published, if nobody has: the bin or part itself,
+// or a part of the bin when that is large.
+template <int MODE>
+__device__ __forceinline__ uint32_t claim_open(const BinArgs& a, const BinShared& sh, uint32_t open) {
+  uint32_t* claim = a.sync + kClaimAt;
+  if (MODE == kCrowded && open < kBins && sh.total[open] > (uint32_t)kBinCap) {
+    const uint32_t first = kBins + sh.first_part[open], parts = parts_of(a, sh.total[open]);
+    for (uint32_t i = first; i < first + parts; ++i)
+      if (atomicCAS(&claim[i * kClaimStride], 0u, 1u) == 0u) return i;
+  }
+  return atomicCAS(&claim[open * kClaimStride], 0u, 1u) == 0u ? open : kNoItem;
+}
+
+// Waits for the counts that the threads with `watch` look at and adds them up: base are the clusters before the item.
+// kNoItem: done; else something was open for long and is claimed now, to be done first (sh.open: the count it keeps back).
+// patient: nothing is taken over.
+template <int MODE>
+__device__ __forceinline__ uint32_t wait_for_counts(const BinArgs& a, BinShared& sh, uint32_t own, bool watch, bool patient,
+                                                    bool& numbered, uint32_t& base) {
+  const uint32_t tid = own_thread();
+  uint32_t v = 0;                                   // one more than the clusters, 0 as long as there is no count
+  for (uint32_t spin = 1;; ++spin) {
+    if (watch && v == 0) v = __hip_atomic_load(&a.sync[kCountAt + tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool open = watch && v == 0;
+    if (!workgroup_any(open, sh.said[spin & 1])) break;
+    if (!seldom(!patient && spin >= a.spins)) continue;
+    spin = 0;
+    if (MODE == kCrowded && !numbered) {
+      __syncthreads();
+      number_parts(a, own, sh);
+      numbered = true;
+    }
+    if (tid == 0) sh.open = kNoItem;
+    __syncthreads();
+    if (open) atomicMin(&sh.open, tid);             // a bin before a part
+    __syncthreads();
+    if (tid == 0) sh.claimed = claim_open<MODE>(a, sh, sh.open);
+    __syncthreads();
+    if (sh.claimed != kNoItem) return scalar(sh.claimed);
+  }
+  bin_exclusive_scan(v == 0 ? 0u : v - 1u, sh.wave_sum[1], base);
+  return kNoItem;
+}
+
+// The turns of a workgroup when some bin may be large.  Its own bin is sorted and counted first; a part that falls to the
+// workgroup comes next, between the sorting and the writing of the own bin: no workgroup waits for anything while it
+// has not published what it has claimed, or has a part still to claim.  What it takes over while it waits needs no takeover
+// itself: that waits for workgroups that run.
+__device__ __forceinline__ void crowded_turns(uint32_t own, BinLds& m, BinShared& sh) {
+  enum : uint32_t {
+    kFirstTurn = 1,
+    kNumbered = 2,      // the parts are numbered
+    kAnnounced = 4,     // the item's count is published
+    kOwnLeft = 8,       // the own bin is still to be written
+    kAside = 16,        // ... and its ids are in perm
+    kRestore = 32,      // ... and need not be sorted again
+    kTakenOver = 64     // the item was open; sh.interrupted waits
+  };
+  uint32_t item = own, bin = own, taken = 0, state = kFirstTurn;
+  for (;;) {
+    auto ap = (const __attribute__((address_space(4))) BinArgs*)__builtin_amdgcn_kernarg_segment_ptr();
+    asm volatile("" : "+s"(ap));
+    const BinArgs& a = *(const BinArgs*)ap;
+    const uint32_t tid = own_thread();
+    bool sorted = true, big = false;
+    uint32_t heads = 0;
+    if (state & kRestore) {
+      state &= ~kRestore;
+      heads = scalar(sh.aside);
+      big = (heads >> 31) != 0;
+      heads &= 0x7fffffffu;
+    } else {
+      bool unused;
+      sorted = sort_item<kCrowded>(a, item, bin, taken, (state & kFirstTurn) != 0, unused, heads, big, m, sh);
+      if (item >= kBins) state |= kNumbered;
+    }
+    const BinState& st = sh.state[item >= kBins ? 1 : 0];
+    taken = 0;
+    if (sorted && !(state & kAnnounced) && tid == 0) {
+      __hip_atomic_store(&a.sync[kCountAt + item], heads + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (item >= kBins) {
+        constexpr uint32_t kOne = 1u << 22;         // parts above, clusters (2^19 at most) below
+        const uint32_t now = atomicAdd(&a.sync[kArriveAt + bin], heads + kOne) + heads + kOne;
+        if (now / kOne == parts_of(a, sh.total[bin]))
+          __hip_atomic_store(&a.sync[kCountAt + bin], now % kOne + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      }
+    }
+    // (a bin that is large and not done in parts leaves its workgroup no time for others)
+    if ((state & (kFirstTurn | kNumbered)) == kFirstTurn && !(sorted && scalar(st.n) > (uint32_t)kBinCap)) {
+      number_parts(a, own, sh);
+      state |= kNumbered;
+      if (sh.my_part != kNoItem) {
+        if (sorted) {
+          state |= kOwnLeft;
+          const uint32_t n = scalar(st.n);
+          if (n <= (uint32_t)kBinThreads) {
+            // its ids go to their place already; it is written like a bin that was sorted through global memory (of so
+            // few keys a wave's first round is its whole slice there)
+            state |= kAside;
+            if (tid < n) a.perm[scalar(st.start) + tid] = m.idx[tid];
+            if (tid < (uint32_t)kBinWaves) sh.aside_heads[tid] = sh.head_cnt[tid];
+            big = n != 0;
+          }
+          if (tid == 0) sh.aside = heads | (big ? 0x80000000u : 0u);
+        }
+        item = scalar(sh.my_part);
+        bin = scalar(sh.my_bin);
+        state &= ~(kFirstTurn | kAnnounced);
+        taken = tid == 0 ? atomicExch(&a.sync[kClaimAt + item * kClaimStride], 1u) : 0u;
+        continue;
+      }
+    }
+    state &= ~kFirstTurn;
+    if (sorted) {
+      const uint32_t n = scalar(st.n), start = scalar(st.start), equal = scalar(st.equal);
+      // the counts of the bins before, and of the parts of the same bin before
+      const bool watch = tid < bin || (item >= kBins && tid < item && tid >= kBins + sh.first_part[bin]);
+      bool numbered = (state & kNumbered) != 0;
+      uint32_t base;
+      const uint32_t other = wait_for_counts<kCrowded>(a, sh, own, watch, (state & kTakenOver) != 0, numbered, base);
+      if (numbered) state |= kNumbered;
+      if (other != kNoItem) {
+        if (tid == 0) {
+          sh.interrupted = item;
+          sh.interrupted_bin = bin;
+        }
+        item = other;
+        if (scalar(sh.open) < kBins) bin = scalar(sh.open);
+        state = (state & ~kAnnounced) | kTakenOver;
+        __syncthreads();
+        continue;
+      }
+      write_item<kCrowded>(a, item, bin, n, start, heads, equal, big, base, m, sh, st);
+    }
+    if (state & kTakenOver) {
+      item = scalar(sh.interrupted);
+      bin = scalar(sh.interrupted_bin);
+      state &= ~kTakenOver;
+    } else if (state & kOwnLeft) {                  // after the part
+      item = bin = own;
+      if (state & kAside) {
+        __syncthreads();
+        if (tid < (uint32_t)kBinWaves) sh.head_cnt[tid] = sh.aside_heads[tid];
+      }
+      if (!sorted || (state & kAside)) state |= kRestore;
+      state &= ~(kOwnLeft | kAside);
+    } else {
+      return;
+    }
+    state |= kAnnounced;
+    __syncthreads();
   }
 }
 
@@ -1027,57 +1499,50 @@ __global__ __launch_bounds__(kBinThreads) void bin_group_kernel(BinArgs args) {
   __shared__ BinShared sh;
   const uint32_t tid = threadIdx.x;
   for (uint32_t i = blockIdx.x * kBinThreads + tid; i < args.n_counters; i += gridDim.x * kBinThreads) args.window_counters[i] = 0;
+  bool crowded = false, big = false;
+  uint32_t heads = 0;
   if (DIRECT) {
-    BinState st;
-    sort_bin<true>(args, 0, 0, m, sh, st);
-    write_bin<true>(args, 0, 0, m, sh, st);
+    uint32_t item = 0;
+    sort_item<kDirect>(args, item, 0, 0, true, crowded, heads, big, m, sh);
+    write_item<kDirect>(args, 0, 0, args.N, 0, heads, 0, false, 0, m, sh, sh.state[0]);
     return;
   }
   // consecutive workgroups sit on different XCDs; neighbouring bins, whose keys and table entries share cache lines,
   // go to the same one
   const uint32_t own = (blockIdx.x % kXcds) * (kBins / kXcds) + blockIdx.x / kXcds;
   if (own < args.first_bin) return;                 // never with first_bin = 0
-  uint32_t taken = tid == 0 ? atomicExch(&args.sync[kBins + own * kClaimStride], 1u) : 0u;
+  uint32_t taken = tid == 0 ? atomicExch(&args.sync[kClaimAt + own * kClaimStride], 1u) : 0u;
   // One turn, unless a bin is taken over: that bin then, and after it the own one again (it was in LDS).  The
   // arguments are read through a pointer that the compiler must take for a new one in every turn; otherwise it keeps
   // all of them in scalar registers across the loop, and has to spill those.
+  bool first_turn = true;
   for (uint32_t bin = own;;) {
     auto ap = (const __attribute__((address_space(4))) BinArgs*)__builtin_amdgcn_kernarg_segment_ptr();
     asm volatile("" : "+s"(ap));
     const BinArgs& a = *(const BinArgs*)ap;
-    BinState st;
-    if (!sort_bin<false>(a, bin, taken, m, sh, st)) return;
+    const uint32_t tid = own_thread();
+    uint32_t item = bin;
+    const bool sorted = sort_item<kBalanced>(a, item, bin, taken, first_turn, crowded, heads, big, m, sh);
+    if (seldom(crowded)) break;                     // (on the first turn)
+    if (seldom(!sorted)) return;                    // (on the first turn) the bin is done by a workgroup that waited for it
     taken = 0;
-    if (tid == 0) __hip_atomic_store(&a.sync[bin], st.heads + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // clusters before this bin: every published count is one more than the bin's clusters, 0 as long as there is none
-    uint32_t v = 0;
-    bool take_over = false;
-    for (uint32_t spin = 1;; ++spin) {
-      if (tid < bin && v == 0) v = __hip_atomic_load(&a.sync[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      const bool open = tid < bin && v == 0;
-      if (!__syncthreads_or(open)) break;
-      if (spin < a.spins) continue;
-      spin = 0;
-      if (tid == 0) sh.open_bin = kBins;
-      __syncthreads();
-      if (open) atomicMin(&sh.open_bin, tid);
-      __syncthreads();
-      if (tid == 0) sh.claimed = atomicCAS(&a.sync[kBins + sh.open_bin * kClaimStride], 0u, 1u) == 0u;
-      __syncthreads();
-      if ((take_over = sh.claimed)) break;
-    }
-    if (take_over) {
-      bin = sh.open_bin;
+    first_turn = false;
+    if (tid == 0) __hip_atomic_store(&a.sync[kCountAt + bin], heads + 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint32_t n = scalar(sh.state[0].n), start = scalar(sh.state[0].start);
+    bool numbered = false;
+    uint32_t base;
+    const uint32_t other = wait_for_counts<kBalanced>(a, sh, own, tid < bin, false, numbered, base);
+    if (seldom(other != kNoItem)) {
+      bin = other;
       __syncthreads();
       continue;
     }
-    uint32_t base;
-    bin_exclusive_scan(v == 0 ? 0u : v - 1u, sh.wave_sum[1], base);
-    write_bin<false>(a, bin, base, m, sh, st);
+    write_item<kBalanced>(a, bin, bin, n, start, heads, 0, false, base, m, sh, sh.state[0]);
     if (bin == own) return;
     bin = own;
     __syncthreads();
   }
+  crowded_turns(own, m, sh);
 }
 
 int bits_for(uint64_t max_value) {  // number of bits needed to hold max_value
@@ -1171,11 +1636,16 @@ bool plan_group(int64_t T, int d, int k, int E, int L, int r, GroupPlan* plan) {
     }
   }
   if (p.bins) {
-    // The second key buffer is free.  The table (at most 4 N bytes + 1 KB) and behind it the bins' published counts and
-    // claims lie there: the sizes that the built-in scratch holds do not shrink for the sake of this route.
+    // The second key buffer is free.  The table (at most 4 N bytes + 1 KB) and behind it the largest counts per tile (16
+    // bytes per 256 keys) and the words of the bins and parts lie there: the sizes that the built-in scratch holds do not shrink for
+    // the sake of this route.
+    p.part_keys = max(kPartKeys, (uint32_t)(p.N / kBins));    // no more parts than workgroups
+    p.parts = (uint32_t)(p.N / p.part_keys);
     p.off_table = p.off_key[1];
-    p.off_blocksum = align256(p.off_table + (size_t)kBins * p.tiles * 4);
-    static_assert(4 * (size_t)kSmallMaxN >= 1024 + kSyncWords * 4, "room behind the table at every size of this route");
+    p.off_peak = align256(p.off_table + (size_t)kBins * p.tiles * 4);
+    p.off_blocksum = align256(p.off_peak + (size_t)p.tiles * kPeaks * 4);
+    static_assert((4 - 1.0 / 16 - 1.0 / 32) * kSmallMaxN >= 1024 + 16 + 3 * 256 + sync_words(0) * 4,
+                  "room behind the table at every size of this route");
   } else if (!p.one_bin) {
     p.off_table = off;
     off = align256(off + (size_t)kGroupBins * p.tiles * 4);
@@ -1207,6 +1677,8 @@ hipError_t launch_group(const GroupPlan& plan, const int32_t* expert, const uint
     BinArgs a{};
     a.src = src;
     a.table = table;
+    a.part_keys = plan.part_keys;
+    a.peak = (const uint4*)(ws + plan.off_peak);
     a.tile_key = keybuf[0];
     a.tile_idx = idxbuf[0];
     a.tiles = plan.tiles;
@@ -1232,7 +1704,8 @@ hipError_t launch_group(const GroupPlan& plan, const int32_t* expert, const uint
     if (plan.one_bin) return launch_bins<true>(a, stream);
     const dim3 grid(plan.tiles), block(kSortThreads);
 #define LSHMOE_TILES(TILE) \
-    LSHMOE_LAUNCH((tile_bin_kernel<TILE>), grid, block, 0, stream, src, N, plan.top_shift, table, keybuf[0], idxbuf[0], a.sync)
+    LSHMOE_LAUNCH((tile_bin_kernel<TILE>), grid, block, 0, stream, src, N, plan.top_shift, table, keybuf[0], idxbuf[0], a.sync, \
+                  plan.parts, (uint32_t*)a.peak)
     if (plan.tile == 256) LSHMOE_TILES(256);
     else if (plan.tile == 512) LSHMOE_TILES(512);
     else if (plan.tile == 1024) LSHMOE_TILES(1024);

@@ -42,10 +42,11 @@ struct GroupPlan {
   int shift[8], width[8];  // digit of pass p is (key >> shift[p]) & ((1 << width[p]) - 1)
   int tile;              // assignments per sort tile
   uint32_t tiles;        // sort tiles
+  uint32_t parts, part_keys;   // bins: the most parts that large bins are cut into, keys per part
   uint32_t first_bin, spins;   // bins: see BinArgs (a test forces the takeover of bins with them)
   uint32_t seg_blocks;   // tiles of kSegTile sorted positions
   // byte offsets into the workspace
-  size_t off_key[2], off_idx[2], off_table, off_blocksum;
+  size_t off_key[2], off_idx[2], off_table, off_blocksum, off_peak;
   size_t off_partial, off_counters;  // window sums and window counters of the centroid step
   size_t total_bytes;
 };

@@ -91,3 +91,107 @@ def test_bins_whose_workgroups_do_not_run_are_taken_over(first_bin, skew):
     a, b = outs
     for name in ("num_segments", "seg_offsets", "seg_expert", "expert_offsets", "perm", "seg_of", "centroids"):
         assert torch.equal(getattr(a, name), getattr(b, name)), name
+
+
+def _skewed(name, rng):
+    """Keys of which most share a few bins: (experts [N], ids [N], E, L, r)."""
+    E, L, r, N = 4, 6, 16, 40000                        # 2 expert bits, 30 bucket bits: a bin is 6 bucket bits
+    ids = rng.integers(0, 1 << 30, N, dtype=np.uint64)
+    expert = np.full(N, 2)
+    base = np.uint64(37 << 24)
+    narrow = base | rng.integers(0, 1 << 24, N, dtype=np.uint64)
+    if name == "one bin":
+        ids = narrow
+    elif name == "one bin, few keys":                   # clusters that steps of the sample fall into
+        ids = base | (rng.integers(0, 9, N, dtype=np.uint64) * np.uint64(999))
+    elif name == "last bin":
+        expert, ids = np.full(N, 3), ids | np.uint64(63 << 24)
+    elif name == "first and last key":
+        expert = np.where(rng.random(N) < 0.5, 0, 3)
+        ids = np.where(expert == 0, np.uint64(0), np.uint64((1 << 30) - 1))
+        some = rng.random(N) < 0.3
+        ids = np.where(some & (expert == 0), ids + rng.integers(0, 1 << 20, N, dtype=np.uint64), ids)
+        ids = np.where(some & (expert == 3), ids - rng.integers(0, 1 << 20, N, dtype=np.uint64), ids)
+    elif name == "two frequent keys":
+        u = rng.random(N)
+        ids = np.where(u < 0.4, base | np.uint64(5), np.where(u < 0.7, base | np.uint64(1 << 23), narrow))
+    elif name == "a frequent key among many":           # below the share that makes the bin one workgroup's
+        ids = np.where(rng.random(N) < 0.6, base | np.uint64(1 << 22), narrow)
+    elif name == "several experts per bin":             # 9 expert bits: two experts share a bin
+        E = 300
+        expert = np.where(rng.random(N) < 0.8, rng.integers(100, 104, N), rng.integers(0, E, N))
+        ids = rng.integers(0, 1 << 30, N, dtype=np.uint64)
+    elif name == "every bin large":
+        N = 524288
+        expert, ids = rng.integers(0, 4, N), rng.integers(0, 1 << 30, N, dtype=np.uint64) & np.uint64(0x30ffffff)
+    elif name == "the sample misses":                   # every 16th key of the bin is spread out, the rest is narrow
+        N = 16384
+        expert = np.full(N, 2)
+        ids = base | np.uint64(1 << 22) | rng.permutation(N).astype(np.uint64)
+        ids[8::16] = base | (np.arange(N // 16, dtype=np.uint64) * np.uint64(16000))
+    elif name == "the sample misses, frequent":         # ... and mostly two keys, none of them at a step
+        N = 16384
+        expert = np.full(N, 2)
+        ids = base | np.uint64(1 << 22) | np.where(rng.random(N) < 0.5, np.uint64(77), np.uint64(99))
+        ids[8::16] = base | (np.arange(N // 16, dtype=np.uint64) * np.uint64(16000))
+    elif name == "the sample shows one key":            # ... that is one in sixteen of the bin
+        N = 16384
+        expert = np.full(N, 2)
+        ids = base | np.uint64(1 << 22) | rng.permutation(N).astype(np.uint64)
+        ids[8::16] = base | np.uint64(5 << 20)
+    elif name == "eight key bits":
+        E, L, r = 2, 1, 64                              # the bin is the key
+        expert, ids = np.where(rng.random(N) < 0.7, 1, 0), np.where(rng.random(N) < 0.5, 127, rng.integers(0, 128, N)).astype(np.uint64)
+    return expert, ids.astype(np.uint64), E, L, r
+
+
+@pytest.mark.parametrize("name", ["one bin", "one bin, few keys", "last bin", "first and last key", "two frequent keys",
+                                  "a frequent key among many", "several experts per bin", "every bin large",
+                                  "the sample misses", "the sample misses, frequent", "the sample shows one key",
+                                  "eight key bits"])
+def test_large_bins_in_parts(H, name):
+    rng = np.random.default_rng(len(name))
+    expert, ids, E, L, r = _skewed(name, rng)
+    d, dtype, N = 8, "bf16", expert.size
+    tokens = synth.f32_to_storage(rng.standard_normal((N, d)).astype(np.float32), dtype)
+    print("case large bins:", name, flush=True)
+    H.run_and_check(tokens, np.zeros((L, r, d), tokens.dtype), expert.astype(np.int32).reshape(N, 1), E, dtype, lambda c: c,
+                    bucket_override=ids, skip_hash=True)
+
+
+def _compare_with_takeover(expert, ids, E, L, r, first_bin):
+    """Every output of a call whose first workgroups leave at once equals that of the ordinary call."""
+    lib = lsh.load_library()
+    N, d = expert.size, 8
+    x = torch.randn(N, d, device="cuda")
+    et = torch.from_numpy(expert.astype(np.int32).reshape(N, 1)).cuda()
+    bt = torch.from_numpy(ids.view(np.int64)).cuda()
+    a, b = (lsh.CompressOutputs.allocate(N, d, 1, E, L, r, torch.float32) for _ in range(2))
+    names = ("num_segments", "seg_offsets", "seg_expert", "expert_offsets", "perm", "seg_of", "centroids")
+    for o in (a, b):
+        for n in names:
+            getattr(o, n).fill_(-7)
+        o.workspace.fill_(0xA5)
+    lsh.lshmoe_compress(x, et, bt, E, L, r, a)
+    ws, ws_bytes = binding._aligned_ws(b.workspace)
+    p = lambda t: ctypes.c_void_p(t.data_ptr())
+    status = lib.lshmoe_test_compress_takeover(
+        p(x), p(et), p(bt), ctypes.c_int64(N), d, 1, E, L, r, lsh.LSHMOE_F32, p(b.centroids), p(b.seg_offsets),
+        p(b.seg_expert), p(b.expert_offsets), p(b.perm), p(b.seg_of), p(b.num_segments), ctypes.c_void_p(ws),
+        ctypes.c_size_t(ws_bytes), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream),
+        ctypes.c_uint32(first_bin), ctypes.c_uint32(2))
+    assert status == lsh.LSHMOE_OK
+    torch.cuda.synchronize()
+    for n in names:
+        assert torch.equal(getattr(a, n), getattr(b, n)), n
+
+
+@pytest.mark.parametrize("first_bin", [1, 37, 200])
+@pytest.mark.parametrize("name", ["one bin", "two frequent keys", "the sample misses"])
+def test_parts_whose_workgroups_do_not_run_are_taken_over(name, first_bin):
+    # bin 165 is large, its parts belong to the workgroups of the first bins: those that run claim them while they wait
+    rng = np.random.default_rng(first_bin)
+    expert, ids, E, L, r = _skewed(name, rng)
+    expert[-500:] = 3                                   # work behind the large bin, too
+    print("case parts taken over:", name, first_bin, flush=True)
+    _compare_with_takeover(expert, ids, E, L, r, first_bin)
