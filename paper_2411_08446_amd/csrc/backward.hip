@@ -54,15 +54,19 @@ __global__ __launch_bounds__(256) void grad_tokens_kernel(
         for (int i = 0; i < E; ++i) acc[i] += h[i];
       } else if (no_res) {
         const float fn = (float)n, inv = 1.0f / fn;
+        div_count<DT>(h, fn, inv);
 #pragma unroll
-        for (int i = 0; i < E; ++i) acc[i] += div_count<DT>(h[i], fn, inv);
+        for (int i = 0; i < E; ++i) acc[i] += h[i];
       } else {
         float g[E], gs[E];
         Piece<DT>::widen((STREAM ? load16_stream : load16)(grad_out + (size_t)a * row_bytes + c * 16), g);
         Piece<DT>::widen(load16(grad_expert_out + (size_t)s * row_bytes + c * 16), gs);
         const float fn = (float)n, inv = 1.0f / fn;
 #pragma unroll
-        for (int i = 0; i < E; ++i) acc[i] += g[i] + div_count<DT>(h[i] - gs[i], fn, inv);
+        for (int i = 0; i < E; ++i) h[i] -= gs[i];
+        div_count<DT>(h, fn, inv);
+#pragma unroll
+        for (int i = 0; i < E; ++i) acc[i] += g[i] + h[i];
       }
     }
     store16_stream(grad_tokens + (size_t)t * row_bytes + c * 16, Piece<DT>::narrow(acc));

@@ -189,10 +189,7 @@ __device__ __forceinline__ void long_cluster_window(
     }
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] += err[i];
-    if (mean) {
-#pragma unroll
-      for (int i = 0; i < E; ++i) acc[i] = div_count<DT>(acc[i], fn, inv);
-    }
+    if (mean) div_count<DT>(acc, fn, inv);
     store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
   }
 }
@@ -205,7 +202,8 @@ __device__ __forceinline__ void long_cluster_window(
 // which workgroup came last.  Every join is by two-sums, and the first takes the waves' compensations with it (in LDS, in
 // the columns of the other half): with plain sums the error was a third larger than that of four waves that share the
 // whole cluster (rms against binary64, Gaussian rows, 600 / 1024 members: 2.41 / 1.66e-9 for four waves, 3.00 / 2.21e-9
-// with plain joins, 2.28 / 1.57e-9 so).
+// with plain joins, 2.28 / 1.57e-9 so; without the compensations 2.54 / 1.76e-9, far below the rounding of bfloat16 rows,
+// which do without them).
 // Called by all four waves of the workgroup with the same arguments (barriers inside).
 //
 // W: a wave is bound by memory latency, about 1.8 us per round of eight rows and 64 pieces, and the partial rows are read
@@ -226,6 +224,7 @@ __device__ __forceinline__ void long_cluster_wg_window(
     char* __restrict__ centroids, float* partial, uint32_t* counters, float* coop_sum, int32_t s, uint32_t block_p0,
     uint32_t W, int32_t a, int32_t b, uint32_t slot, uint32_t half, uint32_t k, uint32_t cpr, uint32_t d, uint32_t mean) {
   constexpr int E = Piece<DT>::kElems;
+  constexpr bool kComp = std::is_same<DT, F32>::value;   // the compensations are taken along
   const size_t row_bytes = (size_t)cpr * 16;
   const uint32_t lane = threadIdx.x & 63;
   const uint32_t w4 = (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -243,11 +242,14 @@ __device__ __forceinline__ void long_cluster_wg_window(
 #pragma unroll
       for (int i = 0; i < E; i += 4) {
         *(float4*)(mine + c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
-        *(float4*)(mine + (c * E + to_comp) + i) = make_float4(comp[i], comp[i + 1], comp[i + 2], comp[i + 3]);
+        if (kComp) *(float4*)(mine + (c * E + to_comp) + i) = make_float4(comp[i], comp[i + 1], comp[i + 2], comp[i + 3]);
       }
     });
   } else {
-    for (uint32_t i = c_lo * E + lane; i < c_hi * E; i += 64) mine[i] = mine[i + to_comp] = 0.0f;
+    for (uint32_t i = c_lo * E + lane; i < c_hi * E; i += 64) {
+      mine[i] = 0.0f;
+      if (kComp) mine[i + to_comp] = 0.0f;
+    }
   }
   const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[s]);
   const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[s + 1]);
@@ -262,11 +264,13 @@ __device__ __forceinline__ void long_cluster_wg_window(
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
         const float4 u = *(const float4*)(coop_sum + w * stride + i);
-        const float4 q = *(const float4*)(coop_sum + w * stride + (i + to_comp));
         if (w > 0) {
           two_sum(v.x, u.x, e.x); two_sum(v.y, u.y, e.y); two_sum(v.z, u.z, e.z); two_sum(v.w, u.w, e.w);
         }
-        e.x -= q.x; e.y -= q.y; e.z -= q.z; e.w -= q.w;
+        if (kComp) {
+          const float4 q = *(const float4*)(coop_sum + w * stride + (i + to_comp));
+          e.x -= q.x; e.y -= q.y; e.z -= q.z; e.w -= q.w;
+        }
       }
       *(float4*)(out_row + i) = make_float4(v.x + e.x, v.y + e.y, v.z + e.z, v.w + e.w);
     }
@@ -321,8 +325,8 @@ __device__ __forceinline__ void long_cluster_wg_window(
 #pragma unroll
       for (int w = 1; w < 4; ++w) two_sum(acc[i], coop_sum[w * stride + c * E + i], err);
       acc[i] += err;
-      if (mean) acc[i] = div_count<DT>(acc[i], fn, inv);
     }
+    if (mean) div_count<DT>(acc, fn, inv);
     store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
   }
   __syncthreads();  // before the LDS rows are used again
@@ -393,8 +397,8 @@ __global__ __launch_bounds__(256) void centroid_kernel(
           acc[i] = coop_sum[(size_t)c * E + i];
 #pragma unroll
           for (int w = 1; w < 4; ++w) acc[i] += coop_sum[((size_t)w * cpr + c) * E + i];
-          if (mean) acc[i] = div_count<DT>(acc[i], fn, inv);
         }
+        if (mean) div_count<DT>(acc, fn, inv);
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       }
       __syncthreads();  // before the partial sums are overwritten
@@ -410,10 +414,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
       char* dst = centroids + (size_t)s * row_bytes;
       const float fn = (float)n, inv = 1.0f / fn;
       row_sum_kahan<DT>(tokens, perm, lo, hi, k, 0, cpr, row_bytes, [&](uint32_t c, float (&acc)[E], const float (&)[E]) {
-        if (mean) {
-#pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] = div_count<DT>(acc[i], fn, inv);
-        }
+        if (mean) div_count<DT>(acc, fn, inv);
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       });
     } else if (n <= kWindowMin) {
@@ -474,8 +475,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
         }
         if (mean) {
           const float fn = (float)n, inv = 1.0f / fn;
-#pragma unroll
-          for (int i = 0; i < E; ++i) acc[i] = div_count<DT>(acc[i], fn, inv);
+          div_count<DT>(acc, fn, inv);
         }
         store16_stream(dst + c * 16, Piece<DT>::narrow(acc));
       }
