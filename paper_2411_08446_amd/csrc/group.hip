@@ -889,22 +889,25 @@ __device__ __forceinline__ bool sort_item(const BinArgs& a, uint32_t& item, uint
           for (int q = 0; q < kBigRounds; ++q) f(b + q * 64 + lane < hhi, k[q], id[q]);
         }
       };
-      // keys before the part, of it, of the common key, of the part before that; the part's go to the wave's places in LDS
-      // as long as there are any left
+      // Keys before the part, of it, of the common key, of the part before that.  What is to be sorted goes to the wave's
+      // places in LDS as long as there are any left; the ids of a bin's common key, if the bin is not too large, go to
+      // those of the wave's slice where the counters of the sort will be.
       uint32_t below = 0, in = 0, eq = 0, lt = 0;
+      constexpr uint32_t kWaveIds = sizeof(m.cnt) / sizeof(int32_t) / kBinWaves;
+      const bool ids_kept = !part && n <= kWaveIds * kBinWaves;
+      int32_t* wave_ids = reinterpret_cast<int32_t*>(&m.cnt[0][0]) + wave * kWaveIds;
       walk([&](bool valid, uint64_t k, int32_t id) {
         const bool low = has_lo && k < range_lo, inside = valid && !low && !(has_hi && k >= range_hi);
-        const uint64_t r = __ballot(inside);
-        if (part) {
-          const uint32_t at = in + (uint32_t)__popcll(r & lt_mask);
-          if (inside && at < kWaveSlot) {
-            m.key[wave * kWaveSlot + at] = k;
-            m.idx[wave * kWaveSlot + at] = id;
-          }
+        const uint64_t r = __ballot(inside), e = __ballot(inside && k == common), sort = part ? r : r & ~e;
+        const uint32_t at = (part ? in : in - eq) + (uint32_t)__popcll(sort & lt_mask);
+        if ((sort >> lane & 1ull) != 0 && at < kWaveSlot) {
+          m.key[wave * kWaveSlot + at] = k;
+          m.idx[wave * kWaveSlot + at] = id;
         }
+        if (ids_kept && inside && k == common) wave_ids[eq + (uint32_t)__popcll(e & lt_mask)] = id;
         below += (uint32_t)__popcll(__ballot(valid && low));
         in += (uint32_t)__popcll(r);
-        eq += (uint32_t)__popcll(__ballot(inside && k == common));
+        eq += (uint32_t)__popcll(e);
         lt += (uint32_t)__popcll(__ballot(inside && k < common));
       });
       if (lane == 0) sh.wave_four[wave] = make_uint4(in, eq, lt, below);
@@ -921,7 +924,7 @@ __device__ __forceinline__ bool sort_item(const BinArgs& a, uint32_t& item, uint
         eq_all += c.y;
         lt_all += c.z;
         below_all += c.w;
-        in_most = max(in_most, c.x);
+        in_most = max(in_most, part ? c.x : c.x - c.y);
       }
       in_all = scalar(in_all);
       eq_all = scalar(eq_all);
@@ -938,7 +941,7 @@ __device__ __forceinline__ bool sort_item(const BinArgs& a, uint32_t& item, uint
           big = true;
         }
       }
-      if (part && scalar(in_most) <= kWaveSlot) {   // all of them are there: closed up
+      if ((part || ids_kept) && !big && scalar(in_most) <= kWaveSlot) {   // all of them are there: closed up
         static_assert(kWaveSlot == kBinItems * 64, "a wave's places in its registers");
         uint64_t k[kBinItems];
         int32_t id[kBinItems];
@@ -947,10 +950,13 @@ __device__ __forceinline__ bool sort_item(const BinArgs& a, uint32_t& item, uint
           k[q] = m.key[wave * kWaveSlot + q * 64 + lane];
           id[q] = m.idx[wave * kWaveSlot + q * 64 + lane];
         }
+        if (!part)
+          for (uint32_t i = lane; i < eq; i += 64) a.perm[start + less + eq_at + i] = wave_ids[i];
         __syncthreads();
+        const uint32_t here = part ? in : in - eq;
 #pragma unroll
         for (int q = 0; q < kBinItems; ++q) {
-          if (q * 64 + (uint32_t)lane < in) {
+          if (q * 64 + (uint32_t)lane < here) {
             m.key[rest_at + q * 64 + lane] = k[q];
             m.idx[rest_at + q * 64 + lane] = id[q];
           }
