@@ -517,7 +517,7 @@ struct BinArgs {               // what is needed first comes first: the fields a
   int32_t *seg_offsets, *seg_expert, *expert_offsets, *perm, *seg_of, *num_segments;
   uint32_t* window_counters;  // cleared here for the centroid step
   uint32_t n_counters;
-  uint32_t first_bin;         // the workgroups of the bins before it leave at once (0; a test forces the takeover of bins with it)
+  uint32_t first_bin;         // SKIP: see bin_group_kernel
   int shift[8], width[8];
   uint32_t part_keys;         // keys of a part, on average
   int32_t* big_idx;           // the ids of a part that is sorted through global memory go between here and perm
@@ -1498,7 +1498,8 @@ __device__ __forceinline__ void crowded_turns(uint32_t own, BinLds& m, BinShared
   }
 }
 
-template <bool DIRECT>
+// SKIP: the workgroups of the bins before first_bin leave at once, for a test of the takeover.
+template <bool DIRECT, bool SKIP = false>
 __global__ __launch_bounds__(kBinThreads) void bin_group_kernel(BinArgs args) {
   extern __shared__ uint64_t bin_lds[];
   BinLds& m = *reinterpret_cast<BinLds*>(bin_lds);
@@ -1516,7 +1517,7 @@ __global__ __launch_bounds__(kBinThreads) void bin_group_kernel(BinArgs args) {
   // consecutive workgroups sit on different XCDs; neighbouring bins, whose keys and table entries share cache lines,
   // go to the same one
   const uint32_t own = (blockIdx.x % kXcds) * (kBins / kXcds) + blockIdx.x / kXcds;
-  if (own < args.first_bin) return;                 // never with first_bin = 0
+  if (SKIP && own < args.first_bin) return;
   uint32_t taken = tid == 0 ? atomicExch(&args.sync[kClaimAt + own * kClaimStride], 1u) : 0u;
   // One turn, unless a bin is taken over: that bin then, and after it the own one again (it was in LDS).  The
   // arguments are read through a pointer that the compiler must take for a new one in every turn; otherwise it keeps
@@ -1588,9 +1589,9 @@ hipError_t launch_scatter(const KeySource& src, uint32_t N, int shift, uint32_t 
   return hipSuccess;
 }
 
-template <bool DIRECT>
+template <bool DIRECT, bool SKIP = false>
 hipError_t launch_bins(const BinArgs& a, hipStream_t stream) {
-  auto kern = bin_group_kernel<DIRECT>;
+  auto kern = bin_group_kernel<DIRECT, SKIP>;
   static std::atomic<bool> raised{false};
   if (hipError_t e = raise_lds(kern, sizeof(BinLds), raised); e != hipSuccess) return e;
   LSHMOE_LAUNCH(kern, dim3(DIRECT ? 1 : kBins), dim3(kBinThreads), sizeof(BinLds), stream, a);
@@ -1717,7 +1718,7 @@ hipError_t launch_group(const GroupPlan& plan, const int32_t* expert, const uint
     else if (plan.tile == 1024) LSHMOE_TILES(1024);
     else LSHMOE_TILES(2048);
 #undef LSHMOE_TILES
-    return launch_bins<false>(a, stream);
+    return plan.first_bin == 0 ? launch_bins<false>(a, stream) : launch_bins<false, true>(a, stream);
   }
 
   const uint64_t* sorted_key = nullptr;

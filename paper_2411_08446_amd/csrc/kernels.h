@@ -43,7 +43,7 @@ struct GroupPlan {
   int tile;              // assignments per sort tile
   uint32_t tiles;        // sort tiles
   uint32_t parts, part_keys;   // bins: the most parts that large bins are cut into, keys per part
-  uint32_t first_bin, spins;   // bins: see BinArgs (a test forces the takeover of bins with them)
+  uint32_t first_bin, spins;   // bins: see BinArgs; first_bin is 0 but for a test of the takeover
   uint32_t seg_blocks;   // tiles of kSegTile sorted positions
   // byte offsets into the workspace
   size_t off_key[2], off_idx[2], off_table, off_blocksum, off_peak;
