@@ -331,7 +331,7 @@ __global__ __launch_bounds__(GROUPS * HALVES * 64, 1) void hash_stream_kernel(
   __builtin_assume(tid >= 0 && tid < TH);
   const int lane = tid & 63, wave = tid >> 6;
   const int n = lane & 31, h = lane >> 5;
-  const int g = wave / HALVES, mh = wave % HALVES;   // token group, half of the rows
+  const int g = wave / HALVES, mh = wave % HALVES;   // token group, which of the waves that share its rows of R
   const uint32_t row_bytes = (uint32_t)row_pieces * 16u;
   const int nchunks = KTAIL ? (row_pieces + kPieces - 1) / kPieces : row_pieces / kPieces;
   const int last_pieces = KTAIL ? row_pieces - (nchunks - 1) * kPieces : kPieces;   // pieces of the last chunk, 1..8

@@ -136,14 +136,13 @@ def test_group_routes_by_key_width_and_size(H, N, E, L, r):
     (4100, 1, 3), (6149, 1, 4000), (10240, 1, 7), (34817, 1, 20000), (65536, 1, 1), (131072, 1, 90000),
     (524288, 1, 300000), (524288, 1, 2), (70001, 3, 50000), (200003, 5, 11), (300000, 2, 150000), (40000, 7, 64)])
 def test_group_bins_of_many_chunks(H, N, bins_used, distinct):
-    # Bins of the one global pass that hold 2 .. 256 chunks of 2048 keys (all keys share the top key bits of a few
-    # bins): the chunks are merged pairwise by the workgroups that sorted them, level by level; odd chunk counts,
-    # a ragged last chunk, runs without a neighbour, many equal keys and all-distinct keys.
-    d, dtype, E, L, r = 8, "bf16", 4, 4, 16                     # 2 expert bits + 20 bucket bits: top 9 bits pick the bin
+    # All keys share the top key bits of a few bins, which hold 4100 to 524288 keys each and are cut into parts for
+    # several workgroups: many equal keys (frequent ones that begin a part, or make up the bin) and all-distinct keys.
+    d, dtype, E, L, r = 8, "bf16", 4, 4, 16                     # 2 expert bits + 20 bucket bits: top 8 bits pick the bin
     rng = np.random.default_rng(N + 7 * bins_used + distinct)
     tokens = synth.f32_to_storage(rng.standard_normal((N, d)).astype(np.float32), dtype)
     rot = synth.f32_to_storage(rng.standard_normal((L, r, d)).astype(np.float32), dtype)
-    low_bits = 20 - 7                                            # key bits below the bin digit
+    low_bits = 20 - 7                                            # 9 top bits: two neighbouring values share a bin
     tops = rng.choice(4 << 7, bins_used, replace=False)          # (expert, top 7 bucket bits) of the bins used
     pool_top = tops[rng.integers(0, bins_used, distinct)]
     pool_low = rng.integers(0, 1 << low_bits, distinct, dtype=np.uint64)
@@ -156,9 +155,9 @@ def test_group_bins_of_many_chunks(H, N, bins_used, distinct):
 
 
 def test_chunk_merges_give_the_same_result_every_time(H):
-    # The merges inside the bin-sort launch depend on which of two neighbouring workgroups finishes last; the result
-    # must not.  One bin of 64 chunks and three bins of a dozen, forty calls on the same buffers (workspace included),
-    # every output compared with the first call's (which the parity cases above compare with the oracle).
+    # Which workgroup publishes a large bin's count depends on which of its parts is counted last; the result must not.
+    # One bin of 128 parts and three bins of about 40, forty calls on the same buffers (workspace included), every
+    # output compared with the first call's (which the parity cases above compare with the oracle).
     lsh = H.lsh
     E, L, r, d, N = 4, 4, 16, 8, 131072
     rng = np.random.default_rng(99)
@@ -214,7 +213,7 @@ def test_long_clusters_are_summed_in_windows(H, dtype, d, k):
     # cluster sizes around the window length of the centroid step (128 sorted positions) and far beyond it, with
     # heads on and off the window grid; d = 1032 makes rows wider than one pass of a wave over the row; with
     # d = 4096 the four partial rows of a workgroup-shared sum no longer fit the LDS set aside for them, so
-    # clusters of 33..1024 members stay with one wave
+    # clusters of 33..256 members stay with one wave and longer ones go by blocks of one wave each
     sizes = [128, 129, 1, 127, 256, 257, 3, 1000, 2, 5000, 131, 1, 1, 384, 640, 7, 2049]
     T, E, L, r = sum(sizes), 3, 2, 16
     tokens, rot, _ = _rand_inputs(21, T, d, 1, E, L, r, dtype)
@@ -253,7 +252,7 @@ def test_long_clusters_of_both_block_sizes(H, dtype, sizes, d):
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_one_huge_cluster_many_windows(H, dtype):
-    # 20000 identical tokens on the multi-launch grouping route: 157 window sums are combined by the last wave
+    # 20000 identical tokens, one bin of one key: 157 block sums are combined by the last wave
     T, d, E = 20000, 64, 2
     tokens, rot, _ = _rand_inputs(23, 1, d, 1, E, 2, 16, dtype)
     tokens = np.repeat(tokens, T, axis=0)
@@ -332,9 +331,9 @@ def test_hash_streaming_instances(H, dtype, T, L, r):
 @pytest.mark.parametrize("L,r", [(1, 32), (2, 32), (3, 32), (4, 32), (5, 32), (6, 32), (7, 32), (8, 32), (10, 16),
                                  (4, 40), (6, 24), (7, 20), (2, 88), (1, 160), (9, 32), (3, 100)])
 def test_hash_every_row_tile_count(H, dtype, T, L, r):
-    # 1..8 tiles of 32 rows per pass over the tokens (L * r rows, at most 256 per pass), at sizes that take the
-    # small, the 64-token and the 128-token workgroups; 129..160 rows (5 tiles) must take a 6-tile instance;
-    # r = 20 and r = 100 are not multiples of 8 (general epilogue), (9, 32) and (3, 100) need two passes.
+    # 1..8 tiles of 32 rows per pass over the tokens (L * r rows, at most 256 per pass), at sizes that take workgroups
+    # of 32, 64 and 128 tokens; 129..160 rows (5 tiles) must take a shape of 6 tiles; r = 20 and r = 100 are not
+    # multiples of 8 (a test per row in the arg-max), (9, 32) and (3, 100) need two passes.
     _hash_case(H, dtype, T, L, r)
 
 
@@ -342,8 +341,8 @@ def test_hash_every_row_tile_count(H, dtype, T, L, r):
 @pytest.mark.parametrize("T", [777, 8192 + 33, 65536 + 77])
 @pytest.mark.parametrize("L,r", [(1, 32), (4, 32), (5, 32), (6, 32), (8, 32), (3, 100), (2, 256)])
 def test_hash_rows_with_a_tail(H, dtype, T, L, r):
-    # rows of 33 16-byte pieces: not a whole number of 128-byte chunks, so every size takes the general kernel
-    # with its tail step, at every number of row tiles
+    # rows of 33 16-byte pieces: not a whole number of 128-byte chunks, so the last chunk is fetched clamped and zeroed
+    # behind the row's end, at every number of row tiles
     _hash_case(H, dtype, T, L, r, d=264 if dtype == "bf16" else 132)
 
 
@@ -360,12 +359,11 @@ def test_hash_edges_of_the_shapes(H, dtype, T, L, r, pieces):
 
 
 def _hash_case(H, dtype, T, L, r, d=None):
-    # Large inputs with rows of whole 128-byte chunks take the kernels that stage both operands through LDS:
-    # 193..256 rows of R per pass and T >= 65536 the one that splits the rows of R between two waves and joins the
-    # halves at the end (r = 256 puts ONE hash on both halves, L = 7 with r = 32 leaves the last 32 staged rows
-    # unused); up to 128 rows the 128-token (T >= 24576) or 64-token workgroups.  Random tokens plus exact +-ties
-    # inside a lane, across lane halves, across tiles and across the two row halves, at the start and in the
-    # ragged tail.
+    # The rows of R of a token group sit in one, two or four waves and the results of several are joined at the end: one
+    # row tile per wave up to 8192 tokens and in single precision, two waves with more than 128 rows (r = 256 puts ONE
+    # hash on both, L = 7 with r = 32 leaves the last 32 staged rows unused), one otherwise, with workgroups of 128
+    # (T >= 24576) or 64 tokens.  Random tokens plus exact +-ties inside a lane, across lane halves, across tiles and
+    # across the waves' rows, at the start and in the ragged tail.
     import oracle
     if d is None:
         d = 256 if dtype == "bf16" else 128
