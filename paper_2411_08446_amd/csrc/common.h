@@ -50,15 +50,15 @@ template <typename DT, int E> __device__ __forceinline__ void div_count(float (&
 
 // One wave per row (or cluster), or several waves to a few tokens, can mean more than 2^32 threads, which a
 // one-dimensional launch cannot express (a dispatch counts work-items per dimension in 32 bits): grids beyond 2^22
-// workgroups (of at most 512 threads) are folded into two dimensions.  Surplus workgroups of the last row leave through
-// the kernels' bounds checks.
+// workgroups (of at most 512 threads) are folded into rows of kFoldedRow.  Surplus workgroups of the last row leave
+// through the kernels' bounds checks.  The width is a constant: a kernel that asks for the grid's width waits for one more
+// load before it can start (hash of 16384 rows of 768 bf16: 8.6 against 8.0 us).
+constexpr uint32_t kFoldedRow = 1u << 16;
 inline dim3 grid_of_blocks(uint64_t blocks) {
-  constexpr uint64_t kMaxX = 1ull << 22;
-  if (blocks <= kMaxX) return dim3((uint32_t)(blocks == 0 ? 1 : blocks));
-  const uint64_t by = (blocks + kMaxX - 1) / kMaxX;
-  return dim3((uint32_t)((blocks + by - 1) / by), (uint32_t)by);
+  if (blocks <= 1ull << 22) return dim3((uint32_t)(blocks == 0 ? 1 : blocks));
+  return dim3(kFoldedRow, (uint32_t)((blocks + kFoldedRow - 1) / kFoldedRow));
 }
-__device__ __forceinline__ uint64_t linear_block() { return (uint64_t)blockIdx.y * gridDim.x + blockIdx.x; }
+__device__ __forceinline__ uint64_t linear_block() { return (uint64_t)blockIdx.y * kFoldedRow + blockIdx.x; }
 
 // Rows are moved as raw 16-byte pieces (uint4) and only widened to binary32
 // where arithmetic happens, so that loads in flight cost 4 registers each.
