@@ -853,6 +853,8 @@ __device__ __forceinline__ bool sort_item(const BinArgs& a, uint32_t& item, uint
     st.equal = 0;
     st.common = common;
   }
+  // the places of the sample are computed from st.n (kPick has a barrier of its own before it reads st)
+  if (CROWDED && step == kSample) __syncthreads();
   uint32_t rest = n;                                // keys to sort
   for (;;) {
     const uint32_t tid = own_thread();
