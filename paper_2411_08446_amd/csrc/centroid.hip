@@ -369,13 +369,14 @@ __global__ __launch_bounds__(256) void centroid_kernel(
   // here: behind the row stores the three dependent loads would also wait for the stores to land (65536 rows of 1024
   // bf16 to two experts each, no such cluster: 76.4 -> 75.3 us)
   bool meets_long = false;
+  int32_t end_cluster = 0;   // lanes 0..2: clusters of the block's first position and of the two block sizes' last ones
   if (shares && (uint64_t)(block >> 1) * kSmallWindow < N) {
     const uint32_t m = block >> 1, p0 = m * kSmallWindow;
     const uint32_t p = lane == 0 ? p0 : min(p0 + (lane == 1 ? kSmallWindow : kLargeWindow), N) - 1;
     bool cut = false;
     if (lane < (m % 2 == 0 ? 3u : 2u)) {
-      const int32_t sc = seg_of[perm[p]];
-      cut = seg_offsets[sc + 1] - seg_offsets[sc] > kWindowMin;
+      end_cluster = seg_of[perm[p]];
+      cut = seg_offsets[end_cluster + 1] - seg_offsets[end_cluster] > kWindowMin;
     }
     meets_long = __builtin_amdgcn_ballot_w64(cut) != 0;
   }
@@ -503,13 +504,9 @@ __global__ __launch_bounds__(256) void centroid_kernel(
     const uint32_t m = block >> 1, half = block & 1;
     const uint32_t p0 = m * kSmallWindow;
     const bool wide = (m & 1) == 0;
-    const int32_t pos[3] = {(int32_t)p0, (int32_t)(min(p0 + kSmallWindow, N) - 1),
-                            (int32_t)(min(p0 + (wide ? kLargeWindow : kSmallWindow), N) - 1)};
-    int32_t at[3];                           // clusters of the block's first position and of the two blocks' last ones
+    int32_t at[3];
 #pragma unroll
-    for (int j = 0; j < 3; ++j) at[j] = perm[pos[j]];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) at[j] = __builtin_amdgcn_readfirstlane(seg_of[at[j]]);
+    for (int j = 0; j < 3; ++j) at[j] = __builtin_amdgcn_readlane(end_cluster, j);
     const uint32_t d = cpr * E;
     auto duty = [&](int32_t sc, uint32_t W, uint32_t slot) {
       const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[sc]);
