@@ -195,3 +195,31 @@ def test_parts_whose_workgroups_do_not_run_are_taken_over(name, first_bin):
     expert[-500:] = 3                                   # work behind the large bin, too
     print("case parts taken over:", name, first_bin, flush=True)
     _compare_with_takeover(expert, ids, E, L, r, first_bin)
+
+
+def test_large_bins_of_changing_sizes(H):
+    # The same result every time, whatever the call before has left in LDS: large bins of several sizes (more than 65536
+    # keys draw a larger sample) and a balanced input in turn.  The workgroups of a bin's parts must agree on the parts'
+    # ranges to the key.
+    rng = np.random.default_rng(17)
+    E, L, r = 4, 6, 16                                  # 2 expert bits, 30 bucket bits: a bin is 6 bucket bits
+    cases = []
+    for N, spread in ((131072, 1 << 24), (20000, 1 << 24), (80000, 1 << 24), (16384, 1 << 30)):
+        ids = rng.integers(0, spread, N, dtype=np.uint64)
+        expert = np.full(N, 2) if spread == 1 << 24 else rng.integers(0, E, N)
+        x = torch.randn(N, 8, device="cuda")
+        et = torch.from_numpy(expert.astype(np.int32).reshape(N, 1)).cuda()
+        bt = torch.from_numpy(ids.view(np.int64)).cuda()
+        cases.append((x, et, bt, lsh.CompressOutputs.allocate(N, 8, 1, E, L, r, torch.float32), []))
+    for call in range(30):
+        for x, et, bt, o, first in cases:
+            lsh.lshmoe_compress(x, et, bt, E, L, r, o)
+            S = int(o.num_segments)
+            got = [o.num_segments.clone(), o.perm.clone(), o.seg_of.clone(), o.seg_offsets[:S + 1].clone(),
+                   o.seg_expert[:S].clone(), o.expert_offsets.clone(), o.centroids[:S].clone()]
+            if not first:
+                key = (et[:, 0].long() << 40) + bt
+                assert S == int(torch.unique(key).numel())
+                first.extend(got)
+            for a, b in zip(got, first):
+                assert torch.equal(a, b), "call %d of %d assignments" % (call, x.shape[0])
