@@ -93,6 +93,31 @@ __device__ __forceinline__ void row_sum_kahan(const char* __restrict__ tokens, c
   }
 }
 
+// Data that workgroups of one launch hand to each other, whatever XCD they run on: eight bytes at a time past the XCD's own
+// L2 (relaxed device-scope accesses).  Such a store is in memory once it is counted off (vmcnt), so "written before the
+// counter moves" is a wait and not a device-scope fence, which writes back all that the L2 holds: with two fences per block a
+// call with 64 clusters of 1024 members took 178 us, with 200 of 300 269 us, one of 65536 278 us; without 141, 173, 180.
+__device__ __forceinline__ void store_shared8(void* p, uint32_t lo, uint32_t hi) {
+  __hip_atomic_store((uint64_t*)p, (uint64_t)hi << 32 | lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ __forceinline__ uint2 load_shared8(const void* p) {
+  const uint64_t v = __hip_atomic_load((const uint64_t*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return make_uint2((uint32_t)v, (uint32_t)(v >> 32));
+}
+__device__ __forceinline__ void store_shared_row(float* p, float4 v) {
+  store_shared8(p, __float_as_uint(v.x), __float_as_uint(v.y));
+  store_shared8(p + 2, __float_as_uint(v.z), __float_as_uint(v.w));
+}
+__device__ __forceinline__ float4 load_shared_row(const float* p) {
+  const uint2 a = load_shared8(p), b = load_shared8(p + 2);
+  return make_float4(__uint_as_float(a.x), __uint_as_float(a.y), __uint_as_float(b.x), __uint_as_float(b.y));
+}
+__device__ __forceinline__ void wait_for_stores() {
+  asm volatile("" ::: "memory");               // the stores stay in front of it, the counter's increment behind
+  __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
+  asm volatile("" ::: "memory");
+}
+
 // A cluster with more than kWindowMin members is summed by many waves: the sorted positions are cut into
 // aligned blocks of kCentroidWindow; the wave that owns block m sums the part of the block that belongs to the
 // long cluster containing the block's first position (slot 2m) and the part that belongs to a long cluster
@@ -130,20 +155,18 @@ __device__ __forceinline__ void long_cluster_window(
     }
 #pragma unroll
     for (int i = 0; i < E; i += 4) {
-      *(float4*)(out_row + (size_t)c * E + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+      store_shared_row(out_row + (size_t)c * E + i, make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]));
       if (whole)
-        *(float4*)(out_row + d + (size_t)c * E + i) = make_float4(comp[i], comp[i + 1], comp[i + 2], comp[i + 3]);
+        store_shared_row(out_row + d + (size_t)c * E + i, make_float4(comp[i], comp[i + 1], comp[i + 2], comp[i + 3]));
       else if (kEndRows)
-        *(uint2*)(end_half + c * 16) =
-            make_uint2(f32_to_bf16_pair(comp[i], comp[i + 1]), f32_to_bf16_pair(comp[i + 2], comp[i + 3]));
+        store_shared8(end_half + c * 16, f32_to_bf16_pair(comp[i], comp[i + 1]), f32_to_bf16_pair(comp[i + 2], comp[i + 3]));
     }
   });
-  __threadfence();  // the partial row is visible device-wide before the counter moves
+  wait_for_stores();  // the partial row is in memory before the counter moves
   uint32_t old = 0;
   if (lane == 0) old = atomicAdd(&counters[first_slot], 1u);
   old = __builtin_amdgcn_readfirstlane(old);
   if (old != m1 - m0) return;
-  __threadfence();  // last window of the cluster: every other partial row is complete and visible
   const uint32_t nwin = m1 - m0 + 1;
   const bool whole0 = (uint32_t)lo % kCentroidWindow == 0, whole1 = (uint32_t)hi % kCentroidWindow == 0;
   const float fn = (float)(hi - lo), inv = 1.0f / fn;
@@ -156,7 +179,7 @@ __device__ __forceinline__ void long_cluster_window(
 #pragma unroll
       for (int end = 0; end < 2; ++end) {
         if (end == 0 ? whole0 : whole1) continue;
-        const uint2 w = *(const uint2*)(dst + c * 16 + end * 8);
+        const uint2 w = load_shared8(dst + c * 16 + end * 8);
         err[0] -= __uint_as_float(w.x << 16); err[1] -= __uint_as_float(w.x & 0xffff0000u);
         err[2] -= __uint_as_float(w.y << 16); err[3] -= __uint_as_float(w.y & 0xffff0000u);
       }
@@ -170,8 +193,8 @@ __device__ __forceinline__ void long_cluster_window(
         const bool whole_j = (jj != 0 || whole0) && (jj != nwin - 1 || whole1);
 #pragma unroll
         for (int i = 0; i < E; i += 4) {
-          const float4 v = *(const float4*)(src + i);
-          const float4 w = whole_j ? *(const float4*)(src + d + i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          const float4 v = load_shared_row(src + i);
+          const float4 w = whole_j ? load_shared_row(src + d + i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
           x[u][i] = v.x; x[u][i + 1] = v.y; x[u][i + 2] = v.z; x[u][i + 3] = v.w;
           comp[u][i] = w.x; comp[u][i + 1] = w.y; comp[u][i + 2] = w.z; comp[u][i + 3] = w.w;
         }
@@ -196,8 +219,9 @@ __device__ __forceinline__ void long_cluster_window(
 
 // The same with workgroups (needs the LDS of the shared sums).  The sorted positions are cut into aligned blocks of W and
 // two workgroups take a block, each one half of the columns: every wave sums its quarter of the block's part of the
-// cluster into LDS, wave 0 adds the four in wave order, writes half a partial row, fences and bumps the counter (two
-// device-scope fences per block).  The workgroup that brings the counter to twice the cluster's block count adds the partial
+// cluster into LDS, wave 0 adds the four in wave order, writes half a partial row and bumps the half's counter (that of the
+// cluster's first slot, or the one of its next block's, which counts for nobody else: the cluster covers that block's first
+// position).  The workgroup that brings the counter to the cluster's block count adds its half of the partial
 // rows in position order, again a quarter per wave joined through LDS in wave order, so the result does not depend on
 // which workgroup came last.  Every join is by two-sums, and the first takes the waves' compensations with it (in LDS, in
 // the columns of the other half): with plain sums the error was a third larger than that of four waves that share the
@@ -215,6 +239,16 @@ __device__ __forceinline__ void long_cluster_window(
 // and at most one cluster beyond kWindowMin covers a block's first position and one starts inside it - of both sizes
 // together, since no two clusters of 256 members and more start within 256 positions.
 constexpr int kSmallWindowMax = 8192;
+// The blocks are looked after by workgroups of their own, the first of the grid: with the long clusters' blocks behind the
+// clusters that a workgroup has itself (up to 32 rows one after the other), the kernel waited for them (16384 rows of 1536
+// bytes, one cluster of 4362: 26.9 us; first 18.9; without fences, see store_shared8, 16.5).  A workgroup asks for up to 16
+// of its (block, half) duties with one chain of three loads.  No more than 1024, or their looking around delays inputs
+// that have no long cluster (65536 rows of 2048 bytes, two experts each: 2048 of them + 1 us); with 256, inputs of long
+// clusters alone wait for them (64 clusters of 1024: 215 us for the call, with 1024 202, fences in both).
+constexpr uint32_t kDutyWorkgroups = 1024, kDutiesAtOnce = 16;
+__host__ __device__ inline uint32_t duty_workgroups(uint32_t N) {
+  return N <= (uint32_t)kWindowMin ? 0u : min(2 * ((N + kCentroidWindow - 1) / kCentroidWindow), kDutyWorkgroups);
+}
 constexpr uint32_t kSmallWindow = kCentroidWindow, kLargeWindow = 2 * kCentroidWindow;
 static_assert(kLargeWindow <= (uint32_t)kWindowMin, "a block meets at most two clusters that are cut into blocks");
 
@@ -272,19 +306,18 @@ __device__ __forceinline__ void long_cluster_wg_window(
           e.x -= q.x; e.y -= q.y; e.z -= q.z; e.w -= q.w;
         }
       }
-      *(float4*)(out_row + i) = make_float4(v.x + e.x, v.y + e.y, v.z + e.z, v.w + e.w);
+      store_shared_row(out_row + i, make_float4(v.x + e.x, v.y + e.y, v.z + e.z, v.w + e.w));
     }
-    __threadfence();  // the partial row is visible device-wide before the counter moves
-    if (lane == 0) *last_flag = atomicAdd(&counters[first_slot], 1u) == 2 * (m1 - m0) + 1 ? 1u : 0u;
+    wait_for_stores();  // the partial row is in memory before the counter moves
+    if (lane == 0) *last_flag = atomicAdd(&counters[half == 0 ? first_slot : step * (m0 + 1)], 1u) == m1 - m0 ? 1u : 0u;
   }
   __syncthreads();    // the flag is set; the four LDS rows are free again
   if (*last_flag == 0u) return;   // the same for all four waves
-  __threadfence();    // last half block of the cluster: every other partial row is complete and visible
   const uint32_t nwin = m1 - m0 + 1;
   const uint32_t per = (nwin + 3) / 4;
   const uint32_t j0 = min(w4 * per, nwin), j1 = min(j0 + per, nwin);
   constexpr int kRows = 4;
-  for (uint32_t c = lane; c < cpr; c += 64) {
+  for (uint32_t c = c_lo + lane; c < c_hi; c += 64) {
     float acc[E], err[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) acc[i] = err[i] = 0.0f;
@@ -296,7 +329,7 @@ __device__ __forceinline__ void long_cluster_wg_window(
         const float* src = partial + (size_t)(jj == 0 ? first_slot : step * (m0 + jj)) * d + (size_t)c * E;
 #pragma unroll
         for (int i = 0; i < E; i += 4) {
-          const float4 v = *(const float4*)(src + i);
+          const float4 v = load_shared_row(src + i);
           x[u][i] = v.x; x[u][i + 1] = v.y; x[u][i + 2] = v.z; x[u][i + 3] = v.w;
         }
       }
@@ -316,7 +349,7 @@ __device__ __forceinline__ void long_cluster_wg_window(
   __syncthreads();
   const float fn = (float)(hi - lo), inv = 1.0f / fn;
   char* dst = centroids + (size_t)s * row_bytes;
-  for (uint32_t c = threadIdx.x; c < cpr; c += 256) {
+  for (uint32_t c = c_lo + threadIdx.x; c < c_hi; c += 256) {
     float acc[E];
 #pragma unroll
     for (int i = 0; i < E; ++i) {
@@ -344,8 +377,12 @@ __global__ __launch_bounds__(256) void centroid_kernel(
   const uint32_t S = (uint32_t)*num_segments;
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t block64 = linear_block();
-  if (block64 * 4u > (uint64_t)N) return;   // surplus workgroups of a folded grid (whole workgroup: no barrier is skipped by part of one)
-  const uint32_t block = (uint32_t)block64;
+  const bool shares = LPR == 64 && coop != 0;
+  const uint32_t duty_wgs = shares ? duty_workgroups(N) : 0;
+  // surplus workgroups of a folded grid (whole workgroups: no barrier is skipped by part of one)
+  if (block64 >= duty_wgs + ((uint64_t)N + 3) / 4) return;
+  const bool on_duty = block64 < duty_wgs;
+  const uint32_t block = (uint32_t)(on_duty ? block64 : block64 - duty_wgs);
   const uint32_t wave = block * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t s = wave * G + lane / LPR;
   const size_t row_bytes = (size_t)cpr * 16;
@@ -353,8 +390,51 @@ __global__ __launch_bounds__(256) void centroid_kernel(
   // cluster is bound by memory latency (one round of 8 rows per ~2 us), and when a few hundred of them hold
   // most of the assignments the kernel waits for them.  The four waves of the workgroup therefore share each
   // such cluster among the workgroup's four: a quarter of the members each, joined through LDS in wave order.
-  const bool shares = LPR == 64 && coop != 0;
   auto shared_size = [&](int32_t n) { return shares && n > kCoopMin && n <= kWindowMin; };
+  if constexpr (LPR == 64) {
+    if (on_duty) {
+      // window duty with the workgroup's LDS rows.  Duty 2 m + half: one half of the columns of block m of kSmallWindow positions
+      // and, with m even, of the block of kLargeWindow positions that starts there.
+      const uint32_t duties = 2 * ((N + kSmallWindow - 1) / kSmallWindow), d = cpr * E;
+      // (a turn by two from one round to the next: the wide blocks fall to other workgroups then)
+      auto duty_of = [&](uint32_t q) { return (block + 2 * q) % duty_wgs + q * duty_wgs; };
+      for (uint32_t q0 = 0; q0 * duty_wgs < duties; q0 += kDutiesAtOnce) {
+        // lanes 3 j .. 3 j + 2: the clusters of the j-th duty's first position and of the two block sizes' last ones
+        const uint32_t mine = duty_of(q0 + lane / 3);
+        bool cut = false;
+        int32_t cluster = 0;
+        if (lane < 3 * kDutiesAtOnce && mine < duties) {
+          const uint32_t m = mine >> 1, p0 = m * kSmallWindow;
+          const uint32_t p = lane % 3 == 0 ? p0 : min(p0 + (lane % 3 == 1 || m % 2 != 0 ? kSmallWindow : kLargeWindow), N) - 1;
+          cluster = seg_of[perm[p]];
+          cut = seg_offsets[cluster + 1] - seg_offsets[cluster] > kWindowMin;
+        }
+        for (uint64_t left = __builtin_amdgcn_ballot_w64(cut); left != 0;) {   // the same in all four waves
+          const uint32_t j = (uint32_t)__builtin_ctzll(left) / 3;
+          left = left >> (3 * j + 3) << (3 * j + 3);
+          const uint32_t at = duty_of(q0 + j), m = at >> 1, half = at & 1, p0 = m * kSmallWindow;
+          int32_t of[3];
+#pragma unroll
+          for (int i = 0; i < 3; ++i) of[i] = __builtin_amdgcn_readlane(cluster, (int)(3 * j) + i);
+          auto duty = [&](int32_t sc, uint32_t W, uint32_t slot) {
+            const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[sc]);
+            const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[sc + 1]);
+            if (hi - lo <= kWindowMin || (hi - lo <= kSmallWindowMax) != (W == kSmallWindow)) return;
+            long_cluster_wg_window<DT>(tokens, perm, seg_offsets, centroids, partial, counters, coop_sum, sc, p0, W,
+                                       max(lo, (int32_t)p0), min(hi, (int32_t)min(p0 + W, N)), slot, half, k, cpr, d, mean);
+          };
+          // both block sizes meet the cluster of the first position; it is of one size class
+          duty(of[0], kSmallWindow, 2 * m);
+          if (of[1] != of[0]) duty(of[1], kSmallWindow, 2 * m + 1);
+          if (m % 2 == 0) {
+            duty(of[0], kLargeWindow, 2 * m);
+            if (of[2] != of[0]) duty(of[2], kLargeWindow, 2 * m + 1);
+          }
+        }
+      }
+      return;
+    }
+  }
   // the offsets of the workgroup's four clusters, fetched now (lane j holds the start of cluster 4*block + j,
   // clamped to the end) so that the sharing pass below does not start with a memory round trip
   // (read into scalars at once: waiting for this load later, behind the row stores, would keep the wave alive
@@ -364,21 +444,6 @@ __global__ __launch_bounds__(256) void centroid_kernel(
     const int32_t v = seg_offsets[min(block * 4u + min(lane, 4u), S)];
 #pragma unroll
     for (int j = 0; j < 5; ++j) wg_off[j] = __builtin_amdgcn_readlane(v, j);
-  }
-  // whether the workgroup's block of positions meets a cluster that is cut into blocks (the window duty below), asked
-  // here: behind the row stores the three dependent loads would also wait for the stores to land (65536 rows of 1024
-  // bf16 to two experts each, no such cluster: 76.4 -> 75.3 us)
-  bool meets_long = false;
-  int32_t end_cluster = 0;   // lanes 0..2: clusters of the block's first position and of the two block sizes' last ones
-  if (shares && (uint64_t)(block >> 1) * kSmallWindow < N) {
-    const uint32_t m = block >> 1, p0 = m * kSmallWindow;
-    const uint32_t p = lane == 0 ? p0 : min(p0 + (lane == 1 ? kSmallWindow : kLargeWindow), N) - 1;
-    bool cut = false;
-    if (lane < (m % 2 == 0 ? 3u : 2u)) {
-      end_cluster = seg_of[perm[p]];
-      cut = seg_offsets[end_cluster + 1] - seg_offsets[end_cluster] > kWindowMin;
-    }
-    meets_long = __builtin_amdgcn_ballot_w64(cut) != 0;
   }
   // the sharing pass comes first: after its own cluster's stores a wave should have nothing left to wait for
   if (shares) {
@@ -496,34 +561,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
       }
     }
   }
-  if (shares) {
-    // window duty with the workgroup's LDS rows: workgroups 2m and 2m + 1 look after block m of kSmallWindow positions
-    // and, with m even, the block of kLargeWindow positions that starts there
-    // (every wave of the workgroup gets here: nothing above returns for a single wave)
-    if (!meets_long) return;
-    const uint32_t m = block >> 1, half = block & 1;
-    const uint32_t p0 = m * kSmallWindow;
-    const bool wide = (m & 1) == 0;
-    int32_t at[3];
-#pragma unroll
-    for (int j = 0; j < 3; ++j) at[j] = __builtin_amdgcn_readlane(end_cluster, j);
-    const uint32_t d = cpr * E;
-    auto duty = [&](int32_t sc, uint32_t W, uint32_t slot) {
-      const int32_t lo = __builtin_amdgcn_readfirstlane(seg_offsets[sc]);
-      const int32_t hi = __builtin_amdgcn_readfirstlane(seg_offsets[sc + 1]);
-      if (hi - lo <= kWindowMin || (hi - lo <= kSmallWindowMax) != (W == kSmallWindow)) return;
-      long_cluster_wg_window<DT>(tokens, perm, seg_offsets, centroids, partial, counters, coop_sum, sc, p0, W,
-                                 max(lo, (int32_t)p0), min(hi, (int32_t)min(p0 + W, N)), slot, half, k, cpr, d, mean);
-    };
-    // both block sizes meet the cluster of the first position; it is of one size class
-    duty(at[0], kSmallWindow, 2 * m);
-    if (at[1] != at[0]) duty(at[1], kSmallWindow, 2 * m + 1);
-    if (wide) {
-      duty(at[0], kLargeWindow, 2 * m);
-      if (at[2] != at[0]) duty(at[2], kLargeWindow, 2 * m + 1);
-    }
-    return;
-  }
+  if (shares) return;
   // window duty: wave m looks after block m of the sorted positions
   if ((uint64_t)wave * kCentroidWindow >= N) return;
   const uint32_t p0 = wave * (uint32_t)kCentroidWindow;
@@ -557,9 +595,10 @@ void launch_lpr(const void* tokens, const int32_t* perm, const int32_t* seg_offs
   const size_t coop_bytes = (size_t)4 * cpr * Piece<DT>::kElems * sizeof(float);  // four partial rows in binary32
   const bool coop = LPR == 64 && coop_bytes <= kCoopMaxLds;
   constexpr size_t kCoopMore = 4 * Piece<DT>::kElems * sizeof(float) + 16;   // a piece more per row, the flag
-  hipLaunchKernelGGL((centroid_kernel<DT, LPR>), grid_of_blocks(blocks), dim3(256), coop ? coop_bytes + kCoopMore : 0, stream,
-                     (const char*)tokens, perm, seg_offsets, seg_of, num_segments, (char*)centroids, partial, counters,
-                     (uint32_t)N, (uint32_t)k, cpr, mean ? 1u : 0u, coop ? 1u : 0u);
+  const dim3 grid = grid_of_blocks((uint64_t)blocks + (coop ? duty_workgroups((uint32_t)N) : 0u));
+  hipLaunchKernelGGL((centroid_kernel<DT, LPR>), grid, dim3(256), coop ? coop_bytes + kCoopMore : 0, stream, (const char*)tokens,
+                     perm, seg_offsets, seg_of, num_segments, (char*)centroids, partial, counters, (uint32_t)N, (uint32_t)k,
+                     cpr, mean ? 1u : 0u, coop ? 1u : 0u);
 }
 
 template <typename DT>

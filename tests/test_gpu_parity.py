@@ -251,6 +251,20 @@ def test_long_clusters_of_both_block_sizes(H, dtype, sizes, d):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("sizes", [(257, 8193, 1, 300, 40000, 258, 30000, 12000), (300,) * 300])
+def test_more_blocks_than_workgroups_that_look_after_them(H, dtype, sizes):
+    # 719 blocks of 128 positions are 1438 halves for 1024 workgroups: a second round, with the wide blocks on others
+    T, E = 92000, 2
+    sizes = sizes + (T - sum(sizes),) if sum(sizes) < T else sizes
+    d = 136 if dtype == "bf16" else 68
+    tokens, rot, _ = _rand_inputs(27, T, d, 1, E, 2, 16, dtype)
+    ids = np.empty(T, np.uint64)
+    ids[np.random.default_rng(28).permutation(T)] = np.repeat(np.arange(len(sizes)), sizes).astype(np.uint64)
+    run = H.run_and_check(tokens, rot, np.zeros((T, 1), np.int32), E, dtype, _scale_fn, bucket_override=ids)
+    assert np.diff(run.out.seg_offsets[:run.S + 1].cpu().numpy()).tolist() == list(sizes)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 def test_one_huge_cluster_many_windows(H, dtype):
     # 20000 identical tokens, one bin of one key: 157 block sums are combined by the last wave
     T, d, E = 20000, 64, 2
