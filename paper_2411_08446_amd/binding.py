@@ -111,8 +111,10 @@ def _ptr(t, dtype=None) -> int:
 
 
 def _stream(stream) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    if stream is not None:
+        return stream.cuda_stream
+    # the handle of torch's current stream, without the Stream object around it: 0.2 instead of 2.6 us of a call's 8
+    return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
 
 
 def lshmoe_workspace_bytes(T: int, d: int, k: int, E: int, L: int, r: int, dtype_code: int) -> int:
