@@ -374,7 +374,6 @@ __global__ __launch_bounds__(256) void centroid_kernel(
   constexpr int E = Piece<DT>::kElems;
   // coop: [4 waves][cpr * E] partial sums of a cluster the workgroup shares, or [4 waves][(cpr + 1) * E] and a flag
   extern __shared__ float coop_sum[];
-  const uint32_t S = (uint32_t)*num_segments;
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t block64 = linear_block();
   const bool shares = LPR == 64 && coop != 0;
@@ -386,6 +385,15 @@ __global__ __launch_bounds__(256) void centroid_kernel(
   const uint32_t wave = block * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t s = wave * G + lane / LPR;
   const size_t row_bytes = (size_t)cpr * 16;
+  // Whole-wave rows: the offsets of the workgroup's four clusters, in lanes 0 to 4, asked for together with the number of
+  // clusters (there are N + 1 entries; those behind the last cluster mean nothing and are not used).  One after the other,
+  // and a wave's own offsets once more behind them, these loads were two of the five trips to memory of a one-member
+  // cluster's wave.
+  int32_t offsets = 0;
+  if constexpr (LPR == 64) {
+    if (!on_duty) offsets = seg_offsets[min(block * 4u + min(lane, 4u), N)];
+  }
+  const uint32_t S = (uint32_t)*num_segments;
   // Clusters of kCoopMin+1 .. kWindowMin members (whole-wave rows only): a single wave walking such a
   // cluster is bound by memory latency (one round of 8 rows per ~2 us), and when a few hundred of them hold
   // most of the assignments the kernel waits for them.  The four waves of the workgroup therefore share each
@@ -435,24 +443,20 @@ __global__ __launch_bounds__(256) void centroid_kernel(
       return;
     }
   }
-  // the offsets of the workgroup's four clusters, fetched now (lane j holds the start of cluster 4*block + j,
-  // clamped to the end) so that the sharing pass below does not start with a memory round trip
-  // (read into scalars at once: waiting for this load later, behind the row stores, would keep the wave alive
-  // until its stores have landed)
-  int32_t wg_off[5] = {0, 0, 0, 0, 0};
-  if (shares) {
-    const int32_t v = seg_offsets[min(block * 4u + min(lane, 4u), S)];
-#pragma unroll
-    for (int j = 0; j < 5; ++j) wg_off[j] = __builtin_amdgcn_readlane(v, j);
+  // the sharing pass comes first: after its own cluster's stores a wave should have nothing left to wait for.  One vote over
+  // the four sizes skips it: looking at them one by one cost the common case 1.4 us of 75 (65536 x 1024 bf16, 2 experts).
+  bool any_shared = false;
+  if constexpr (LPR == 64) {
+    const int32_t next = __builtin_amdgcn_update_dpp(0, offsets, 0x101, 0xf, 0xf, false);   // row_shl:1, the next lane's
+    any_shared = __builtin_amdgcn_ballot_w64(lane < 4 && block * 4u + lane < S && shared_size(next - offsets)) != 0;
   }
-  // the sharing pass comes first: after its own cluster's stores a wave should have nothing left to wait for
-  if (shares) {
+  if (__builtin_expect(any_shared, false)) {   // the same for every wave of the workgroup
     const uint32_t s0 = block * 4u, w4 = threadIdx.x >> 6;
 #pragma unroll
     for (uint32_t j = 0; j < 4; ++j) {
       const uint32_t sj = s0 + j;
       if (sj >= S) break;  // the same for every wave of the workgroup
-      const int32_t lo = wg_off[j], hi = wg_off[j + 1];
+      const int32_t lo = __builtin_amdgcn_readlane(offsets, j), hi = __builtin_amdgcn_readlane(offsets, j + 1);
       const int32_t n = hi - lo;
       if (!shared_size(n)) continue;
       const int32_t quarter = (n + 3) / 4;
@@ -485,7 +489,15 @@ __global__ __launch_bounds__(256) void centroid_kernel(
     }
   }
   if (s < S) {
-    const int32_t lo = uniform<LPR>(seg_offsets[s]), hi = uniform<LPR>(seg_offsets[s + 1]);
+    int32_t lo, hi;
+    if constexpr (LPR == 64) {
+      const int32_t w4 = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+      lo = __builtin_amdgcn_readlane(offsets, w4);
+      hi = __builtin_amdgcn_readlane(offsets, w4 + 1);
+    } else {
+      lo = seg_offsets[s];
+      hi = seg_offsets[s + 1];
+    }
     const int32_t n = hi - lo;
     if (shared_size(n)) {
       // done by the workgroup, above
