@@ -47,18 +47,27 @@ __global__ __launch_bounds__(256) void restore_kernel(
   const size_t row_bytes = (size_t)cpr * 16;
   const bool no_res = (flags & 1u) != 0;
 
+  // what either order needs first is asked for together with the number of clusters that decides between them
   bool by_cluster = false;
-  if (perm != nullptr && num_segments != nullptr)
+  int32_t member[kRows], s[kRows];
+#pragma unroll
+  for (int u = 0; u < kRows; ++u) s[u] = seg_of[min(a0 + u, N - 1)];
+  if (perm != nullptr && num_segments != nullptr) {
+#pragma unroll
+    for (int u = 0; u < kRows; ++u) member[u] = perm[min(a0 + u, N - 1)];
     by_cluster = (uint64_t)(uint32_t)*num_segments * kClusterOrderBelowDen < (uint64_t)N * kClusterOrderBelowNum;
-  int32_t s[kRows];
+  }
   uint32_t a[kRows];   // the rows this lane group restores
   bool live[kRows], full[kRows];
 #pragma unroll
   for (int u = 0; u < kRows; ++u) {
     live[u] = a0 + u < N;
     a[u] = a0 + u;
-    if (by_cluster && live[u]) a[u] = (uint32_t)uniform<LPR>(perm[a0 + u]);
-    s[u] = live[u] ? uniform<LPR>(seg_of[a[u]]) : 0;
+    if (by_cluster) {
+      a[u] = (uint32_t)uniform<LPR>(member[u]);
+      s[u] = seg_of[a[u]];
+    }
+    s[u] = uniform<LPR>(s[u]);
   }
 #pragma unroll
   for (int u = 0; u < kRows; ++u) {
