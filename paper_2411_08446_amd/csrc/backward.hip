@@ -10,6 +10,7 @@
 // sum.  HBM-bound gather like the restore; for a one-member cluster G_s is the
 // row dL/dY_a itself, so the term is h_s and two of the three reads are skipped.
 #include "kernels.h"
+#include "stretch.h"
 
 namespace lshmoe {
 
@@ -28,16 +29,99 @@ template <int LPR> __device__ __forceinline__ int32_t uniform(int32_t v) {
 // the segment sums, who pay more for it than this kernel would (large clusters: 375.5 -> 391.3; 32768 rows: 223.1 -> 216.5).
 inline bool streams_rows(int64_t T, uint32_t cpr) { return (uint64_t)T * cpr * 16 >= 32ull << 20; }
 
+// The same for one stretch of the rows (stretch.h): sixteen lanes to a token.
+template <typename DT>
+__device__ __forceinline__ void grad_stretch(const char* __restrict__ grad_out, const char* __restrict__ grad_centroids,
+                                             const char* __restrict__ grad_expert_out, const int32_t* __restrict__ seg_of,
+                                             const int32_t* __restrict__ seg_offsets, char* __restrict__ grad_tokens, uint32_t k,
+                                             size_t row_bytes, bool no_res, const StretchDuty& duty, int2* look) {
+  constexpr int E = Piece<DT>::kElems, Q = 2;
+  constexpr uint32_t kGroups = 256 / kStretchPieces;
+  static_assert(kGroups * Q == kStretchTokens, "two tokens per lane group");
+  const uint32_t at = duty.at + threadIdx.x % kStretchPieces * 16;
+  for (uint32_t first = duty.first; first < duty.end; first += kStretchTokens) {
+    const uint32_t here = min(kStretchTokens, duty.end - first);
+    // the rows of the lane group's first token are on their way while the lookups are made
+    uint32_t t = first + min(threadIdx.x / kStretchPieces, here - 1);
+    uint4 ahead[2];
+#pragma unroll
+    for (uint32_t j = 0; j < 2; ++j)
+      ahead[j] = no_res || j >= k ? make_uint4(0, 0, 0, 0) : load16_stream(grad_out + ((size_t)t * k + j) * row_bytes + at);
+    __builtin_amdgcn_sched_barrier(0);
+    for (uint32_t i = threadIdx.x; i < here * k; i += 256) {
+      const int32_t s = seg_of[first * k + i];
+      look[i] = make_int2(s, seg_offsets[s + 1] - seg_offsets[s]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      // lane groups past the end do the last token once more
+      if (q > 0) t = first + min(q * kGroups + threadIdx.x / kStretchPieces, here - 1);
+      float acc[E];
+#pragma unroll
+      for (int i = 0; i < E; ++i) acc[i] = 0.0f;
+      for (uint32_t j = 0; j < k; ++j) {
+        const int2 l = look[(t - first) * k + j];
+        const size_t row = (uint32_t)l.x * row_bytes + at;
+        const uint4 h4 = load16(grad_centroids + row);
+        uint4 g4 = make_uint4(0, 0, 0, 0), s4 = g4;
+        if (l.y != 1 && !no_res) {
+          g4 = q == 0 && j < 2 ? (j == 0 ? ahead[0] : ahead[1]) : load16_stream(grad_out + ((size_t)t * k + j) * row_bytes + at);
+          s4 = load16(grad_expert_out + row);
+        }
+        float h[E];
+        Piece<DT>::widen(h4, h);
+        if (l.y != 1) {
+          const float fn = (float)l.y, inv = 1.0f / fn;
+          if (no_res) {
+            div_count<DT>(h, fn, inv);
+          } else {
+            float g[E], gs[E];
+            Piece<DT>::widen(s4, gs);
+#pragma unroll
+            for (int i = 0; i < E; ++i) h[i] -= gs[i];
+            div_count<DT>(h, fn, inv);
+            Piece<DT>::widen(g4, g);
+#pragma unroll
+            for (int i = 0; i < E; ++i) h[i] = g[i] + h[i];
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < E; ++i) acc[i] += h[i];
+      }
+      store16_stream(grad_tokens + t * row_bytes + at, Piece<DT>::narrow(acc));
+    }
+    if (first + kStretchTokens < duty.end) __syncthreads();   // before the lookups are overwritten
+  }
+}
+
+// By columns from 64 MB of gradient rows on, of binary32 from 128 MB and two experts.  Measured with 10, 20, 30 per cent of
+// clusters per assignment, us: 16384 x 1024 bf16, two experts 30.8 -> 28.7, 33.1 -> 29.3, 33.7 -> 29.8; 65536 of them 128 -> 107,
+// 131 -> 119, 130 -> 126; one expert 71.4 -> 65.5, 73.6 -> 67.7, 73.4 -> 69.6; 8192, two experts 14.6 -> 15.4, 16.4 -> 15.8; binary32
+// 32768 x 1024, two experts 128 -> 110, 130 -> 122, 130 -> 134; one 71.1 -> 73.9; 8192, two 29.5 -> 30.8.
+StretchPlan plan_grad_tokens(int64_t T, int k, uint32_t cpr, bool bf16) {
+  const bool many = (uint64_t)T * k * cpr * 16 >= (bf16 ? 64ull : 128ull) << 20 && (bf16 || k > 1);
+  return many ? plan_stretches(T, k, cpr, bf16 ? 25 : 20) : StretchPlan{};
+}
+
 template <typename DT, int LPR, bool STREAM>
 __global__ __launch_bounds__(256) void grad_tokens_kernel(
     const char* __restrict__ grad_out, const char* __restrict__ grad_centroids,
     const char* __restrict__ grad_expert_out, const int32_t* __restrict__ seg_of,
     const int32_t* __restrict__ seg_offsets, char* __restrict__ grad_tokens, uint32_t T, uint32_t k, uint32_t cpr,
-    uint32_t flags) {
+    uint32_t flags, StretchPlan plan) {
   constexpr int G = 64 / LPR;
   constexpr int E = Piece<DT>::kElems;
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t wave64 = linear_block() * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (LPR == 64) {
+    if (plan.stretches != 0 && large_clusters(seg_of, T * k, plan.percent)) {   // the same for every workgroup
+      __shared__ int2 look[kStretchTokens * kStretchExperts];
+      grad_stretch<DT>(grad_out, grad_centroids, grad_expert_out, seg_of, seg_offsets, grad_tokens, k, (size_t)cpr * 16,
+                       (flags & 1u) != 0, stretch_duty(plan, linear_block(), T), look);
+      return;
+    }
+  }
   if (wave64 * G >= T) return;
   const uint32_t t = (uint32_t)(wave64 * G) + lane / LPR;   // below T + 64: 32 bits are enough
   if (t >= T) return;
@@ -83,11 +167,14 @@ void launch_lpr(const void* grad_out, const void* grad_centroids, const void* gr
                 hipStream_t stream) {
   constexpr int G = 64 / LPR;
   const uint64_t waves = ((uint64_t)T + G - 1) / G;
-  const uint32_t blocks = (uint32_t)((waves + 3) / 4);
+  uint64_t blocks = (waves + 3) / 4;
+  StretchPlan plan{};
+  if (LPR == 64) plan = plan_grad_tokens(T, k, cpr, std::is_same<DT, BF16>::value);
+  if (plan.workgroups() > blocks) blocks = plan.workgroups();
   auto kern = streams_rows(T, cpr) ? grad_tokens_kernel<DT, LPR, true> : grad_tokens_kernel<DT, LPR, false>;
   hipLaunchKernelGGL(kern, grid_of_blocks(blocks), dim3(256), 0, stream, (const char*)grad_out,
                      (const char*)grad_centroids, (const char*)grad_expert_out, seg_of, seg_offsets,
-                     (char*)grad_tokens, (uint32_t)T, (uint32_t)k, cpr, flags);
+                     (char*)grad_tokens, (uint32_t)T, (uint32_t)k, cpr, flags, plan);
 }
 
 template <typename DT>

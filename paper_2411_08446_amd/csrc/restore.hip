@@ -9,6 +9,7 @@
 // 1 KB and more that is a whole wave, and the cluster lookups are wave-uniform
 // scalars.  Output rows are written with streaming stores.
 #include "kernels.h"
+#include "stretch.h"
 
 namespace lshmoe {
 
@@ -113,15 +114,92 @@ __global__ __launch_bounds__(256) void restore_kernel(
 //     out[t] = sum_j w[t][j] * (expert_out[s_j] + (tokens[t] - centroids[s_j])),   s_j = seg_of[t*k + j],
 // accumulated in binary32 in the order j = 0..k-1 and rounded once.  One lane group per token: the token row
 // is read once, and one row is written instead of k.
+// The same for one stretch of the rows (stretch.h): sixteen lanes to a token.  The tokens' own loads go out first, the lookups
+// of all tokens and experts are made once per workgroup and not once per lane group.
+template <typename DT>
+__device__ __forceinline__ void combine_stretch(const char* __restrict__ tokens, const char* __restrict__ centroids,
+                                                const char* __restrict__ expert_out, const int32_t* __restrict__ seg_of,
+                                                const int32_t* __restrict__ seg_offsets, const float* __restrict__ gate_weight,
+                                                char* __restrict__ out, uint32_t k, size_t row_bytes, bool no_res,
+                                                const StretchDuty& duty, uint2* look) {
+  constexpr int E = Piece<DT>::kElems, Q = 2;
+  constexpr uint32_t kGroups = 256 / kStretchPieces;
+  static_assert(kGroups * Q == kStretchTokens, "two tokens per lane group");
+  const uint32_t at = duty.at + threadIdx.x % kStretchPieces * 16;
+  for (uint32_t first = duty.first; first < duty.end; first += kStretchTokens) {
+    const uint32_t here = min(kStretchTokens, duty.end - first);
+    uint32_t i_of[Q];                     // lane groups past the end do the last token once more
+    uint4 x[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      i_of[q] = min(q * kGroups + threadIdx.x / kStretchPieces, here - 1);
+      x[q] = no_res ? make_uint4(0, 0, 0, 0) : load16_stream(tokens + (first + i_of[q]) * row_bytes + at);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (uint32_t i = threadIdx.x; i < here * k; i += 256) {
+      const uint32_t a = first * k + i, s = (uint32_t)seg_of[a];
+      bool full = !no_res;
+      if (full && seg_offsets != nullptr) full = seg_offsets[s + 1] - seg_offsets[s] != 1;
+      look[i] = make_uint2(s | (full ? 0x80000000u : 0u), __float_as_uint(gate_weight[a]));
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      float acc[E];
+#pragma unroll
+      for (int i = 0; i < E; ++i) acc[i] = 0.0f;
+      for (uint32_t j = 0; j < k; ++j) {
+        const uint2 l = look[i_of[q] * k + j];
+        const bool full = l.x >> 31;
+        const size_t row = (l.x & 0x7fffffffu) * row_bytes + at;
+        const uint4 ec = load16(expert_out + row);
+        uint4 cc = make_uint4(0, 0, 0, 0);
+        if (full) cc = load16(centroids + row);
+        float e[E];
+        Piece<DT>::widen(ec, e);
+        if (full) {
+          float xv[E], cv[E];
+          Piece<DT>::widen(x[q], xv);
+          Piece<DT>::widen(cc, cv);
+#pragma unroll
+          for (int i = 0; i < E; ++i) e[i] += xv[i] - cv[i];
+        }
+        const float w = __uint_as_float(l.y);
+#pragma unroll
+        for (int i = 0; i < E; ++i) acc[i] = fmaf(w, e[i], acc[i]);
+      }
+      store16_stream(out + (first + i_of[q]) * row_bytes + at, Piece<DT>::narrow(acc));
+    }
+    if (first + kStretchTokens < duty.end) __syncthreads();   // before the lookups are overwritten
+  }
+}
+
+// By columns from rows of 8 MB in all on.  Measured with 10, 20, 30, 40 per cent of clusters per assignment, us: 4096 x 1024
+// bf16, two experts 8.8 -> 6.5, 9.0 -> 6.3, 9.0 -> 6.7, 9.1 -> 7.1; 32768 of them 53.6 -> 39.9, 56.1 -> 44.8, 57.0 -> 47.6,
+// 56.9 -> 50.6; 65536 109 -> 84, 112 -> 99, 111 -> 107, 111 -> 110; one expert 75.6 -> 59.3 .. 76.3 -> 71.1.  Rows of binary32
+// are twice as wide for the same L2: 32768 x 1024, two experts 110 -> 82, 114 -> 103, 114 -> 114, 114 -> 119; 8192, one
+// expert 18.2 -> 18.1, 19.5 -> 20.1.
+StretchPlan plan_combine(int64_t T, int k, uint32_t cpr, bool bf16) {
+  return (uint64_t)T * cpr * 16 >= 8ull << 20 ? plan_stretches(T, k, cpr, bf16 ? 25 : 15) : StretchPlan{};
+}
+
 template <typename DT, int LPR>
 __global__ __launch_bounds__(256) void restore_combine_kernel(
     const char* __restrict__ tokens, const char* __restrict__ centroids, const char* __restrict__ expert_out,
     const int32_t* __restrict__ seg_of, const int32_t* __restrict__ seg_offsets, const float* __restrict__ gate_weight,
-    char* __restrict__ out, uint32_t T, uint32_t k, uint32_t cpr, uint32_t flags) {
+    char* __restrict__ out, uint32_t T, uint32_t k, uint32_t cpr, uint32_t flags, StretchPlan plan) {
   constexpr int G = 64 / LPR;
   constexpr int E = Piece<DT>::kElems;
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t wave64 = linear_block() * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if constexpr (LPR == 64) {
+    if (plan.stretches != 0 && large_clusters(seg_of, T * k, plan.percent)) {   // the same for every workgroup
+      __shared__ uint2 look[kStretchTokens * kStretchExperts];
+      combine_stretch<DT>(tokens, centroids, expert_out, seg_of, seg_offsets, gate_weight, out, k, (size_t)cpr * 16,
+                          (flags & 1u) != 0, stretch_duty(plan, linear_block(), T), look);
+      return;
+    }
+  }
   if (wave64 * G >= T) return;
   const uint32_t t = (uint32_t)(wave64 * G) + lane / LPR;   // below T + 64: 32 bits are enough
   if (t >= T) return;
@@ -163,10 +241,13 @@ void launch_combine_lpr(const void* tokens, const void* centroids, const void* e
                         uint32_t cpr, uint32_t flags, hipStream_t stream) {
   constexpr int G = 64 / LPR;
   const uint64_t waves = ((uint64_t)T + G - 1) / G;
-  const uint32_t blocks = (uint32_t)((waves + 3) / 4);
+  uint64_t blocks = (waves + 3) / 4;
+  StretchPlan plan{};
+  if (LPR == 64) plan = plan_combine(T, k, cpr, std::is_same<DT, BF16>::value);
+  if (plan.workgroups() > blocks) blocks = plan.workgroups();
   hipLaunchKernelGGL((restore_combine_kernel<DT, LPR>), grid_of_blocks(blocks), dim3(256), 0, stream, (const char*)tokens,
                      (const char*)centroids, (const char*)expert_out, seg_of, seg_offsets, gate_weight, (char*)out,
-                     (uint32_t)T, (uint32_t)k, cpr, flags);
+                     (uint32_t)T, (uint32_t)k, cpr, flags, plan);
 }
 
 template <typename DT>
