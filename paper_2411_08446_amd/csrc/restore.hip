@@ -28,12 +28,75 @@ template <int LPR> __device__ __forceinline__ int32_t uniform(int32_t v) {
 // 101 against 106 us; S/N 0.38: 124 against 104 us).
 constexpr uint32_t kClusterOrderBelowNum = 13, kClusterOrderBelowDen = 20;  // S / N < 0.65
 
+// The rows of whole tokens for one stretch (stretch.h): sixteen lanes to a token.
+template <typename DT>
+__device__ __forceinline__ void restore_stretch(const char* __restrict__ tokens, const char* __restrict__ centroids,
+                                                const char* __restrict__ expert_out, const int32_t* __restrict__ seg_of,
+                                                const int32_t* __restrict__ seg_offsets, char* __restrict__ out, uint32_t k,
+                                                size_t row_bytes, bool no_res, const StretchDuty& duty, uint32_t* look) {
+  constexpr int E = Piece<DT>::kElems, Q = 2;
+  constexpr uint32_t kGroups = 256 / kStretchPieces;
+  static_assert(kGroups * Q == kStretchTokens, "two tokens per lane group");
+  const uint32_t at = duty.at + threadIdx.x % kStretchPieces * 16;
+  for (uint32_t first = duty.first; first < duty.end; first += kStretchTokens) {
+    const uint32_t here = min(kStretchTokens, duty.end - first);
+    uint32_t i_of[Q];                     // lane groups past the end do the last token once more
+    uint4 x[Q];
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      i_of[q] = min(q * kGroups + threadIdx.x / kStretchPieces, here - 1);
+      x[q] = no_res ? make_uint4(0, 0, 0, 0) : load16_stream(tokens + (first + i_of[q]) * row_bytes + at);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+    for (uint32_t i = threadIdx.x; i < here * k; i += 256) {
+      const uint32_t s = (uint32_t)seg_of[first * k + i];
+      bool full = !no_res;
+      if (full && seg_offsets != nullptr) full = seg_offsets[s + 1] - seg_offsets[s] != 1;
+      look[i] = s | (full ? 0x80000000u : 0u);
+    }
+    __syncthreads();
+    for (uint32_t j = 0; j < k; ++j) {
+      uint4 ec[Q], cc[Q];
+      uint32_t l[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        l[q] = look[i_of[q] * k + j];
+        const size_t row = (l[q] & 0x7fffffffu) * row_bytes + at;
+        ec[q] = load16(expert_out + row);
+        cc[q] = make_uint4(0, 0, 0, 0);
+        if (l[q] >> 31) cc[q] = load16(centroids + row);
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        uint4 y = ec[q];
+        if (!no_res) {
+          float e[E];
+          Piece<DT>::widen(ec[q], e);
+          if (l[q] >> 31) {
+            float xv[E], cv[E];
+            Piece<DT>::widen(x[q], xv);
+            Piece<DT>::widen(cc[q], cv);
+#pragma unroll
+            for (int i = 0; i < E; ++i) e[i] += xv[i] - cv[i];
+          } else {
+#pragma unroll
+            for (int i = 0; i < E; ++i) e[i] += 0.0f;   // as the full formula would, -0 into +0
+          }
+          y = Piece<DT>::narrow(e);
+        }
+        store16_stream(out + ((size_t)(first + i_of[q]) * k + j) * row_bytes + at, y);
+      }
+    }
+    if (first + kStretchTokens < duty.end) __syncthreads();   // before the lookups are overwritten
+  }
+}
+
 template <typename DT, int LPR>
 __global__ __launch_bounds__(256) void restore_kernel(
     const char* __restrict__ tokens, const char* __restrict__ centroids, const char* __restrict__ expert_out,
     const int32_t* __restrict__ seg_of, const int32_t* __restrict__ seg_offsets, const int32_t* __restrict__ perm,
     const int32_t* __restrict__ num_segments, char* __restrict__ out, uint32_t N, uint32_t k, uint32_t cpr,
-    uint32_t flags) {
+    uint32_t flags, StretchPlan plan) {
   constexpr int G = 64 / LPR;
   constexpr int E = Piece<DT>::kElems;
   const uint32_t lane = threadIdx.x & 63;
@@ -42,6 +105,14 @@ __global__ __launch_bounds__(256) void restore_kernel(
   // become scalar-cache loads, and this kernel then runs 3 us slower at the T5 shape (the gate-weighted
   // variant and the token-gradient kernel, which have one more lookup per row, gain from the scalar form).
   const uint64_t block64 = linear_block();
+  if constexpr (LPR == 64) {
+    if (plan.stretches != 0 && (uint64_t)(uint32_t)*num_segments * 100 < (uint64_t)N * plan.percent) {
+      __shared__ uint32_t look[kStretchTokens * kStretchExperts];
+      restore_stretch<DT>(tokens, centroids, expert_out, seg_of, seg_offsets, out, k, (size_t)cpr * 16, (flags & 1u) != 0,
+                          stretch_duty(plan, block64, N / k), look);
+      return;
+    }
+  }
   if (block64 * (4u * G * kRows) >= N) return;
   const uint32_t a0 = (((uint32_t)block64 * 4u + (threadIdx.x >> 6)) * G + lane / LPR) * kRows;
   if (a0 >= N) return;
@@ -262,6 +333,18 @@ void launch_combine_typed(const void* tokens, const void* centroids, const void*
     launch_combine_lpr<DT, 4>(tokens, centroids, expert_out, seg_of, seg_offsets, gate_weight, out, T, k, cpr, flags, stream);
 }
 
+// By columns, in assignment order, when clusters are large and the output, which is written in pieces of 256 bytes then, is
+// about half the last-level cache: whole steps of 32768 x 1024 bf16 and two experts with 0.145 clusters per assignment 117.8
+// -> 116.5 us, of 30000 with 0.07 108.8 -> 103.1, of 20000 x 512 binary32 with 0.06 97.6 -> 93.8.  Twice the rows: 207 -> 220 us
+// (cluster order writes whole rows); one expert per token, where cluster order reads a token's row once too: 16384 rows 15.1
+// -> 15.6, 15.7 -> 17.2 us for this kernel; 0.2 and 0.3 clusters per assignment, two experts, 32768 rows 54 -> 57, 58 -> 62; rows
+// of 1 KB or 4 KB 26.0 -> 28.3, 56 -> 61; fewer rows: the same within 1 per cent.
+StretchPlan plan_restore(int64_t N, int k, uint32_t cpr) {
+  const uint64_t bytes = (uint64_t)N * cpr * 16;
+  return cpr == 8 * kStretchPieces && k > 1 && bytes >= 64ull << 20 && bytes <= 128ull << 20
+             ? plan_stretches(N / k, k, cpr, 15) : StretchPlan{};
+}
+
 template <typename DT, int LPR>
 void launch_lpr(const void* tokens, const void* centroids, const void* expert_out, const int32_t* seg_of,
                 const int32_t* seg_offsets, const int32_t* perm, const int32_t* num_segments, void* out, int64_t N,
@@ -269,10 +352,13 @@ void launch_lpr(const void* tokens, const void* centroids, const void* expert_ou
   constexpr int G = 64 / LPR;
   const uint64_t groups = ((uint64_t)N + kRows - 1) / kRows;
   const uint64_t waves = (groups + G - 1) / G;
-  const uint32_t blocks = (uint32_t)((waves + 3) / 4);
+  uint64_t blocks = (waves + 3) / 4;
+  StretchPlan plan{};
+  if (LPR == 64 && num_segments != nullptr) plan = plan_restore(N, k, cpr);
+  if (plan.workgroups() > blocks) blocks = plan.workgroups();
   hipLaunchKernelGGL((restore_kernel<DT, LPR>), grid_of_blocks(blocks), dim3(256), 0, stream, (const char*)tokens,
                      (const char*)centroids, (const char*)expert_out, seg_of, seg_offsets, perm, num_segments,
-                     (char*)out, (uint32_t)N, (uint32_t)k, cpr, flags);
+                     (char*)out, (uint32_t)N, (uint32_t)k, cpr, flags, plan);
 }
 
 template <typename DT>

@@ -1,4 +1,4 @@
-"""Rows dealt by columns (restore + combine, token gradient on large clusters) against the same calls on parts of the tokens
+"""Rows dealt by columns (restore, restore + combine, token gradient on large clusters) against the same calls on parts of the tokens
 that are too few for it: a token's row depends on nothing else, so the results agree bit for bit.  The parts run the way
 that the other tests hold to the oracle."""
 import pytest
@@ -96,3 +96,25 @@ def test_token_gradient_by_columns(dtype, d, T, k, flags):
         ref = y.sum(1)
         tol = 2.0 ** -7 if dtype == "bf16" else 1e-5
         assert float((got[t].double() - ref).abs().max()) <= tol * float(ref.abs().max())
+
+
+# 64 to 128 MB of output and two to four experts go by columns, the others do not
+@pytest.mark.parametrize("flags", [0, 1])
+@pytest.mark.parametrize("dtype,d,T,k", [("bf16", 1024, 16384, 2), ("bf16", 1024, 32768, 2), ("bf16", 1024, 16384 + 13, 3),
+                                         ("f32", 512, 8192 + 1, 4), ("bf16", 1024, 16383, 2), ("bf16", 1024, 32769, 2)])
+def test_restore_by_columns(dtype, d, T, k, flags):
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(T + d + k)
+    dt = DTYPES[dtype]
+    for share, with_offsets in ((0.002, True), (0.1, True), (0.1, False), (0.3, True)):
+        print("case restore", dtype, d, T, k, flags, share, with_offsets, flush=True)
+        seg, off, size = _clusters(T, k, share, gen)
+        S = size.numel()
+        perm = torch.sort(seg, stable=True)[1].to(torch.int32)
+        count = torch.tensor([S], dtype=torch.int32, device="cuda")
+        x, c, e = _rows(T, d, dt, gen), _rows(S, d, dt, gen), _rows(S, d, dt, gen)
+        got, want = torch.zeros(T, k, d, dtype=dt, device="cuda"), torch.ones(T, k, d, dtype=dt, device="cuda")
+        given = off if with_offsets else None
+        lsh.lshmoe_decompress(x, c, e, seg, given, k, got, flags, perm=perm, num_segments=count)
+        lsh.lshmoe_decompress(x, c, e, seg, given, k, want, flags)      # without the count: assignment order, row by row
+        assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
