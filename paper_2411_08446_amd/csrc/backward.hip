@@ -9,6 +9,7 @@
 // with h_s the expert's gradient for its input c_s and G_s the stored segment
 // sum.  HBM-bound gather like the restore; for a one-member cluster G_s is the
 // row dL/dY_a itself, so the term is h_s and two of the three reads are skipped.
+// With large clusters the rows are dealt to the XCDs by columns (stretch.h, plan_grad_tokens).
 #include "kernels.h"
 #include "stretch.h"
 

@@ -7,7 +7,8 @@
 // consecutive output rows (the k assignments of a token are consecutive, so
 // they share the token row) and strides over the 16-byte pieces; with rows of
 // 1 KB and more that is a whole wave, and the cluster lookups are wave-uniform
-// scalars.  Output rows are written with streaming stores.
+// scalars.  Output rows are written with streaming stores.  With large clusters the
+// rows are dealt to the XCDs by columns instead (stretch.h, plan_restore, plan_combine).
 #include "kernels.h"
 #include "stretch.h"
 
