@@ -234,17 +234,18 @@ __device__ __forceinline__ void long_cluster_window(
 // in rounds of four by the last workgroup alone.  Blocks of 128 positions halve the first part for clusters of up to
 // kSmallWindowMax members; beyond that the second part would outweigh it and blocks are of 256 (with one huge cluster
 // 128 and 512 were both slower).  One cluster of 4362 rows of 1536 bytes among 12022 others: the whole kernel
-// 39.3 -> 25.1 us (with blocks of 256 by one workgroup each before).
+// 39.3 -> 25.1 us (with blocks of 256 by one workgroup each before; 14.3 now, see below).
 // A cluster's blocks of either size use slots of their own: block m of 256 positions holds the slots of block 2m of 128,
 // and at most one cluster beyond kWindowMin covers a block's first position and one starts inside it - of both sizes
 // together, since no two clusters of 256 members and more start within 256 positions.
 constexpr int kSmallWindowMax = 8192;
 // The blocks are looked after by workgroups of their own, the first of the grid: with the long clusters' blocks behind the
 // clusters that a workgroup has itself (up to 32 rows one after the other), the kernel waited for them (16384 rows of 1536
-// bytes, one cluster of 4362: 26.9 us; first 18.9; without fences, see store_shared8, 16.5).  A workgroup asks for up to 16
-// of its (block, half) duties with one chain of three loads.  No more than 1024, or their looking around delays inputs
-// that have no long cluster (65536 rows of 2048 bytes, two experts each: 2048 of them + 1 us); with 256, inputs of long
-// clusters alone wait for them (64 clusters of 1024: 215 us for the call, with 1024 202, fences in both).
+// bytes, one cluster of 4362: the step 66.4 -> 55.1 us; without fences, see store_shared8, 53.7; this kernel 26.9 -> 14.3).
+// A workgroup asks for up to 16 of its (block, half) duties with one chain of three loads.  No more than 1024, or their
+// looking around delays inputs that have no long cluster (65536 rows of 2048 bytes, two experts each: 2048 of them + 1 us);
+// with 256, inputs of long clusters alone wait for them (64 clusters of 1024: 215 us for the call, with 1024 202, fences in
+// both).
 constexpr uint32_t kDutyWorkgroups = 1024, kDutiesAtOnce = 16;
 __host__ __device__ inline uint32_t duty_workgroups(uint32_t N) {
   return N <= (uint32_t)kWindowMin ? 0u : min(2 * ((N + kCentroidWindow - 1) / kCentroidWindow), kDutyWorkgroups);
