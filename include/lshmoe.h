@@ -345,7 +345,7 @@ lshmoe_status lshmoe_backward_workspace_bytes(int64_t T, int32_t d, int32_t k, l
  * members) and rounded once; reproducible bit for bit.
  *
  *   grad_out        [T, k, d] in   dtype; dL/dY in assignment order
- *   perm, seg_offsets, seg_of, num_segments   in, as written by lshmoe_compress
+ *   perm [N], seg_offsets [S+1], seg_of [N], num_segments [1]   in, as written by lshmoe_compress
  *   grad_expert_out [N, d]    out  dtype; rows 0..S-1 are written
  *   workspace                 scratch of at least lshmoe_backward_workspace_bytes(...) bytes, 256-byte
  *                             aligned; contents on entry are ignored

@@ -137,7 +137,7 @@ lshmoe_status compress(const void* tokens, const int32_t* expert, const uint64_t
   e = lshmoe::launch_centroid(tokens, perm, seg_offsets, seg_of, num_segments, centroids,
                               (float*)((char*)workspace + plan.off_partial),
                               (uint32_t*)((char*)workspace + plan.off_counters), plan.N, k, d, dtype == LSHMOE_BF16,
-                              /*mean=*/true, s);
+                              /*mean=*/true, /*all_offsets=*/true, s);
   if (e != hipSuccess) return hip_fail("centroid launch", e);
   return ok();
 }
@@ -340,10 +340,11 @@ lshmoe_status lshmoe_decompress_backward(const void* grad_out, const int32_t* pe
   uint32_t* counters = (uint32_t*)((char*)workspace + plan.off_counters);
   hipError_t e = lshmoe::launch_clear_counters(counters, plan.windows, s);
   if (e != hipSuccess) return hip_fail("counter clear launch", e);
-  // a segment sum over the rows of grad_out: row of sorted position p is grad_out[perm[p]]
+  // a segment sum over the rows of grad_out: row of sorted position p is grad_out[perm[p]].  The offsets are the caller's and
+  // may end at entry S
   e = lshmoe::launch_centroid(grad_out, perm, seg_offsets, seg_of, num_segments, grad_expert_out,
                               (float*)((char*)workspace + plan.off_partial), counters, N, /*k=*/1, d,
-                              dtype == LSHMOE_BF16, /*mean=*/false, s);
+                              dtype == LSHMOE_BF16, /*mean=*/false, /*all_offsets=*/false, s);
   if (e != hipSuccess) return hip_fail("segment sum launch", e);
   return ok();
 }

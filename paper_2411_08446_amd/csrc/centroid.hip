@@ -370,7 +370,7 @@ template <typename DT, int LPR>
 __global__ __launch_bounds__(256) void centroid_kernel(
     const char* __restrict__ tokens, const int32_t* __restrict__ perm, const int32_t* __restrict__ seg_offsets,
     const int32_t* __restrict__ seg_of, const int32_t* __restrict__ num_segments, char* __restrict__ centroids,
-    float* partial, uint32_t* counters, uint32_t N, uint32_t k, uint32_t cpr, uint32_t mean, uint32_t coop) {
+    float* partial, uint32_t* counters, uint32_t early, uint32_t N, uint32_t k, uint32_t cpr, uint32_t mean, uint32_t coop) {
   constexpr int G = 64 / LPR;  // clusters handled side by side by one wave
   constexpr int E = Piece<DT>::kElems;
   // coop: [4 waves][cpr * E] partial sums of a cluster the workgroup shares, or [4 waves][(cpr + 1) * E] and a flag
@@ -386,15 +386,19 @@ __global__ __launch_bounds__(256) void centroid_kernel(
   const uint32_t wave = block * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t s = wave * G + lane / LPR;
   const size_t row_bytes = (size_t)cpr * 16;
-  // Whole-wave rows: the offsets of the workgroup's four clusters, in lanes 0 to 4, asked for together with the number of
-  // clusters (there are N + 1 entries; those behind the last cluster mean nothing and are not used).  One after the other,
-  // and a wave's own offsets once more behind them, these loads were two of the five trips to memory of a one-member
-  // cluster's wave.
+  // Whole-wave rows: the offsets of the workgroup's four clusters, in lanes 0 to 4.  Where the array has N + 1 entries (early:
+  // the highest one, N) they are asked for together with the number of clusters; those behind the last cluster mean nothing
+  // and are not used.  One after the other, and a wave's own offsets once more behind them, these loads were two of the five
+  // trips to memory of a one-member cluster's wave.  Where the array may end at entry S (early: 0) they wait for S.
   int32_t offsets = 0;
+  const uint32_t entry = block * 4u + min(lane, 4u);
   if constexpr (LPR == 64) {
-    if (!on_duty) offsets = seg_offsets[min(block * 4u + min(lane, 4u), N)];
+    if (!on_duty && early != 0) offsets = seg_offsets[min(entry, early)];
   }
   const uint32_t S = (uint32_t)*num_segments;
+  if constexpr (LPR == 64) {
+    if (!on_duty && early == 0) offsets = seg_offsets[min(entry, S)];
+  }
   // Clusters of kCoopMin+1 .. kWindowMin members (whole-wave rows only): a single wave walking such a
   // cluster is bound by memory latency (one round of 8 rows per ~2 us), and when a few hundred of them hold
   // most of the assignments the kernel waits for them.  The four waves of the workgroup therefore share each
@@ -601,7 +605,7 @@ __global__ __launch_bounds__(256) void centroid_kernel(
 template <typename DT, int LPR>
 void launch_lpr(const void* tokens, const int32_t* perm, const int32_t* seg_offsets, const int32_t* seg_of,
                 const int32_t* num_segments, void* centroids, float* partial, uint32_t* counters, int64_t N, int k,
-                uint32_t cpr, bool mean, hipStream_t stream) {
+                uint32_t cpr, bool mean, bool all_offsets, hipStream_t stream) {
   constexpr int G = 64 / LPR;
   const uint64_t waves = ((uint64_t)N + G - 1) / G;  // worst case S == N; surplus waves leave at once
   const uint32_t blocks = (uint32_t)((waves + 3) / 4);
@@ -610,32 +614,37 @@ void launch_lpr(const void* tokens, const int32_t* perm, const int32_t* seg_offs
   constexpr size_t kCoopMore = 4 * Piece<DT>::kElems * sizeof(float) + 16;   // a piece more per row, the flag
   const dim3 grid = grid_of_blocks((uint64_t)blocks + (coop ? duty_workgroups((uint32_t)N) : 0u));
   hipLaunchKernelGGL((centroid_kernel<DT, LPR>), grid, dim3(256), coop ? coop_bytes + kCoopMore : 0, stream, (const char*)tokens,
-                     perm, seg_offsets, seg_of, num_segments, (char*)centroids, partial, counters, (uint32_t)N, (uint32_t)k,
-                     cpr, mean ? 1u : 0u, coop ? 1u : 0u);
+                     perm, seg_offsets, seg_of, num_segments, (char*)centroids, partial, counters, all_offsets ? (uint32_t)N : 0u,
+                     (uint32_t)N, (uint32_t)k, cpr, mean ? 1u : 0u, coop ? 1u : 0u);
 }
 
 template <typename DT>
 void launch_typed(const void* tokens, const int32_t* perm, const int32_t* seg_offsets, const int32_t* seg_of,
                   const int32_t* num_segments, void* centroids, float* partial, uint32_t* counters, int64_t N, int k,
-                  uint32_t cpr, bool mean, hipStream_t stream) {
+                  uint32_t cpr, bool mean, bool all_offsets, hipStream_t stream) {
   if (cpr > 16)
-    launch_lpr<DT, 64>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, stream);
+    launch_lpr<DT, 64>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, all_offsets,
+                       stream);
   else if (cpr > 4)
-    launch_lpr<DT, 16>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, stream);
+    launch_lpr<DT, 16>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, all_offsets,
+                       stream);
   else
-    launch_lpr<DT, 4>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, stream);
+    launch_lpr<DT, 4>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, all_offsets,
+                      stream);
 }
 
 }  // namespace
 
 hipError_t launch_centroid(const void* tokens, const int32_t* perm, const int32_t* seg_offsets, const int32_t* seg_of,
                            const int32_t* num_segments, void* centroids, float* partial, uint32_t* counters, int64_t N,
-                           int k, int d, bool bf16, bool mean, hipStream_t stream) {
+                           int k, int d, bool bf16, bool mean, bool all_offsets, hipStream_t stream) {
   const uint32_t cpr = (uint32_t)((size_t)d * (bf16 ? 2 : 4) / 16);
   if (bf16)
-    launch_typed<BF16>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, stream);
+    launch_typed<BF16>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, all_offsets,
+                       stream);
   else
-    launch_typed<F32>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, stream);
+    launch_typed<F32>(tokens, perm, seg_offsets, seg_of, num_segments, centroids, partial, counters, N, k, cpr, mean, all_offsets,
+                      stream);
   return hipGetLastError();
 }
 

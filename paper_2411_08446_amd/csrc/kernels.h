@@ -63,10 +63,10 @@ hipError_t launch_group(const GroupPlan& plan, const int32_t* expert, const uint
 // ---- step 3: centroid ---------------------------------------------------
 // Row of sorted position p is rows[perm[p] / k].  mean: divide each cluster's sum by its member count.
 // partial: 2 * ceil(N / kCentroidWindow) rows of d binary32 sums; counters: as many counts, zero on entry
-// (launch_group clears them).
+// (launch_group clears them).  all_offsets: seg_offsets has N + 1 entries that may be read; otherwise it may end at entry S.
 hipError_t launch_centroid(const void* rows, const int32_t* perm, const int32_t* seg_offsets, const int32_t* seg_of,
                            const int32_t* num_segments, void* centroids, float* partial, uint32_t* counters, int64_t N,
-                           int k, int d, bool bf16, bool mean, hipStream_t stream);
+                           int k, int d, bool bf16, bool mean, bool all_offsets, hipStream_t stream);
 
 // ---- step 4: restore ----------------------------------------------------
 // perm and num_segments (both optional): allow the kernel to walk the rows in cluster order when clusters are long.

@@ -473,6 +473,18 @@ def test_backward_long_clusters(H, dtype):
 
 # ------------------------------------------------------------------ hash fused with the gate projection
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("T,d,centers", [(3001, 136, 200), (3001, 136, None), (2500, 40, 300), (1200, 8192, 40), (1, 136, None)])
+def test_backward_with_offsets_that_end_at_the_last_cluster(H, dtype, T, d, centers):
+    # seg_offsets of S + 1 entries, as a program keeps it between the passes; what lies behind them is not an offset
+    tokens, rot, expert = _rand_inputs(29, T, d, 1, 1, 2, 16, dtype, centers=centers, sigma=0.01)
+    run = H.run_and_check(tokens, rot, expert, 1, dtype, _scale_fn)
+    room = torch.full((T + 1,), 0x7f7f7f7f, dtype=torch.int32, device="cuda")
+    room[:run.S + 1] = run.out.seg_offsets[:run.S + 1]
+    run.out.seg_offsets = room[:run.S + 1]
+    H.check_backward(run, T, d, 1, dtype, seed=30)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
 @pytest.mark.parametrize("T,L,r,E", [(32768 + 9, 3, 32, 32),    # GPT shape: 96 + 32 rows, one pass, 128-token workgroups
                                      (16384 + 3, 2, 32, 16),    # RoBERTa shape: 64-token workgroups
                                      (9000, 1, 8, 5),           # E not a multiple of 4, a single tile
