@@ -167,6 +167,7 @@ __device__ __forceinline__ void long_cluster_window(
   if (lane == 0) old = atomicAdd(&counters[first_slot], 1u);
   old = __builtin_amdgcn_readfirstlane(old);
   if (old != m1 - m0) return;
+  asm volatile("" ::: "memory");   // the loads of the other windows' rows stay behind the counter (no barrier here does that)
   const uint32_t nwin = m1 - m0 + 1;
   const bool whole0 = (uint32_t)lo % kCentroidWindow == 0, whole1 = (uint32_t)hi % kCentroidWindow == 0;
   const float fn = (float)(hi - lo), inv = 1.0f / fn;
