@@ -116,7 +116,7 @@ __global__ __launch_bounds__(256) void grad_tokens_kernel(
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t wave64 = linear_block() * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (LPR == 64) {
-    if (plan.stretches != 0 && large_clusters(seg_of, T * k, plan.percent)) {   // the same for every workgroup
+    if (plan.stretches != 0 && large_clusters(seg_of, T, k, plan.percent)) {   // the same for every workgroup
       __shared__ int2 look[kStretchTokens * kStretchExperts];
       grad_stretch<DT>(grad_out, grad_centroids, grad_expert_out, seg_of, seg_offsets, grad_tokens, k, (size_t)cpr * 16,
                        (flags & 1u) != 0, stretch_duty(plan, linear_block(), T), look);
