@@ -367,11 +367,12 @@ __device__ __forceinline__ void long_cluster_wg_window(
   __syncthreads();  // before the LDS rows are used again
 }
 
-template <typename DT, int LPR>
+// ALL: seg_offsets has N + 1 entries that may be read; otherwise it may end at entry S.
+template <typename DT, int LPR, bool ALL>
 __global__ __launch_bounds__(256) void centroid_kernel(
     const char* __restrict__ tokens, const int32_t* __restrict__ perm, const int32_t* __restrict__ seg_offsets,
     const int32_t* __restrict__ seg_of, const int32_t* __restrict__ num_segments, char* __restrict__ centroids,
-    float* partial, uint32_t* counters, uint32_t early, uint32_t N, uint32_t k, uint32_t cpr, uint32_t mean, uint32_t coop) {
+    float* partial, uint32_t* counters, uint32_t N, uint32_t k, uint32_t cpr, uint32_t mean, uint32_t coop) {
   constexpr int G = 64 / LPR;  // clusters handled side by side by one wave
   constexpr int E = Piece<DT>::kElems;
   // coop: [4 waves][cpr * E] partial sums of a cluster the workgroup shares, or [4 waves][(cpr + 1) * E] and a flag
@@ -387,18 +388,16 @@ __global__ __launch_bounds__(256) void centroid_kernel(
   const uint32_t wave = block * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const uint32_t s = wave * G + lane / LPR;
   const size_t row_bytes = (size_t)cpr * 16;
-  // Whole-wave rows: the offsets of the workgroup's four clusters, in lanes 0 to 4.  Where the array has N + 1 entries (early:
-  // the highest one, N) they are asked for together with the number of clusters; those behind the last cluster mean nothing
-  // and are not used.  One after the other, and a wave's own offsets once more behind them, these loads were two of the five
-  // trips to memory of a one-member cluster's wave.  Where the array may end at entry S (early: 0) they wait for S.
+  // Whole-wave rows: the offsets of the workgroup's four clusters, in lanes 0 to 4, with ALL asked for together with the number
+  // of clusters (those behind the last cluster mean nothing and are not used).  One after the other, and a wave's own offsets
+  // once more behind them, these loads were two of the five trips to memory of a one-member cluster's wave.
   int32_t offsets = 0;
-  const uint32_t entry = block * 4u + min(lane, 4u);
-  if constexpr (LPR == 64) {
-    if (!on_duty && early != 0) offsets = seg_offsets[min(entry, early)];
+  if constexpr (LPR == 64 && ALL) {
+    if (!on_duty) offsets = seg_offsets[min(block * 4u + min(lane, 4u), N)];
   }
   const uint32_t S = (uint32_t)*num_segments;
-  if constexpr (LPR == 64) {
-    if (!on_duty && early == 0) offsets = seg_offsets[min(entry, S)];
+  if constexpr (LPR == 64 && !ALL) {
+    if (!on_duty) offsets = seg_offsets[min(block * 4u + min(lane, 4u), S)];
   }
   // Clusters of kCoopMin+1 .. kWindowMin members (whole-wave rows only): a single wave walking such a
   // cluster is bound by memory latency (one round of 8 rows per ~2 us), and when a few hundred of them hold
@@ -614,9 +613,12 @@ void launch_lpr(const void* tokens, const int32_t* perm, const int32_t* seg_offs
   const bool coop = LPR == 64 && coop_bytes <= kCoopMaxLds;
   constexpr size_t kCoopMore = 4 * Piece<DT>::kElems * sizeof(float) + 16;   // a piece more per row, the flag
   const dim3 grid = grid_of_blocks((uint64_t)blocks + (coop ? duty_workgroups((uint32_t)N) : 0u));
-  hipLaunchKernelGGL((centroid_kernel<DT, LPR>), grid, dim3(256), coop ? coop_bytes + kCoopMore : 0, stream, (const char*)tokens,
-                     perm, seg_offsets, seg_of, num_segments, (char*)centroids, partial, counters, all_offsets ? (uint32_t)N : 0u,
-                     (uint32_t)N, (uint32_t)k, cpr, mean ? 1u : 0u, coop ? 1u : 0u);
+  // the instances differ for whole-wave rows only, and a choice inside the kernel costs the compress call: 65536 x 1024 bf16,
+  // 0.16 clusters per assignment, this kernel 53.7 -> 55.4 us
+  auto kern = all_offsets || LPR != 64 ? centroid_kernel<DT, LPR, true> : centroid_kernel<DT, LPR, LPR != 64>;
+  hipLaunchKernelGGL(kern, grid, dim3(256), coop ? coop_bytes + kCoopMore : 0, stream, (const char*)tokens, perm, seg_offsets,
+                     seg_of, num_segments, (char*)centroids, partial, counters, (uint32_t)N, (uint32_t)k, cpr, mean ? 1u : 0u,
+                     coop ? 1u : 0u);
 }
 
 template <typename DT>
