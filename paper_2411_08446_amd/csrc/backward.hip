@@ -96,15 +96,6 @@ __device__ __forceinline__ void grad_stretch(const char* __restrict__ grad_out, 
   }
 }
 
-// By columns from 64 MB of gradient rows on, of binary32 from 128 MB and two experts.  Measured with 10, 20, 30 per cent of
-// clusters per assignment, us: 16384 x 1024 bf16, two experts 30.8 -> 28.7, 33.1 -> 29.3, 33.7 -> 29.8; 65536 of them 128 -> 107,
-// 131 -> 119, 130 -> 126; one expert 71.4 -> 65.5, 73.6 -> 67.7, 73.4 -> 69.6; 8192, two experts 14.6 -> 15.4, 16.4 -> 15.8; binary32
-// 32768 x 1024, two experts 128 -> 110, 130 -> 122, 130 -> 134; one 71.1 -> 73.9; 8192, two 29.5 -> 30.8.
-StretchPlan plan_grad_tokens(int64_t T, int k, uint32_t cpr, bool bf16) {
-  const bool many = (uint64_t)T * k * cpr * 16 >= (bf16 ? 64ull : 128ull) << 20 && (bf16 || k > 1);
-  return many ? plan_stretches(T, k, cpr, bf16 ? 25 : 20) : StretchPlan{};
-}
-
 template <typename DT, int LPR, bool STREAM>
 __global__ __launch_bounds__(256) void grad_tokens_kernel(
     const char* __restrict__ grad_out, const char* __restrict__ grad_centroids,
@@ -116,7 +107,7 @@ __global__ __launch_bounds__(256) void grad_tokens_kernel(
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t wave64 = linear_block() * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (LPR == 64) {
-    if (plan.stretches != 0 && large_clusters(seg_of, T, k, plan.percent)) {   // the same for every workgroup
+    if (plan.stretches != 0 && pays(plan, estimate_clusters(seg_of, T, k))) {   // the same for every workgroup
       __shared__ int2 look[kStretchTokens * kStretchExperts];
       grad_stretch<DT>(grad_out, grad_centroids, grad_expert_out, seg_of, seg_offsets, grad_tokens, k, (size_t)cpr * 16,
                        (flags & 1u) != 0, stretch_duty(plan, linear_block(), T), look);

@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void restore_kernel(
   // variant and the token-gradient kernel, which have one more lookup per row, gain from the scalar form).
   const uint64_t block64 = linear_block();
   if constexpr (LPR == 64) {
-    if (plan.stretches != 0 && (uint64_t)(uint32_t)*num_segments * 100 < (uint64_t)N * plan.percent) {
+    if (plan.stretches != 0 && pays(plan, (uint32_t)*num_segments)) {
       __shared__ uint32_t look[kStretchTokens * kStretchExperts];
       restore_stretch<DT>(tokens, centroids, expert_out, seg_of, seg_offsets, out, k, (size_t)cpr * 16, (flags & 1u) != 0,
                           stretch_duty(plan, block64, N / k), look);
@@ -246,15 +246,6 @@ __device__ __forceinline__ void combine_stretch(const char* __restrict__ tokens,
   }
 }
 
-// By columns from rows of 8 MB in all on.  Measured with 10, 20, 30, 40 per cent of clusters per assignment, us: 4096 x 1024
-// bf16, two experts 8.8 -> 6.5, 9.0 -> 6.3, 9.0 -> 6.7, 9.1 -> 7.1; 32768 of them 53.6 -> 39.9, 56.1 -> 44.8, 57.0 -> 47.6,
-// 56.9 -> 50.6; 65536 109 -> 84, 112 -> 99, 111 -> 107, 111 -> 110; one expert 75.6 -> 59.3 .. 76.3 -> 71.1.  Rows of binary32
-// are twice as wide for the same L2: 32768 x 1024, two experts 110 -> 82, 114 -> 103, 114 -> 114, 114 -> 119; 8192, one
-// expert 18.2 -> 18.1, 19.5 -> 20.1.
-StretchPlan plan_combine(int64_t T, int k, uint32_t cpr, bool bf16) {
-  return (uint64_t)T * cpr * 16 >= 8ull << 20 ? plan_stretches(T, k, cpr, bf16 ? 25 : 15) : StretchPlan{};
-}
-
 template <typename DT, int LPR>
 __global__ __launch_bounds__(256) void restore_combine_kernel(
     const char* __restrict__ tokens, const char* __restrict__ centroids, const char* __restrict__ expert_out,
@@ -265,7 +256,7 @@ __global__ __launch_bounds__(256) void restore_combine_kernel(
   const uint32_t lane = threadIdx.x & 63;
   const uint64_t wave64 = linear_block() * 4u + (uint32_t)__builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   if constexpr (LPR == 64) {
-    if (plan.stretches != 0 && large_clusters(seg_of, T, k, plan.percent)) {   // the same for every workgroup
+    if (plan.stretches != 0 && pays(plan, estimate_clusters(seg_of, T, k))) {   // the same for every workgroup
       __shared__ uint2 look[kStretchTokens * kStretchExperts];
       combine_stretch<DT>(tokens, centroids, expert_out, seg_of, seg_offsets, gate_weight, out, k, (size_t)cpr * 16,
                           (flags & 1u) != 0, stretch_duty(plan, linear_block(), T), look);
@@ -343,7 +334,7 @@ void launch_combine_typed(const void* tokens, const void* centroids, const void*
 StretchPlan plan_restore(int64_t N, int k, uint32_t cpr) {
   const uint64_t bytes = (uint64_t)N * cpr * 16;
   return cpr == 8 * kStretchPieces && k > 1 && bytes >= 64ull << 20 && bytes <= 128ull << 20
-             ? plan_stretches(N / k, k, cpr, 15) : StretchPlan{};
+             ? plan_stretches(N / k, k, cpr, 0, N * 15 / 100) : StretchPlan{};
 }
 
 template <typename DT, int LPR>

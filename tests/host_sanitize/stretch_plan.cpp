@@ -15,6 +15,9 @@ static void expect(bool ok, const char* what, long long T, int k, int more) {
   if (!ok && ++failures <= 20) printf("FAIL %s T=%lld k=%d %d\n", what, T, k, more);
 }
 
+// Whether a number of clusters is more than a quarter of the assignments.
+static bool small(uint32_t clusters, uint32_t T, uint32_t k) { return (uint64_t)clusters * 4 > (uint64_t)T * k; }
+
 // Cluster numbers of T tokens with k experts each: alone, every assignment has a cluster of its own, and the assignments that
 // `shared` names are all in a few clusters that come first.
 template <typename F>
@@ -33,15 +36,15 @@ static void check_estimate() {
     for (uint32_t k = 1; k <= kStretchExperts; ++k) {
       for (uint32_t seq : {64u, 128u, 512u, 1000u, 1024u, 2048u, 4096u}) {
         std::vector<int32_t> seg = mostly_alone(T, k, [&](uint32_t t, uint32_t) { return t % seq == 0; });
-        expect(!large_clusters(seg.data(), T, k, 25), "sequences that begin alike", T, (int)k, (int)seq);
+        expect(small(estimate_clusters(seg.data(), T, k), T, k), "sequences that begin alike", T, (int)k, (int)seq);
         seg = mostly_alone(T, k, [&](uint32_t t, uint32_t) { return t % seq < seq / 4; });
-        expect(!large_clusters(seg.data(), T, k, 25), "a quarter of padding in front", T, (int)k, (int)seq);
+        expect(small(estimate_clusters(seg.data(), T, k), T, k), "a quarter of padding in front", T, (int)k, (int)seq);
         seg = mostly_alone(T, k, [&](uint32_t t, uint32_t) { return t % seq >= seq - seq / 4; });
-        expect(!large_clusters(seg.data(), T, k, 25), "a quarter of padding behind", T, (int)k, (int)seq);
+        expect(small(estimate_clusters(seg.data(), T, k), T, k), "a quarter of padding behind", T, (int)k, (int)seq);
       }
       for (uint32_t one = 0; one < k && k > 1; ++one) {
         const std::vector<int32_t> seg = mostly_alone(T, k, [&](uint32_t, uint32_t j) { return j == one; });
-        expect(!large_clusters(seg.data(), T, k, 25), "one expert of a token shared by all", T, (int)k, (int)one);
+        expect(small(estimate_clusters(seg.data(), T, k), T, k), "one expert of a token shared by all", T, (int)k, (int)one);
       }
       for (int percent : {1, 10, 90}) {                        // clusters drawn uniformly: estimated from below, by about a ninth
         std::vector<int32_t> seg((size_t)T * k);
@@ -50,7 +53,7 @@ static void check_estimate() {
           x ^= x << 13; x ^= x >> 7; x ^= x << 17;
           s = (int32_t)(x % ((uint64_t)T * k * percent / 100));
         }
-        expect(large_clusters(seg.data(), T, k, 25) == (percent < 25), "uniform clusters", T, (int)k, percent);
+        expect(small(estimate_clusters(seg.data(), T, k), T, k) == (percent > 25), "uniform clusters", T, (int)k, percent);
       }
       for (uint32_t i = 0; i < 8; ++i) expect(sample_place(i, T, k) < T * k, "place", T, (int)k, (int)i);
     }
@@ -59,8 +62,83 @@ static void check_estimate() {
     for (uint32_t i = 0; i < 8; ++i) expect(sample_place(i, T, 1) < T, "place", T, 1, (int)i);
 }
 
+// Every stretch of every token is somebody's, once, for any grid that has enough workgroups.
+static void check_duties() {
+  for (uint32_t cpr : {64u, 128u, 192u, 256u, 320u, 512u}) {
+    for (uint32_t T : {1u, 2u, 31u, 33u, 4096u, 8192u + 13u, 30001u}) {
+      const StretchPlan p = plan_stretches(T, 2, cpr, 0, 1);
+      std::vector<uint8_t> done((size_t)T * p.stretches);
+      for (uint64_t block = 0; block < p.workgroups() + 5000; ++block) {
+        const StretchDuty d = stretch_duty(p, block, T);
+        for (uint32_t t = d.first; t < d.end; ++t)
+          if (d.at % (kStretchPieces * 16) == 0 && d.at < cpr * 16 && t < T) ++done[(size_t)t * p.stretches + d.at / (kStretchPieces * 16)];
+      }
+      bool ok = p.stretches * kStretchPieces == cpr;
+      for (uint8_t n : done) ok = ok && n == 1;
+      expect(ok, "duties", T, 2, (int)cpr);
+    }
+  }
+  const uint32_t T = (1u << 27) + 6;                           // a grid of many rows of workgroups
+  const StretchPlan p = plan_stretches(T, 1, 64, 0, 1);
+  uint64_t done = 0, last = 0;
+  for (uint64_t block = 0; block < p.workgroups(); ++block) {
+    const StretchDuty d = stretch_duty(p, block, T);
+    if (d.first < d.end) { done += d.end - d.first; if (d.end > last) last = d.end; }
+  }
+  expect(done == (uint64_t)T * p.stretches && last == T, "duties", T, 1, 64);
+}
+
+// Which calls go by columns.
+static void check_rules() {
+  const auto share = [](uint64_t T, uint64_t k, uint64_t percent) { return (uint32_t)(T * k * percent / 100); };
+  struct { uint32_t T; int k; uint32_t cpr; bool bf16; int percent; bool combine, gradient; } cases[] = {
+      {65536, 2, 128, true, 16, true, true},       // 2 KB rows, the method's rates
+      {65536, 2, 128, true, 90, false, false},     // small clusters
+      {32768, 2, 128, true, 1, false, false},      // cluster rows that an L2 holds
+      {32768, 2, 128, true, 3, true, false},       // as they are; the token gradient passes more through it
+      {32768, 1, 128, true, 12, true, true},
+      {4096, 2, 128, true, 16, true, false},       // 16 MB of gradient rows
+      {4095, 2, 128, true, 16, false, false},      // below 8 MB of tokens
+      {262144, 2, 128, true, 10, true, true},
+      {262144, 2, 128, true, 14, false, false},    // more clusters than an L2 has lines in use
+      {65536, 2, 64, true, 20, true, true},
+      {131072, 2, 64, true, 14, false, false},
+      {131072, 1, 64, true, 11, true, false},      // 1 KB rows, one expert
+      {131072, 1, 64, true, 14, false, false},
+      {32768, 2, 192, true, 16, true, true},
+      {16384, 2, 256, true, 16, true, false},      // 4 KB rows
+      {16384, 1, 256, true, 16, false, false},
+      {16384, 4, 512, true, 16, true, false},
+      {32768, 2, 256, false, 12, true, false},     // binary32
+      {32768, 2, 256, false, 16, false, false},
+      {65536, 2, 128, false, 14, true, true},
+      {65536, 2, 128, false, 18, false, true},
+      {65536, 1, 128, false, 14, true, false},
+      {65536, 5, 128, true, 10, false, false},     // more experts than the lookups have room for
+      {65536, 2, 96, true, 16, false, false},      // rows of six stretches
+      // the shapes of tests/test_gpu_stretch.py: restore + combine
+      {8192 + 13, 1, 64, true, 20, false, false}, {16384 + 13, 1, 64, true, 14, true, false}, {4096, 2, 128, true, 14, true, false},
+      {8192 + 1, 3, 128, true, 10, true, false}, {4096 + 31, 2, 192, true, 10, true, false}, {4096 + 33, 4, 256, true, 10, true, false},
+      {8192 + 7, 2, 64, false, 14, true, false}, {4096 + 65, 1, 256, false, 10, false, false}, {4096 + 65, 2, 256, false, 10, true, false},
+      {4096 + 5, 5, 128, true, 10, false, false}, {8192 + 3, 2, 96, true, 10, false, false},
+      // token gradient
+      {32768 + 13, 2, 64, true, 12, true, true}, {32768 + 1, 1, 128, true, 12, true, true}, {16384 + 31, 2, 128, true, 12, true, true},
+      {8192 + 7, 3, 192, true, 12, true, true}, {16384 + 33, 2, 256, false, 12, true, false}, {4096 + 5, 4, 256, true, 12, true, false},
+      {8192 + 3, 5, 128, true, 12, false, false}, {32768 + 3, 1, 256, false, 12, false, false}, {32768 + 33, 2, 128, false, 12, true, true},
+  };
+  int i = 0;
+  for (const auto& c : cases) {
+    const uint32_t S = share(c.T, c.k, c.percent);
+    expect(pays(plan_combine(c.T, c.k, c.cpr, c.bf16), S) == c.combine, "restore + combine", c.T, c.k, i);
+    expect(pays(plan_grad_tokens(c.T, c.k, c.cpr, c.bf16), S) == c.gradient, "token gradient", c.T, c.k, i);
+    ++i;
+  }
+}
+
 int main() {
   check_estimate();
+  check_duties();
+  check_rules();
   printf("%d checks, %d failures\n", checks, failures);
   return failures ? 1 : 0;
 }

@@ -14,7 +14,12 @@ DTYPES = {"bf16": torch.bfloat16, "f32": torch.float32}
 def _clusters(T, k, share, gen):
     """Random clusters of N = T k assignments, every one with members: seg_of and seg_offsets, whose rest is garbage."""
     N = T * k
-    seg = torch.randint(max(1, int(N * share)), (N,), device="cuda", generator=gen)
+    if isinstance(share, tuple):                         # so many alone, the rest in six large clusters that come last
+        alone = int(N * share[0])
+        seg = torch.cat([torch.arange(alone, device="cuda"), alone + torch.randint(6, (N - alone,), device="cuda", generator=gen)])
+        seg = seg[torch.randperm(N, device="cuda", generator=gen)]
+    else:
+        seg = torch.randint(max(1, int(N * share)), (N,), device="cuda", generator=gen)
     _, seg = torch.unique(seg, return_inverse=True)
     size = torch.bincount(seg)
     off = torch.full((N + 1,), 0x7f7f7f7f, dtype=torch.int32, device="cuda")
@@ -27,11 +32,11 @@ def _rows(n, d, dt, gen):
     return torch.randn(n, d, device="cuda", generator=gen).to(dt)
 
 
-# rows of four, eight, twelve and sixteen stretches; tokens off the grid of a workgroup, of a part and of a lane group;
-# the last two shapes go the way of the parts in any case (five experts; rows of six stretches)
+# rows of four, eight, twelve and sixteen stretches; tokens off the grid of a workgroup, of a part and of a lane group.  Which
+# of them go by columns: tests/host_sanitize/stretch_plan.cpp
 SHAPES = [("bf16", 512, 8192 + 13, 1), ("bf16", 1024, 4096, 2), ("bf16", 1024, 8192 + 1, 3), ("bf16", 1536, 4096 + 31, 2),
           ("bf16", 2048, 4096 + 33, 4), ("f32", 256, 8192 + 7, 2), ("f32", 1024, 4096 + 65, 1), ("bf16", 1024, 4096 + 5, 5),
-          ("bf16", 768, 8192 + 3, 2)]
+          ("bf16", 768, 8192 + 3, 2), ("bf16", 512, 16384 + 13, 1), ("f32", 1024, 4096 + 65, 2)]
 
 
 @pytest.mark.parametrize("flags", [0, 1])
@@ -40,7 +45,8 @@ def test_combine_by_columns(dtype, d, T, k, flags):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(T + d + k)
     dt = DTYPES[dtype]
-    for share, with_offsets in ((0.002, True), (0.1, True), (0.1, False), (0.9, True)):
+    for share, with_offsets in ((0.002, True), (0.1, True), (0.1, False), (0.9, True), (0.14, True), (0.14, False), (0.2, True),
+                                ((0.14,), True), ((0.14,), False)):
         print("case combine", dtype, d, T, k, flags, share, with_offsets, flush=True)
         seg, off, size = _clusters(T, k, share, gen)
         S = size.numel()
@@ -65,7 +71,7 @@ def test_combine_by_columns(dtype, d, T, k, flags):
 
 
 GRAD_SHAPES = [("bf16", 512, 32768 + 13, 2), ("bf16", 1024, 32768 + 1, 1), ("bf16", 1024, 16384 + 31, 2), ("bf16", 1536, 8192 + 7, 3),
-               ("f32", 1024, 16384 + 33, 2), ("bf16", 2048, 4096 + 5, 4), ("bf16", 1024, 8192 + 3, 5), ("f32", 1024, 32768 + 3, 1)]
+               ("f32", 1024, 16384 + 33, 2), ("bf16", 2048, 4096 + 5, 4), ("bf16", 1024, 8192 + 3, 5), ("f32", 1024, 32768 + 3, 1), ("f32", 512, 32768 + 33, 2)]
 
 
 @pytest.mark.parametrize("flags", [0, 1])
@@ -74,7 +80,7 @@ def test_token_gradient_by_columns(dtype, d, T, k, flags):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(T + d + k)
     dt = DTYPES[dtype]
-    for share in (0.002, 0.12, 0.9):
+    for share in (0.002, 0.12, 0.9, (0.14,)):
         print("case gradient", dtype, d, T, k, flags, share, flush=True)
         seg, off, size = _clusters(T, k, share, gen)
         S = size.numel()
