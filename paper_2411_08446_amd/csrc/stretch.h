@@ -51,20 +51,28 @@ constexpr uint64_t kXcdL2 = 4ull << 20;
 //    Rows that are not eight or twelve stretches bear half of that: 131072 x 512, 31 thousand 107.5 -> 106.1, 52 109.4 ->
 //    111.5; 131072 x 2048, 31 433 -> 391, 52 445 -> 453; and of four with one expert a quarter: 131072 x 512, 16 76.3 -> 75.4,
 //    26 76.9 -> 78.5.
-inline uint64_t most_clusters(int k, uint32_t cpr) {
-  if (cpr == 8 * kStretchPieces || cpr == 12 * kStretchPieces) return 65536;
-  return cpr == 4 * kStretchPieces && k == 1 ? 16384 : 32768;
+//  * To ask costs 0.4 us of a call that then goes the way round, and more where a wave has little else to do: restore + combine,
+//    0.4 clusters per assignment, 65536 x 1024, two experts 107.8 -> 107.9; 16384 x 512, one expert 10.0 -> 10.7, 131072 of them
+//    75.4 -> 77.9, 524288 x 256 binary32 306 -> 316.  So it is asked only where the bound on the clusters leaves a tenth of the
+//    assignments, with rows of 1 KB the whole share for which columns pay.
+inline uint64_t fewer_clusters_than(uint64_t N, int k, uint32_t cpr, uint64_t percent) {
+  const bool narrow = cpr == 4 * kStretchPieces, eight_or_twelve = cpr == 8 * kStretchPieces || cpr == 12 * kStretchPieces;
+  const uint64_t most = eight_or_twelve ? 65536 : narrow && k == 1 ? 16384 : 32768;
+  if (most * 100 < N * (narrow ? percent : 10)) return 0;
+  return at_most(N * percent / 100, most);
 }
 
 // Restore + combine: from rows of 8 MB in all on.  Measured with 10, 20, 30, 40 per cent of clusters per assignment, us: 4096 x
 // 1024 bf16, two experts 8.8 -> 6.5, 9.0 -> 6.3, 9.0 -> 6.7, 9.1 -> 7.1; 32768 of them 53.6 -> 39.9, 56.1 -> 44.8, 57.0 -> 47.6,
 // 56.9 -> 50.6; 65536 109 -> 84, 112 -> 99, 111 -> 107, 111 -> 110; one expert 75.6 -> 59.3 .. 76.3 -> 71.1.  Rows of binary32
 // are twice as wide for the same L2: 32768 x 1024, two experts 110 -> 82, 114 -> 103, 114 -> 114, 114 -> 119.  One expert and rows
-// of 4 KB and more lose (a row takes two turns of the XCDs): 8192, 32768, 65536 x 2048, 0.05: 15.6 -> 17.9, 67 -> 72, 142 -> 142.
+// of 4 KB and more lose (a row takes two turns of the XCDs): 8192, 32768, 65536 x 2048, 0.05: 15.6 -> 17.9, 67 -> 72, 142 -> 142;
+// and so do rows of 1 KB of binary32, for which there is less to gain: 65536 x 256, 0.05 to 0.2: 1.04, 0.99, 0.96 times as fast.
 inline StretchPlan plan_combine(int64_t T, int k, uint32_t cpr, bool bf16) {
   const uint64_t row = cpr * 16ull, N = (uint64_t)T * k;
-  if (T * row < 8ull << 20 || (k == 1 && cpr > 12 * kStretchPieces)) return StretchPlan{};
-  return plan_stretches(T, k, cpr, kXcdL2 / (2 * row), at_most(N * (bf16 ? 25 : 15) / 100, most_clusters(k, cpr)));
+  if (T * row < 8ull << 20) return StretchPlan{};
+  if (k == 1 && (cpr > 12 * kStretchPieces || (!bf16 && cpr < 8 * kStretchPieces))) return StretchPlan{};
+  return plan_stretches(T, k, cpr, kXcdL2 / (2 * row), fewer_clusters_than(N, k, cpr, bf16 ? 25 : 15));
 }
 
 // Token gradient: from 64 MB of gradient rows on, of binary32 from 128 MB and two experts.  Measured with 10, 20, 30 per cent of
@@ -77,7 +85,7 @@ inline StretchPlan plan_grad_tokens(int64_t T, int k, uint32_t cpr, bool bf16) {
   const uint64_t row = cpr * 16ull, N = (uint64_t)T * k;
   if (N * row < (bf16 ? 64ull : 128ull) << 20 || cpr > 12 * kStretchPieces) return StretchPlan{};
   if (k == 1 && (!bf16 || cpr < 8 * kStretchPieces)) return StretchPlan{};
-  return plan_stretches(T, k, cpr, 2 * kXcdL2 / (2 * row), at_most(N * (bf16 ? 25 : 20) / 100, most_clusters(k, cpr)));
+  return plan_stretches(T, k, cpr, 2 * kXcdL2 / (2 * row), fewer_clusters_than(N, k, cpr, bf16 ? 25 : 20));
 }
 
 // What a workgroup does: the stretch `at` bytes from a row's start of tokens first .. end - 1 (none, if first >= end).

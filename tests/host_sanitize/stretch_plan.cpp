@@ -101,10 +101,13 @@ static void check_rules() {
       {4095, 2, 128, true, 16, false, false},      // below 8 MB of tokens
       {262144, 2, 128, true, 10, true, true},
       {262144, 2, 128, true, 14, false, false},    // more clusters than an L2 has lines in use
-      {65536, 2, 64, true, 20, true, true},
-      {131072, 2, 64, true, 14, false, false},
-      {131072, 1, 64, true, 11, true, false},      // 1 KB rows, one expert
-      {131072, 1, 64, true, 14, false, false},
+      {65536, 2, 64, true, 20, true, true},        // 1 KB rows
+      {65537, 2, 64, true, 20, false, false},
+      {65536, 1, 64, true, 20, true, false},       // one expert
+      {65537, 1, 64, true, 20, false, false},
+      {32768, 1, 64, false, 13, false, false},
+      {327680, 2, 128, true, 9, true, true},       // the bound on the clusters leaves a tenth
+      {327681, 2, 128, true, 9, false, false},
       {32768, 2, 192, true, 16, true, true},
       {16384, 2, 256, true, 16, true, false},      // 4 KB rows
       {16384, 1, 256, true, 16, false, false},
