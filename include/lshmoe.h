@@ -254,10 +254,12 @@ lshmoe_status lshmoe_compress_static(const void* tokens, const int32_t* expert, 
  *                            exactly zero); the result is the same either way.
  *   perm [N], num_segments [1]  in  int32 or both NULL, as written by lshmoe_compress.
  *                            When given and the clusters are long on average
- *                            (S / N < 0.65), the rows are produced in cluster order,
- *                            which fetches every cluster's expert-output and centroid
- *                            row once instead of once per member; the result is the
- *                            same either way.
+ *                            (S / N < 0.65), the rows are produced in an order that
+ *                            fetches every cluster's expert-output and centroid row
+ *                            once instead of once per member: in cluster order, or,
+ *                            for some sizes and large clusters, in assignment order a
+ *                            part of the columns at a time (perm is not read then).
+ *                            The result is the same either way.
  *   out         [T, k, d] out dtype, assignment order
  *
  * Errors: NULL pointer (seg_offsets excepted; perm and num_segments both or neither); T, d, k <= 0; N >= 2^30

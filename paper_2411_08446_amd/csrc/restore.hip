@@ -325,18 +325,6 @@ void launch_combine_typed(const void* tokens, const void* centroids, const void*
     launch_combine_lpr<DT, 4>(tokens, centroids, expert_out, seg_of, seg_offsets, gate_weight, out, T, k, cpr, flags, stream);
 }
 
-// By columns, in assignment order, when clusters are large and the output, which is written in pieces of 256 bytes then, is
-// about half the last-level cache: whole steps of 32768 x 1024 bf16 and two experts with 0.145 clusters per assignment 117.8
-// -> 116.5 us, of 30000 with 0.07 108.8 -> 103.1, of 20000 x 512 binary32 with 0.06 97.6 -> 93.8.  Twice the rows: 207 -> 220 us
-// (cluster order writes whole rows); one expert per token, where cluster order reads a token's row once too: 16384 rows 15.1
-// -> 15.6, 15.7 -> 17.2 us for this kernel; 0.2 and 0.3 clusters per assignment, two experts, 32768 rows 54 -> 57, 58 -> 62; rows
-// of 1 KB or 4 KB 26.0 -> 28.3, 56 -> 61; fewer rows: the same within 1 per cent.
-StretchPlan plan_restore(int64_t N, int k, uint32_t cpr) {
-  const uint64_t bytes = (uint64_t)N * cpr * 16;
-  return cpr == 8 * kStretchPieces && k > 1 && bytes >= 64ull << 20 && bytes <= 128ull << 20
-             ? plan_stretches(N / k, k, cpr, 0, N * 15 / 100) : StretchPlan{};
-}
-
 template <typename DT, int LPR>
 void launch_lpr(const void* tokens, const void* centroids, const void* expert_out, const int32_t* seg_of,
                 const int32_t* seg_offsets, const int32_t* perm, const int32_t* num_segments, void* out, int64_t N,

@@ -75,6 +75,22 @@ inline StretchPlan plan_combine(int64_t T, int k, uint32_t cpr, bool bf16) {
   return plan_stretches(T, k, cpr, kXcdL2 / (2 * row), fewer_clusters_than(N, k, cpr, bf16 ? 25 : 15));
 }
 
+// Restore knows the number of clusters and has another way round: in cluster order it reads a cluster's rows once and a token's
+// once per expert, by columns the other way about, and writes the output in pieces of 256 bytes to all rows.  Measured as whole
+// steps, rows of 1 to 4 KB, 4 to 512 MB of output, two to four experts, 0.03 to 0.15 clusters per assignment (us: cluster
+// order -> columns).  It pays while all stretches of a row are dealt at the same time: 128 MB, two experts, 0.05, 0.07, 0.09,
+// 0.10, 0.14 clusters, 2 KB rows 115 -> 108, 111 -> 107, 112 -> 109, 112 -> 110, 106 -> 107; 1 KB 111 -> 106, 112 -> 107, 112 ->
+// 110, 112 -> 112, 113 -> 113; 3 KB, 0.03 and 0.09, 137 -> 139, 114 -> 122; 4 KB 153 -> 152, 118 -> 125.  And while the output stays
+// in the last-level cache of 256 MB, up to more clusters if it takes no more than half of it: 0.14, 24, 48, 64, 96, 128 MB 44.0 ->
+// 43.5, 58.3 -> 58.1, 65.9 -> 65.8, 87.3 -> 87.4, 108.3 -> 106.2 (10 hash functions 116.9 -> 115.4), with 0.2 three microseconds
+// more; 256 MB, 0.05, 0.07, 0.09, 0.11 196 -> 177, 197 -> 185, 191 -> 185, 190 -> 190; 512 MB 360 -> 359, 359 -> 371, 358 -> 381.
+// From 24 MB on: 24 MB, 0.03 and 0.09, 72.4 -> 70.5, 49.6 -> 48.6; 16 MB, 0.06 and 0.08, 55.3 -> 54.8, 45.4 -> 45.9.
+inline StretchPlan plan_restore(int64_t N, int k, uint32_t cpr) {
+  const uint64_t bytes = (uint64_t)N * cpr * 16;
+  if (k == 1 || cpr > kXcdCount * kStretchPieces || bytes < 24ull << 20 || bytes > 256ull << 20) return StretchPlan{};
+  return plan_stretches(N / k, k, cpr, 0, (uint64_t)N * (bytes <= 128ull << 20 ? 15 : 9) / 100);
+}
+
 // Token gradient: from 64 MB of gradient rows on, of binary32 from 128 MB and two experts.  Measured with 10, 20, 30 per cent of
 // clusters per assignment, us: 16384 x 1024 bf16, two experts 30.8 -> 28.7, 33.1 -> 29.3, 33.7 -> 29.8; 65536 of them 128 -> 107,
 // 131 -> 119, 130 -> 126; one expert 71.4 -> 65.5, 73.6 -> 67.7, 73.4 -> 69.6; 8192, two experts 14.6 -> 15.4, 16.4 -> 15.8; binary32

@@ -136,6 +136,24 @@ static void check_rules() {
     expect(pays(plan_grad_tokens(c.T, c.k, c.cpr, c.bf16), S) == c.gradient, "token gradient", c.T, c.k, i);
     ++i;
   }
+  struct { uint32_t T; int k; uint32_t cpr; int percent; bool restore; } restores[] = {
+      {32768, 2, 128, 14, true},     // 128 MB of output
+      {32768, 2, 128, 15, false},
+      {32768, 1, 128, 8, false},     // one expert
+      {32768, 5, 128, 8, false},
+      {16384, 2, 192, 8, false},     // rows wider than the XCDs take at once
+      {32768 + 1, 2, 128, 9, false},
+      {65536, 2, 128, 8, true},      // 256 MB
+      {65536 + 1, 2, 128, 8, false},
+      {6144, 2, 128, 8, true},       // 24 MB
+      {6144 - 1, 2, 128, 8, false},
+      {43690, 3, 64, 8, true},
+      // the shapes of tests/test_gpu_stretch.py
+      {16384, 2, 128, 6, true}, {16384 + 13, 3, 128, 6, true}, {8192 + 1, 4, 128, 6, true}, {12288 + 5, 2, 64, 6, true},
+      {16384, 2, 128, 10, true}, {65536 + 1, 2, 128, 6, false}, {12288 - 1, 2, 64, 6, false}, {8192 + 3, 2, 192, 6, false},
+  };
+  for (const auto& c : restores)
+    expect(pays(plan_restore((int64_t)c.T * c.k, c.k, c.cpr), share(c.T, c.k, c.percent)) == c.restore, "restore", c.T, c.k, (int)c.cpr);
 }
 
 int main() {

@@ -104,15 +104,17 @@ def test_token_gradient_by_columns(dtype, d, T, k, flags):
         assert float((got[t].double() - ref).abs().max()) <= tol * float(ref.abs().max())
 
 
-# 64 to 128 MB of output and two to four experts go by columns, the others do not
+# 24 to 256 MB of output in rows of 1 or 2 KB and two to four experts go by columns at the smaller shares, the others do not
 @pytest.mark.parametrize("flags", [0, 1])
 @pytest.mark.parametrize("dtype,d,T,k", [("bf16", 1024, 16384, 2), ("bf16", 1024, 32768, 2), ("bf16", 1024, 16384 + 13, 3),
-                                         ("f32", 512, 8192 + 1, 4), ("bf16", 1024, 16383, 2), ("bf16", 1024, 32769, 2)])
+                                         ("f32", 512, 8192 + 1, 4), ("bf16", 1024, 16383, 2), ("bf16", 1024, 32769, 2),
+                                         ("bf16", 512, 12288 + 5, 2), ("bf16", 512, 12288 - 1, 2), ("bf16", 1536, 8192 + 3, 2),
+                                         ("bf16", 1024, 65536 + 1, 2)])
 def test_restore_by_columns(dtype, d, T, k, flags):
     gen = torch.Generator(device="cuda")
     gen.manual_seed(T + d + k)
     dt = DTYPES[dtype]
-    for share, with_offsets in ((0.002, True), (0.1, True), (0.1, False), (0.3, True)):
+    for share, with_offsets in ((0.002, True), (0.1, True), (0.1, False), (0.3, True), (0.06, True), ((0.06,), True), ((0.06,), False)):
         print("case restore", dtype, d, T, k, flags, share, with_offsets, flush=True)
         seg, off, size = _clusters(T, k, share, gen)
         S = size.numel()
@@ -124,3 +126,11 @@ def test_restore_by_columns(dtype, d, T, k, flags):
         lsh.lshmoe_decompress(x, c, e, seg, given, k, got, flags, perm=perm, num_segments=count)
         lsh.lshmoe_decompress(x, c, e, seg, given, k, want, flags)      # without the count: assignment order, row by row
         assert torch.equal(got.view(torch.uint8), want.view(torch.uint8))
+        t = torch.randint(T, (32,), device="cuda", generator=gen)
+        s = seg.view(T, k)[t].long()
+        y = e[s].double()
+        if flags == 0:
+            res = x[t].double()[:, None] - c[s].double()
+            y = y + (torch.where((size[s] == 1)[..., None], 0.0, res) if with_offsets else res)
+        tol = 2.0 ** -7 if dtype == "bf16" else 1e-6    # one unit of the last place of bf16; two binary32 roundings
+        assert float((got[t].double() - y).abs().max()) <= tol * float(y.abs().max())
