@@ -167,7 +167,11 @@ __device__ __forceinline__ void long_cluster_window(
   if (lane == 0) old = atomicAdd(&counters[first_slot], 1u);
   old = __builtin_amdgcn_readfirstlane(old);
   if (old != m1 - m0) return;
-  asm volatile("" ::: "memory");   // the loads of the other windows' rows stay behind the counter (no barrier here does that)
+  // The last window of the cluster: every other partial row is in memory, and what this XCD's caches may hold of them from
+  // before is dropped once, so that they can be read as any other rows.  One wave reads them all, one pair behind the other, and
+  // with every load past the L2 that took longer than the fences had: segment sums, one cluster of 65536 rows of 128 bytes
+  // 236 -> 188 us, of 4608 bytes 1286 -> 968 (two fences per window 186, 970); 1024 x 256 of 256 bytes 38.3, 38.6 (86).
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
   const uint32_t nwin = m1 - m0 + 1;
   const bool whole0 = (uint32_t)lo % kCentroidWindow == 0, whole1 = (uint32_t)hi % kCentroidWindow == 0;
   const float fn = (float)(hi - lo), inv = 1.0f / fn;
@@ -180,7 +184,7 @@ __device__ __forceinline__ void long_cluster_window(
 #pragma unroll
       for (int end = 0; end < 2; ++end) {
         if (end == 0 ? whole0 : whole1) continue;
-        const uint2 w = load_shared8(dst + c * 16 + end * 8);
+        const uint2 w = *(const uint2*)(dst + c * 16 + end * 8);
         err[0] -= __uint_as_float(w.x << 16); err[1] -= __uint_as_float(w.x & 0xffff0000u);
         err[2] -= __uint_as_float(w.y << 16); err[3] -= __uint_as_float(w.y & 0xffff0000u);
       }
@@ -194,8 +198,8 @@ __device__ __forceinline__ void long_cluster_window(
         const bool whole_j = (jj != 0 || whole0) && (jj != nwin - 1 || whole1);
 #pragma unroll
         for (int i = 0; i < E; i += 4) {
-          const float4 v = load_shared_row(src + i);
-          const float4 w = whole_j ? load_shared_row(src + d + i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+          const float4 v = *(const float4*)(src + i);
+          const float4 w = whole_j ? *(const float4*)(src + d + i) : make_float4(0.0f, 0.0f, 0.0f, 0.0f);
           x[u][i] = v.x; x[u][i + 1] = v.y; x[u][i + 2] = v.z; x[u][i + 3] = v.w;
           comp[u][i] = w.x; comp[u][i + 1] = w.y; comp[u][i + 2] = w.z; comp[u][i + 3] = w.w;
         }
@@ -368,8 +372,9 @@ __device__ __forceinline__ void long_cluster_wg_window(
 }
 
 // ALL: seg_offsets has N + 1 entries that may be read; otherwise it may end at entry S.
+// Seven waves per SIMD are stated: left to itself the compiler takes 75 registers for bfloat16, three too many for it.
 template <typename DT, int LPR, bool ALL>
-__global__ __launch_bounds__(256) void centroid_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void centroid_kernel(
     const char* __restrict__ tokens, const int32_t* __restrict__ perm, const int32_t* __restrict__ seg_offsets,
     const int32_t* __restrict__ seg_of, const int32_t* __restrict__ num_segments, char* __restrict__ centroids,
     float* partial, uint32_t* counters, uint32_t N, uint32_t k, uint32_t cpr, uint32_t mean, uint32_t coop) {
