@@ -30,7 +30,7 @@ template <int LPR> __device__ __forceinline__ int32_t uniform(int32_t v) {
 // the segment sums, who pay more for it than this kernel would (large clusters: 375.5 -> 391.3; 32768 rows: 223.1 -> 216.5).
 inline bool streams_rows(int64_t T, uint32_t cpr) { return (uint64_t)T * cpr * 16 >= 32ull << 20; }
 
-// The same for one stretch of the rows (stretch.h): sixteen lanes to a token.
+// The token gradients (grad_tokens_kernel) of whole tokens for one stretch (stretch.h): sixteen lanes to a token.
 template <typename DT>
 __device__ __forceinline__ void grad_stretch(const char* __restrict__ grad_out, const char* __restrict__ grad_centroids,
                                              const char* __restrict__ grad_expert_out, const int32_t* __restrict__ seg_of,

@@ -95,8 +95,9 @@ __device__ __forceinline__ void row_sum_kahan(const char* __restrict__ tokens, c
 
 // Data that workgroups of one launch hand to each other, whatever XCD they run on: eight bytes at a time past the XCD's own
 // L2 (relaxed device-scope accesses).  Such a store is in memory once it is counted off (vmcnt), so "written before the
-// counter moves" is a wait and not a device-scope fence, which writes back all that the L2 holds: with two fences per block a
-// call with 64 clusters of 1024 members took 178 us, with 200 of 300 269 us, one of 65536 278 us; without 141, 173, 180.
+// counter moves" is a wait and not a device-scope fence, which writes back all that the L2 holds.  The compress call of 65536 x
+// 1024 bf16, two experts, with 64 clusters of 1024 members, 200 of 300 and one of 65536, with two fences per block: 206, 270,
+// 282 us; without 139, 171, 178.
 __device__ __forceinline__ void store_shared8(void* p, uint32_t lo, uint32_t hi) {
   __hip_atomic_store((uint64_t*)p, (uint64_t)hi << 32 | lo, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }

@@ -182,12 +182,8 @@ __global__ __launch_bounds__(256) void restore_kernel(
   }
 }
 
-// Restore fused with the gate-weighted combine of the k expert outputs of a token (Eq. 2 with gate weights):
-//     out[t] = sum_j w[t][j] * (expert_out[s_j] + (tokens[t] - centroids[s_j])),   s_j = seg_of[t*k + j],
-// accumulated in binary32 in the order j = 0..k-1 and rounded once.  One lane group per token: the token row
-// is read once, and one row is written instead of k.
-// The same for one stretch of the rows (stretch.h): sixteen lanes to a token.  The tokens' own loads go out first, the lookups
-// of all tokens and experts are made once per workgroup and not once per lane group.
+// The combine (restore_combine_kernel) of whole tokens for one stretch (stretch.h): sixteen lanes to a token.  The tokens' own
+// loads go out first, the lookups of all tokens and experts are made once per workgroup and not once per lane group.
 template <typename DT>
 __device__ __forceinline__ void combine_stretch(const char* __restrict__ tokens, const char* __restrict__ centroids,
                                                 const char* __restrict__ expert_out, const int32_t* __restrict__ seg_of,
@@ -246,6 +242,10 @@ __device__ __forceinline__ void combine_stretch(const char* __restrict__ tokens,
   }
 }
 
+// Restore fused with the gate-weighted combine of the k expert outputs of a token (Eq. 2 with gate weights):
+//     out[t] = sum_j w[t][j] * (expert_out[s_j] + (tokens[t] - centroids[s_j])),   s_j = seg_of[t*k + j],
+// accumulated in binary32 in the order j = 0..k-1 and rounded once.  One lane group per token, or sixteen lanes for each of its
+// stretches: the token row is read once, and one row is written instead of k.
 template <typename DT, int LPR>
 __global__ __launch_bounds__(256) void restore_combine_kernel(
     const char* __restrict__ tokens, const char* __restrict__ centroids, const char* __restrict__ expert_out,

@@ -83,7 +83,7 @@ int main() {
       }
       for (int k : {1, 2, 8}) {
         if (T * k > top) continue;
-        for (int pieces : {1, 3, 9, 70}) {
+        for (int pieces : {1, 3, 9, 70, 64, 128, 192}) {   // the last three may be dealt by columns
           if ((unsigned long long)T * k * pieces > 0xffffff00ull) continue;
           now_d = pieces * (dt ? 8 : 4);
           now_rows = k;
