@@ -78,16 +78,17 @@ inline StretchPlan plan_combine(int64_t T, int k, uint32_t cpr, bool bf16) {
 // Restore knows the number of clusters and has another way round: in cluster order it reads a cluster's rows once and a token's
 // once per expert, by columns the other way about, and writes the output in pieces of 256 bytes to all rows.  Measured as whole
 // steps, rows of 1 to 4 KB, 4 to 512 MB of output, two to four experts, 0.03 to 0.15 clusters per assignment (us: cluster
-// order -> columns).  It pays while all stretches of a row are dealt at the same time: 128 MB, two experts, 0.05, 0.07, 0.09,
-// 0.10, 0.14 clusters, 2 KB rows 115 -> 108, 111 -> 107, 112 -> 109, 112 -> 110, 106 -> 107; 1 KB 111 -> 106, 112 -> 107, 112 ->
-// 110, 112 -> 112, 113 -> 113; 3 KB, 0.03 and 0.09, 137 -> 139, 114 -> 122; 4 KB 153 -> 152, 118 -> 125.  And while the output stays
-// in the last-level cache of 256 MB, up to more clusters if it takes no more than half of it: 0.14, 24, 48, 64, 96, 128 MB 44.0 ->
-// 43.5, 58.3 -> 58.1, 65.9 -> 65.8, 87.3 -> 87.4, 108.3 -> 106.2 (10 hash functions 116.9 -> 115.4), with 0.2 three microseconds
-// more; 256 MB, 0.05, 0.07, 0.09, 0.11 196 -> 177, 197 -> 185, 191 -> 185, 190 -> 190; 512 MB 360 -> 359, 359 -> 371, 358 -> 381.
-// From 24 MB on: 24 MB, 0.03 and 0.09, 72.4 -> 70.5, 49.6 -> 48.6; 16 MB, 0.06 and 0.08, 55.3 -> 54.8, 45.4 -> 45.9.
+// order -> columns).  It pays where each XCD has one stretch of all tokens: 128 MB of 2 KB rows, two experts, 0.05, 0.07, 0.09,
+// 0.10, 0.14 clusters 115 -> 108, 111 -> 107, 112 -> 109, 112 -> 110, 106 -> 107.  Rows of 3 and 4 KB, 0.03 and 0.09, 137 -> 139,
+// 114 -> 122 and 153 -> 152, 118 -> 125.  Rows of 1 KB, 0.05 and 0.09, 111 -> 106, 112 -> 110, but the call by itself, with its
+// inputs in the last-level cache, 50 -> 50, 51 -> 53 (2 KB 49 -> 46, 49 -> 47) and with 256 MB 97 -> 108.  And it pays while the
+// output stays in the last-level cache of 256 MB, up to more clusters if it takes no more than half of it: 0.14, 24, 48, 64, 96,
+// 128 MB 44.0 -> 43.5, 58.3 -> 58.1, 65.9 -> 65.8, 87.3 -> 87.4, 108.3 -> 106.2 (10 hash functions 116.9 -> 115.4), with 0.2 three
+// microseconds more; 256 MB, 0.05, 0.07, 0.09, 0.11 196 -> 177, 197 -> 185, 191 -> 185, 190 -> 190; 512 MB 360 -> 359, 359 -> 371,
+// 358 -> 381.  From 24 MB on: 24 MB, 0.03 and 0.09, 72.4 -> 70.5, 49.6 -> 48.6; 16 MB, 0.06 and 0.08, 55.3 -> 54.8, 45.4 -> 45.9.
 inline StretchPlan plan_restore(int64_t N, int k, uint32_t cpr) {
   const uint64_t bytes = (uint64_t)N * cpr * 16;
-  if (k == 1 || cpr > kXcdCount * kStretchPieces || bytes < 24ull << 20 || bytes > 256ull << 20) return StretchPlan{};
+  if (k == 1 || cpr != kXcdCount * kStretchPieces || bytes < 24ull << 20 || bytes > 256ull << 20) return StretchPlan{};
   return plan_stretches(N / k, k, cpr, 0, (uint64_t)N * (bytes <= 128ull << 20 ? 15 : 9) / 100);
 }
 

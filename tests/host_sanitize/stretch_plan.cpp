@@ -147,10 +147,11 @@ static void check_rules() {
       {65536 + 1, 2, 128, 8, false},
       {6144, 2, 128, 8, true},       // 24 MB
       {6144 - 1, 2, 128, 8, false},
-      {43690, 3, 64, 8, true},
+      {8192, 3, 128, 8, true},
+      {43690, 3, 64, 8, false},      // rows that two groups of XCDs share
       // the shapes of tests/test_gpu_stretch.py
-      {16384, 2, 128, 6, true}, {16384 + 13, 3, 128, 6, true}, {8192 + 1, 4, 128, 6, true}, {12288 + 5, 2, 64, 6, true},
-      {16384, 2, 128, 10, true}, {65536 + 1, 2, 128, 6, false}, {12288 - 1, 2, 64, 6, false}, {8192 + 3, 2, 192, 6, false},
+      {16384, 2, 128, 6, true}, {16384 + 13, 3, 128, 6, true}, {8192 + 1, 4, 128, 6, true}, {12288 + 5, 2, 64, 6, false},
+      {16384, 2, 128, 10, true}, {65536 + 1, 2, 128, 6, false}, {6144 + 5, 2, 128, 6, true}, {6144 - 1, 2, 128, 6, false}, {8192 + 3, 2, 192, 6, false},
   };
   for (const auto& c : restores)
     expect(pays(plan_restore((int64_t)c.T * c.k, c.k, c.cpr), share(c.T, c.k, c.percent)) == c.restore, "restore", c.T, c.k, (int)c.cpr);
