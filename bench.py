@@ -29,7 +29,7 @@ if ROOT not in sys.path:
 HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 # HBM bytes per restore_kernel launch from rocprofv3 --pmc (FETCH_SIZE x 2.00 + WRITE_SIZE x 1.00, factors from
 # a 1 GiB calibration copy); figures and commands are kept in profiles/path_t5_hbm_traffic.txt
-MEASURED_TRAFFIC_BYTES = {("t5", "topk_logits"): 633.3e6}
+MEASURED_TRAFFIC_BYTES = {("t5", "topk_logits"): 636.1e6}
 MFMA_PEAK_TFLOPS = {"bf16": 2500.0, "f32": 157.3}
 
 
