@@ -373,9 +373,9 @@ __device__ __forceinline__ void long_cluster_wg_window(
 }
 
 // ALL: seg_offsets has N + 1 entries that may be read; otherwise it may end at entry S.
-// Seven waves per SIMD are stated: left to itself the compiler takes 75 registers for bfloat16, three too many for it.
+// Seven waves per SIMD are stated for bfloat16: left to itself the compiler takes 75 registers, three too many for it.
 template <typename DT, int LPR, bool ALL>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(7))) void centroid_kernel(
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(std::is_same<DT, BF16>::value ? 7 : 1))) void centroid_kernel(
     const char* __restrict__ tokens, const int32_t* __restrict__ perm, const int32_t* __restrict__ seg_offsets,
     const int32_t* __restrict__ seg_of, const int32_t* __restrict__ num_segments, char* __restrict__ centroids,
     float* partial, uint32_t* counters, uint32_t N, uint32_t k, uint32_t cpr, uint32_t mean, uint32_t coop) {
